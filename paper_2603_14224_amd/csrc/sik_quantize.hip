@@ -98,12 +98,15 @@ __global__ __launch_bounds__(kBlock) void colsum_kernel(const uint16_t* __restri
         }
     };
     int i = start + r;
-    for (; i + 48 < end; i += 64) {  // four independent loads in flight
-        uint4 v[4];
+    // Independent loads in flight: eight, because a small launch (8 units: two workgroups per compute unit) has too few
+    // wavefronts to cover the HBM latency with four; four with MINMAX, which at eight takes 140 registers.
+    constexpr int kLoads = MINMAX ? 4 : 8;
+    for (; i + 16 * (kLoads - 1) < end; i += 16 * kLoads) {
+        uint4 v[kLoads];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = ld_stream(&base[static_cast<size_t>(i + 16 * u) * 16 + p]);
+        for (int u = 0; u < kLoads; ++u) v[u] = ld_stream(&base[static_cast<size_t>(i + 16 * u) * 16 + p]);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) take(v[u]);
+        for (int u = 0; u < kLoads; ++u) take(v[u]);
     }
     for (; i < end; i += 16) take(base[static_cast<size_t>(i) * 16 + p]);
 #pragma unroll
@@ -140,29 +143,54 @@ __global__ __launch_bounds__(kBlock) void colsum_kernel(const uint16_t* __restri
 
 // fit step 2: mu = (sum of partials, fixed order) / L; with colmm also alpha_d = max(|max_i K_id - mu_d|,
 // |min_i K_id - mu_d|) in binary32 (= max_i |K_id - mu_d|, see colsum_kernel), 0 for an empty sequence.
-__global__ __launch_bounds__(kBlock) void mean_kernel(const double* __restrict__ colsum,
-                                                      const float* __restrict__ colmm,
-                                                      const int32_t* __restrict__ seq_len,
-                                                      float* __restrict__ mu, float* __restrict__ alpha, int Hkv,
-                                                      int Lmax, int nwg) {
-    const int unit = blockIdx.x, tid = threadIdx.x;
+// Bound by load latency (a unit's partials are a few KB): kMeanSlices threads share a channel, so that all of its at
+// most kFitMaxWg partials are requested in one round trip (one thread per channel: eight round trips; with the encoder's
+// four wavefronts and codebook_kernel's slices, keys of 1 x 8 x 32K: 58.5 -> 47.0 us for the whole fit).
+constexpr int kMeanSlices = 8;
+constexpr int kMeanPer = kFitMaxWg / kMeanSlices;  // partials a thread adds up
+__global__ __launch_bounds__(kMeanSlices * kD) void mean_kernel(const double* __restrict__ colsum,
+                                                                const float* __restrict__ colmm,
+                                                                const int32_t* __restrict__ seq_len,
+                                                                float* __restrict__ mu, float* __restrict__ alpha,
+                                                                int Hkv, int Lmax, int nwg) {
+    __shared__ double ps[kMeanSlices][kD];
+    __shared__ float plo[kMeanSlices][kD], phi[kMeanSlices][kD];
+    const int unit = blockIdx.x, d = threadIdx.x % kD, slice = threadIdx.x / kD;
     int L = seq_len[unit / Hkv];
     L = L < 0 ? 0 : (L > Lmax ? Lmax : L);
-    if (tid < kD) {
-        double s = 0.0;
-#pragma unroll 8
-        for (int w = 0; w < nwg; ++w) s += colsum[(static_cast<size_t>(unit) * kFitMaxWg + w) * kD + tid];
-        const float m = L > 0 ? static_cast<float>(s / static_cast<double>(L)) : 0.0f;
-        mu[static_cast<size_t>(unit) * kD + tid] = m;
-        if (colmm != nullptr) {
-            float lo = INFINITY, hi = -INFINITY;
-            for (int w = 0; w < nwg; ++w) {
-                const float* pm = colmm + (static_cast<size_t>(unit) * kFitMaxWg + w) * 2 * kD;
-                lo = fminf(lo, pm[tid]);
-                hi = fmaxf(hi, pm[kD + tid]);
+    const size_t slot0 = static_cast<size_t>(unit) * kFitMaxWg;
+    double s = 0.0;
+    float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < kMeanPer; ++j) {
+        const int w = slice * kMeanPer + j;
+        if (w < nwg) s += colsum[(slot0 + w) * kD + d];
+    }
+    if (colmm != nullptr) {
+#pragma unroll
+        for (int j = 0; j < kMeanPer; ++j) {
+            const int w = slice * kMeanPer + j;
+            if (w < nwg) {
+                lo = fminf(lo, colmm[(slot0 + w) * 2 * kD + d]);
+                hi = fmaxf(hi, colmm[(slot0 + w) * 2 * kD + kD + d]);
             }
-            alpha[static_cast<size_t>(unit) * kD + tid] = L > 0 ? fmaxf(fabsf(hi - m), fabsf(lo - m)) : 0.0f;
         }
+    }
+    ps[slice][d] = s;
+    plo[slice][d] = lo;
+    phi[slice][d] = hi;
+    __syncthreads();
+    if (slice == 0) {
+#pragma unroll
+        for (int x = 1; x < kMeanSlices; ++x) {
+            s += ps[x][d];
+            lo = fminf(lo, plo[x][d]);
+            hi = fmaxf(hi, phi[x][d]);
+        }
+        const float m = L > 0 ? static_cast<float>(s / static_cast<double>(L)) : 0.0f;
+        mu[static_cast<size_t>(unit) * kD + d] = m;
+        if (colmm != nullptr)
+            alpha[static_cast<size_t>(unit) * kD + d] = L > 0 ? fmaxf(fabsf(hi - m), fabsf(lo - m)) : 0.0f;
     }
 }
 
@@ -176,10 +204,12 @@ __global__ __launch_bounds__(kBlock) void mean_kernel(const double* __restrict__
 // tabc[Code][lane] (the count), always on the lane's own banks - so they are updated with plain
 // read-add-write in token order: no atomics (LDS float atomics ran this kernel at 0.4 TB/s) and a
 // sum order that does not depend on scheduling.  Workgroup partials go to part[unit][wg][g][80].
-constexpr int kEncThreads = 128;                 // two wavefronts
-constexpr int kEncEntries = 16 * 5;              // per group: 16 codes x (4 sums + count)
-constexpr int kEncTokPerIter = kEncThreads / 32;  // tokens the two encoding wavefronts take per step
+constexpr int kEncEntries = 16 * 5;  // per group: 16 codes x (4 sums + count)
 constexpr int kEncUnroll = 16;
+// NW encoding wavefronts per workgroup, two tokens each per step.  A lane's token costs one LDS round trip, so what
+// counts is how many encoding wavefronts a compute unit holds; their accumulators (20 KB each) allow eight.  Two per
+// workgroup reach that with four workgroups; launches of too few workgroups for that take four (encoder_waves).
+constexpr int kEncWavesMin = 2;
 
 // The encoder's per-lane state and token step, shared by encode_kernel and compress_kernel.
 template <int DT, bool CLUSTER>
@@ -220,14 +250,15 @@ struct SignEncoder {
 };
 
 // Workgroup partial of the cluster sums: part[g][code][4 sums, count] from the accumulator columns of the
-// encoding wavefronts (waves 0 and 1 of the workgroup); called by `nthreads` threads after a barrier.
+// NW encoding wavefronts (the first of the workgroup); called by `nthreads` threads after a barrier.
+template <int NW>
 __device__ __forceinline__ void publish_cluster_partial(const float4* tabs, const float* tabc, float* pw, int tid,
                                                         int nthreads) {
     for (int e = tid; e < kG * kEncEntries; e += nthreads) {
         const int gg = e / kEncEntries, ent = e % kEncEntries, code = ent / 5, comp = ent % 5;
         float sum = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kEncThreads / kWave; ++w) {
+        for (int w = 0; w < NW; ++w) {
             const int at = (w * 16 + code) * kWave + gg;
             sum += comp < 4 ? reinterpret_cast<const float*>(&tabs[at])[comp] +
                                   reinterpret_cast<const float*>(&tabs[at + 32])[comp]
@@ -237,17 +268,18 @@ __device__ __forceinline__ void publish_cluster_partial(const float4* tabs, cons
     }
 }
 
-template <int DT, bool CLUSTER>
-__global__ __launch_bounds__(kEncThreads) void encode_kernel(const uint16_t* __restrict__ K,
-                                                             const int32_t* __restrict__ seq_len, int t0, int n,
-                                                             const float* __restrict__ mu,
-                                                             uint8_t* __restrict__ codes,
-                                                             float* __restrict__ part, int Hkv, int Lmax,
-                                                             int nwg) {
-    __shared__ float4 tabs[CLUSTER ? (kEncThreads / kWave) * 16 * kWave : 1];  // [wave][code][lane]: 4 sums
-    __shared__ float tabc[CLUSTER ? (kEncThreads / kWave) * 16 * kWave : 1];    // [wave][code][lane]: count
+template <int DT, bool CLUSTER, int NW>
+__global__ __launch_bounds__(NW * kWave) void encode_kernel(const uint16_t* __restrict__ K,
+                                                            const int32_t* __restrict__ seq_len, int t0, int n,
+                                                            const float* __restrict__ mu,
+                                                            uint8_t* __restrict__ codes,
+                                                            float* __restrict__ part, int Hkv, int Lmax,
+                                                            int nwg) {
+    constexpr int kEncTokPerIter = 2 * NW;
+    __shared__ float4 tabs[CLUSTER ? NW * 16 * kWave : 1];  // [wave][code][lane]: 4 sums
+    __shared__ float tabc[CLUSTER ? NW * 16 * kWave : 1];    // [wave][code][lane]: count
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int g = lane & 31, sub = wv * 2 + (lane >> 5);  // sub: which of the 4 tokens of a step
+    const int g = lane & 31, sub = wv * 2 + (lane >> 5);  // sub: which token of a step
     const int unit = blockIdx.x / nwg, wg = blockIdx.x % nwg;
     int lo, hi;
     if constexpr (CLUSTER) {
@@ -296,8 +328,8 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const uint16_t* __r
     }
     if constexpr (CLUSTER) {
         __syncthreads();
-        publish_cluster_partial(tabs, tabc, part + (static_cast<size_t>(unit) * kFitMaxWg + wg) * kG * kEncEntries, tid,
-                                kEncThreads);
+        publish_cluster_partial<NW>(tabs, tabc, part + (static_cast<size_t>(unit) * kFitMaxWg + wg) * kG * kEncEntries,
+                                    tid, NW * kWave);
     }
 }
 
@@ -305,24 +337,24 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const uint16_t* __r
 // sweep over K and V (sections "One-Pass Sign-Based Clustering" and "Token-Wise Quantization Format").  The two
 // jobs want different things from the machine - the cluster sums are chains of dependent LDS updates that need
 // few instructions, the records are some 80 vector instructions per row and no LDS - so one workgroup runs both
-// side by side: wavefronts 0 and 1 encode (one lane = one sign group of a token, as in encode_kernel), wavefronts
-// 2 to 5 build records (16 lanes = one row, as in quantize_kv_kernel).  Both sides walk the workgroup's token range
+// side by side: the first NW wavefronts encode (one lane = one sign group of a token, as in encode_kernel), four
+// more build records (16 lanes = one row, as in quantize_kv_kernel).  Both sides walk the workgroup's token range
 // in blocks of kCmpBlock tokens and meet at a barrier after every block, so that the second reader of a key row
 // finds it in the L2 cache: HBM sees K once here and V once.  (Measured on 4 x 8 x 64K keys: without the barrier
 // 10 % slower; 64-token blocks need more registers than three workgroups per compute unit leave; the launch bound
 // of five wavefronts per SIMD, 102 registers, beats six, which spills.)
-constexpr int kCmpThreads = kEncThreads + 4 * kWave;
-constexpr int kCmpBlock = 32;       // tokens per block: 8 steps of the encoders, 2 steps of the record builders
-constexpr int kCmpEncSteps = kCmpBlock / kEncTokPerIter;
+constexpr int kCmpBlock = 32;  // tokens per block: 16 / NW steps of the encoders, 2 steps of the record builders
 constexpr int kCmpRecSteps = kCmpBlock / 16;
 
-template <int DT>
-__global__ __launch_bounds__(kCmpThreads, 5) void compress_kernel(
+template <int DT, int NW>
+__global__ __launch_bounds__((NW + 4) * kWave, NW == 2 ? 5 : 4) void compress_kernel(
     const uint16_t* __restrict__ K, const uint16_t* __restrict__ V, const int32_t* __restrict__ seq_len,
     const float* __restrict__ mu, const float* __restrict__ alpha, uint8_t* __restrict__ codes,
     float* __restrict__ part, uint2* __restrict__ rec, int Hkv, int Lmax, int nwg) {
-    __shared__ float4 tabs[(kEncThreads / kWave) * 16 * kWave];
-    __shared__ float tabc[(kEncThreads / kWave) * 16 * kWave];
+    constexpr int kEncTokPerIter = 2 * NW;
+    constexpr int kCmpEncSteps = kCmpBlock / kEncTokPerIter;
+    __shared__ float4 tabs[NW * 16 * kWave];
+    __shared__ float tabc[NW * 16 * kWave];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int unit = blockIdx.x / nwg, wg = blockIdx.x % nwg;
     int L = seq_len[unit / Hkv];
@@ -334,7 +366,7 @@ __global__ __launch_bounds__(kCmpThreads, 5) void compress_kernel(
     const int end = min(L, start + chunk);
     const int last = end - 1;
     const size_t row0 = static_cast<size_t>(unit) * Lmax;
-    if (wv < kEncThreads / kWave) {
+    if (wv < NW) {
         // ---- encoders
         const int g = lane & 31, sub = wv * 2 + (lane >> 5);
         const uint2* base = reinterpret_cast<const uint2*>(K + row0 * kD);
@@ -366,7 +398,7 @@ __global__ __launch_bounds__(kCmpThreads, 5) void compress_kernel(
         }
     } else {
         // ---- record builders
-        const int p = lane & 15, r = (lane >> 4) + 4 * (wv - kEncThreads / kWave);  // row of a 16-row step
+        const int p = lane & 15, r = (lane >> 4) + 4 * (wv - NW);  // row of a 16-row step
         const uint4* Kb = reinterpret_cast<const uint4*>(K + row0 * kD);
         const uint4* Vb = reinterpret_cast<const uint4*>(V + row0 * kD);
         float m[8], a[8];
@@ -400,24 +432,42 @@ __global__ __launch_bounds__(kCmpThreads, 5) void compress_kernel(
         }
     }
     __syncthreads();
-    publish_cluster_partial(tabs, tabc, part + (static_cast<size_t>(unit) * kFitMaxWg + wg) * kG * kEncEntries, tid,
-                            kCmpThreads);
+    publish_cluster_partial<NW>(tabs, tabc, part + (static_cast<size_t>(unit) * kFitMaxWg + wg) * kG * kEncEntries, tid,
+                                (NW + 4) * kWave);
 }
 
 // fit step 4: centroid = (sum of the workgroup partials, fixed order, fp64) / member count; empty -> 0.
-// Grid = units x 2; thread = one (group, code) entry.
+// Bound by load latency like mean_kernel: kCbSlices threads share one (group, code) entry and each requests its at most
+// kFitMaxWg / kCbSlices partials at once.  Grid = units x kG * 16 / kCbEntries.
+constexpr int kCbSlices = 8;
+constexpr int kCbPer = kFitMaxWg / kCbSlices;
+constexpr int kCbEntries = kBlock / kCbSlices;
+constexpr int kCbBlocks = kG * 16 / kCbEntries;  // workgroups per unit
 __global__ __launch_bounds__(kBlock) void codebook_kernel(const float* __restrict__ part, int nwg,
                                                           int32_t* __restrict__ counts,
                                                           float* __restrict__ codebook) {
-    const size_t unit = blockIdx.x >> 1;
-    const int e = (blockIdx.x & 1) * kBlock + threadIdx.x;  // e = g * 16 + code
+    __shared__ double ps[kCbSlices][5][kCbEntries];
+    const size_t unit = blockIdx.x / kCbBlocks;
+    const int x = threadIdx.x % kCbEntries, slice = threadIdx.x / kCbEntries;
+    const int e = (blockIdx.x % kCbBlocks) * kCbEntries + x;  // e = g * 16 + code
     double s[5] = {0, 0, 0, 0, 0};
     const float* p = part + (unit * kFitMaxWg * kG * 16 + e) * 5;
-#pragma unroll 4
-    for (int w = 0; w < nwg; ++w) {
 #pragma unroll
-        for (int c = 0; c < 5; ++c) s[c] += static_cast<double>(p[static_cast<size_t>(w) * kG * 16 * 5 + c]);
+    for (int j = 0; j < kCbPer; ++j) {
+        const int w = slice * kCbPer + j;
+        if (w < nwg) {
+#pragma unroll
+            for (int c = 0; c < 5; ++c) s[c] += static_cast<double>(p[static_cast<size_t>(w) * kG * 16 * 5 + c]);
+        }
     }
+#pragma unroll
+    for (int c = 0; c < 5; ++c) ps[slice][c][x] = s[c];
+    __syncthreads();
+    if (slice != 0) return;
+#pragma unroll
+    for (int y = 1; y < kCbSlices; ++y)
+#pragma unroll
+        for (int c = 0; c < 5; ++c) s[c] += ps[y][c][x];
     const int32_t cnt = static_cast<int32_t>(s[4] + 0.5);
     counts[unit * kG * 16 + e] = cnt;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -435,6 +485,11 @@ static int fit_workgroups(const Dims& d) {
     const int by_len = (d.Lmax + 255) / 256;  // at least 256 rows per workgroup
     return nwg < by_len ? nwg : (by_len < 1 ? 1 : by_len);
 }
+
+// Encoding wavefronts per workgroup of a fit: four where two would leave a compute unit with fewer than the eight that
+// its LDS holds (fewer than four workgroups each).  Both entry points that fit go by it, so that their sums agree bit
+// for bit.
+static int encoder_waves(int workgroups) { return workgroups < 1024 ? 2 * kEncWavesMin : kEncWavesMin; }
 
 hipError_t launch_prep(const Dims& d, const Workspace& w, const void* k_new, const void* v_new, void* K,
                        void* V, int32_t* seq_len, const float* mu, uint8_t* codes, hipStream_t s) {
@@ -468,17 +523,19 @@ hipError_t launch_fit(const Dims& d, const Workspace& w, const void* K, const vo
         e = launch_kernel(bf ? colsum_kernel<kBF16, false> : colsum_kernel<kF16, false>, units * nwg, kBlock, s, Kp,
                           seq_len, w.colsum, nullptr, d.Hkv, d.Lmax, nwg);
     if (e != hipSuccess) return e;
-    e = launch_kernel(mean_kernel, units, kBlock, s, w.colsum, V ? w.colmm : nullptr, seq_len, mu, alpha, d.Hkv,
+    e = launch_kernel(mean_kernel, units, kMeanSlices * kD, s, w.colsum, V ? w.colmm : nullptr, seq_len, mu, alpha, d.Hkv,
                       d.Lmax, nwg);
     if (e != hipSuccess) return e;
-    if (V)
-        e = launch_kernel(bf ? compress_kernel<kBF16> : compress_kernel<kF16>, units * nwg, kCmpThreads, s, Kp, Vp,
-                          seq_len, mu, alpha, codes, w.cpart, rp, d.Hkv, d.Lmax, nwg);
-    else
-        e = launch_kernel(bf ? encode_kernel<kBF16, true> : encode_kernel<kF16, true>, units * nwg, kEncThreads, s,
-                          Kp, seq_len, 0, 0, mu, codes, w.cpart, d.Hkv, d.Lmax, nwg);
+    const int nw = encoder_waves(units * nwg);
+#define SIK_FIT(NWV)                                                                                               \
+    V ? launch_kernel(bf ? compress_kernel<kBF16, NWV> : compress_kernel<kF16, NWV>, units * nwg, (NWV + 4) * kWave, s, \
+                      Kp, Vp, seq_len, mu, alpha, codes, w.cpart, rp, d.Hkv, d.Lmax, nwg)                           \
+      : launch_kernel(bf ? encode_kernel<kBF16, true, NWV> : encode_kernel<kF16, true, NWV>, units * nwg,           \
+                      NWV * kWave, s, Kp, seq_len, 0, 0, mu, codes, w.cpart, d.Hkv, d.Lmax, nwg)
+    e = nw == kEncWavesMin ? (SIK_FIT(kEncWavesMin)) : (SIK_FIT(2 * kEncWavesMin));
+#undef SIK_FIT
     if (e != hipSuccess) return e;
-    return launch_kernel(codebook_kernel, units * 2, kBlock, s, w.cpart, nwg, counts, codebook);
+    return launch_kernel(codebook_kernel, units * kCbBlocks, kBlock, s, w.cpart, nwg, counts, codebook);
 }
 
 hipError_t launch_encode(const Dims& d, const void* K, int t0, int n, const float* mu, uint8_t* codes,
@@ -488,8 +545,9 @@ hipError_t launch_encode(const Dims& d, const void* K, int t0, int n, const floa
     const int cap = 2048 / d.units() < 1 ? 1 : 2048 / d.units();
     if (nwg > cap) nwg = cap;
     auto Kp = static_cast<const uint16_t*>(K);
-    return launch_kernel(d.kv_dtype == kBF16 ? encode_kernel<kBF16, false> : encode_kernel<kF16, false>,
-                         d.units() * nwg, kEncThreads, s, Kp, nullptr, t0, n, mu, codes, nullptr, d.Hkv, d.Lmax, nwg);
+    return launch_kernel(d.kv_dtype == kBF16 ? encode_kernel<kBF16, false, kEncWavesMin>
+                                             : encode_kernel<kF16, false, kEncWavesMin>,
+                         d.units() * nwg, kEncWavesMin * kWave, s, Kp, nullptr, t0, n, mu, codes, nullptr, d.Hkv, d.Lmax, nwg);
 }
 
 }  // namespace sik
