@@ -228,8 +228,7 @@ int sik_topk(const sik_layout* layout, const float* scores, const int32_t* seq_l
     rc = check_ws(d, k, workspace, workspace_bytes, &w);
     if (rc) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipError_t e = launch_prep(d, w, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, s);
-    if (e == hipSuccess) e = launch_topk_hist(d, w, scores, seq_len, s);
+    hipError_t e = launch_topk_hist(d, w, scores, seq_len, s);
     if (e == hipSuccess) e = launch_select(d, w, false, scores, seq_len, k, idx, s);
     return launched(e);
 }

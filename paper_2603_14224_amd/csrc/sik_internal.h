@@ -24,9 +24,8 @@ struct Workspace {
     size_t zero_words;      // its length in 32-bit words
     uint32_t* sync;         // one-launch decode step: status word and self-clearing counters (sik_workspace_init)
     uint32_t* counters;     // [rows][8]  0 index-output reservation, 1 candidate count (stand-alone selector),
-                            //            2 select ticket, 3 attention / fused ticket, 4 ~min key (stand-alone
-                            //            top-k) or candidate-pool reservation (fused kernel), 5 max key
-                            //            (stand-alone top-k), 7 of a sequence's first head: heads finished
+                            //            2 select ticket, 3 attention / fused ticket, 4 candidate-pool
+                            //            reservation (fused kernel), 7 of a sequence's first head: heads finished
     // plain scratch
     uint32_t* parthist;     // [rows][nchunk][kBins/2]  per-chunk histograms, two 16-bit counts per word
     float* binp;            // [rows][2]          histogram origin, scale
@@ -36,7 +35,8 @@ struct Workspace {
                             // stand-alone selector; for the fused kernel per row [33][4 * nchunk] words of
                             // wavefront regions, then per row an overflow pool of [kCandCap][2] words
     int32_t* idx;           // [rows][k]          selection when the caller passes no idx_out
-    float* partial;         // [rows][kMaxSplit][D + 2]  split softmax partials (m, l, o[D])
+    float* partial;         // [rows][kMaxSplit][D + 2]  split softmax partials (m, l, o[D]); stand-alone top-k:
+                            //      (min, max) key of each chunk
     float* scores;          // [rows][sstride]    decode step only
     int sstride;            // Lmax rounded up to a multiple of 4 (16-byte aligned score rows)
     // quantiser fit
