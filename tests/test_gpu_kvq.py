@@ -417,6 +417,52 @@ def test_prefill_compress_equals_the_separate_calls_and_the_oracle(oracle, dtype
         assert not got[b, :, L:].any() and not codes2[b, :, L:].any()
 
 
+@pytest.mark.parametrize("batch,lens", [(1, [16]), (1, [257]), (1, [16385]), (42, [8195, 8100, 0]), (43, [6145, 1, 5000])])
+def test_fit_partials_and_encoder_widths(oracle, batch, lens):
+    # 1 to 64 partials per unit, below and above the 1024 workgroups where the encoders go from four wavefronts to two
+    # (3 units per sequence, at least 256 rows per workgroup: 42 x 3 x 16 and 43 x 3 x 15 are above, the others below)
+    B, H, cap = batch, 3, max(lens)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(cap)
+    lens = [lens[b % len(lens)] for b in range(B)]
+    lay = sik.make_layout(B, H, 6, 128, cap, torch.bfloat16, torch.bfloat16)
+    K, V = (torch.randn(B, H, cap, 128, generator=gen, device="cuda").add_(0.7).to(torch.bfloat16) for _ in range(2))
+    dsl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    ws = sik.alloc_workspace(lay, 16)
+    res = []
+    for one_call in (False, True):
+        mu, al = torch.zeros(B, H, 128, device="cuda"), torch.zeros(B, H, 128, device="cuda")
+        cb = torch.zeros(B, H, 32, 16, 4, device="cuda")
+        cnt = torch.zeros(B, H, 32, 16, dtype=torch.int32, device="cuda")
+        codes, rec = torch.zeros(B, H, cap, 16, dtype=torch.uint8, device="cuda"), sik.alloc_kvq(lay)
+        if one_call:
+            sik.sik_prefill_compress(lay, K, V, dsl, mu, cb, cnt, codes, al, rec, ws)
+        else:
+            sik.sik_quantize_keys(lay, K, dsl, 0, 0, sik.SIK_Q_FIT, mu, cb, cnt, codes, ws)
+        res.append((mu, cb, cnt, codes))
+    sync()
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
+    mu, cb, cnt, codes = (x.cpu().numpy() for x in res[0])
+    for b in {0, 1 % B, 2 % B, B - 1}:
+        n = lens[b]
+        x = K[b, :, :n].cpu().double().numpy()
+        m = (x.sum(1) / n if n else np.zeros((H, 128))).astype(np.float32)
+        assert np.array_equal(mu[b], m)
+        sign = x >= m[:, None]
+        assert np.array_equal(codes[b, :, :n], np.packbits(sign, axis=-1))
+        code = (sign.reshape(H, n, 32, 4) * [8, 4, 2, 1]).sum(-1)
+        y = (x - m[:, None].astype(np.float64)).reshape(H, n, 32, 4)
+        for c in range(16):
+            hit = code == c
+            want = hit.sum(1)
+            assert np.array_equal(cnt[b, :, :, c], want)
+            mean = (y * hit[..., None]).sum(1) / np.maximum(want, 1)[..., None]
+            # binary32 sums of at most 2048 differences of one sign: each addition rounds by 2^-24 of the running sum
+            peak = (np.abs(y) * hit[..., None]).sum(1) / np.maximum(want, 1)[..., None]
+            assert (np.abs(cb[b, :, :, c] - mean) <= 2050 * 2.0 ** -24 * peak + 1e-30).all()
+
+
 def test_prefill_compress_argument_errors():
     lay = sik.make_layout(1, 2, 4, 128, 512, torch.bfloat16)
     ws = sik.alloc_workspace(lay, 0)
