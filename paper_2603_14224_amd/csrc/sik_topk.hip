@@ -17,11 +17,11 @@ namespace sik {
 
 SIK_TL_DEFINE(sik_dbg_tl_topk)
 
-constexpr int kSelChunkMax = 4096;  // scores scanned per select workgroup (bounds its LDS list)
+constexpr int kSelChunkMax = 4096;  // scores scanned per select workgroup (16 per thread, in registers)
 
 // ---- stand-alone level 1, pass A: min and max of the order-preserving keys of each chunk ----
 // Also clears the counters of its row for the kernels that follow (chunk 0), so that no launch has to do it first (scoring,
-// top-k and attention of 2 x 32 heads x 20000 as separate calls: 39.5 -> 35.9 us).
+// top-k and attention of 2 x 32 heads x 20000 as separate calls: 39.7 -> 35.9 us, 34.5 with select_kernel's ballots).
 __global__ __launch_bounds__(kBlock) void minmax_kernel(const float* __restrict__ scores,
                                                         const int32_t* __restrict__ seq_len,
                                                         uint32_t* __restrict__ counters,
@@ -107,17 +107,14 @@ __global__ __launch_bounds__(kBlock) void select_kernel(
     const float* __restrict__ scores, const int32_t* __restrict__ seq_len, const uint32_t* __restrict__ parthist,
     const float* __restrict__ binp, int sstride, int Hq, int Lmax, int chunk, int hchunk, uint32_t chunks,
     uint32_t* __restrict__ counters, uint32_t* __restrict__ cand, int32_t* __restrict__ idx, int k) {
-    // 17 KB of LDS per workgroup, so that eight of them fit a compute unit: the selected tokens are kept as 16-bit
-    // offsets into the chunk, and the candidate list shares its storage with the histogram staging of
-    // find_threshold (dead after the barrier that follows it).
-    static_assert(kSelChunkMax <= 65536, "16-bit chunk offsets");
+    // The candidate list shares its storage with the histogram staging of find_threshold (dead after the barrier that
+    // follows it).
     static_assert((kBlock / kWave) * kBins <= 2 * kCandCap + 16, "the staging area fits the candidate list");
     __shared__ uint32_t h256[kBlock];
-    __shared__ uint16_t l_sel[kSelChunkMax];
     __shared__ __align__(8) uint32_t red[2 * kCandCap + 16];
     uint32_t* const l_cand = red;
     __shared__ int s_flag, sthr[3];
-    __shared__ uint32_t s_nsel, s_ncand, s_base[2], sh[4];
+    __shared__ uint32_t wsel[kBlock / kWave], s_ncand, s_base[2], sh[4];
 
     SIK_TL(8);
     const int hchunks = chunks & 0xffffu, nchunk = chunks >> 16;
@@ -132,21 +129,27 @@ __global__ __launch_bounds__(kBlock) void select_kernel(
 
     // threshold bin of this query head from the chunk histograms of the producing kernel
     const float lo = binp[row * 2], scale = binp[row * 2 + 1];
-    if (tid == 0) {
-        s_nsel = 0u;
-        s_ncand = 0u;
-    }
+    if (tid == 0) s_ncand = 0u;
     const int hact = L > 0 ? (L + hchunk - 1) / hchunk : 1;  // chunks the producer ran for this sequence
-    // the first 4096 scores of the chunk (all of them: chunks are at most kSelChunkMax long) are requested
-    // together with the histograms, one round trip for both
-    const bool vec = (sstride & 3) == 0;  // rows are 16-byte aligned: vector loads
-    const float4* s4 = reinterpret_cast<const float4*>(s);
-    const int q0 = start >> 2, q1 = (end + 3) >> 2;  // start is a multiple of 256
-    float4 v[4];
+    // all scores of the chunk (at most kSelChunkMax) are requested together with the histograms, one round trip for
+    // both: kPer per thread, score x of this thread is token(x)
+    constexpr int kPer = kSelChunkMax / kBlock;
+    const bool vec = (sstride & 3) == 0;  // rows are 16-byte aligned (start is a multiple of 256): vector loads
+    auto token = [&](int x) {
+        return vec ? start + ((x >> 2) * kBlock + tid) * 4 + (x & 3) : start + x * kBlock + tid;
+    };
+    float v[kPer];
+    if (vec) {
+        const float4* s4 = reinterpret_cast<const float4*>(s);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int qi = q0 + j * kBlock + tid;
-        v[j] = (vec && qi < q1) ? s4[qi] : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int j = 0; j < kPer / 4; ++j) {
+            const int i = token(4 * j);
+            const float4 f = i < end ? s4[i >> 2] : make_float4(0.f, 0.f, 0.f, 0.f);
+            v[4 * j] = f.x, v[4 * j + 1] = f.y, v[4 * j + 2] = f.z, v[4 * j + 3] = f.w;
+        }
+    } else {
+#pragma unroll
+        for (int x = 0; x < kPer; ++x) v[x] = token(x) < end ? s[token(x)] : 0.0f;
     }
     const HistLoads hl = load_chunk_hists(parthist + static_cast<size_t>(row) * hchunks * kHistWords, hact);
     const Threshold th = find_threshold(hl, kk, L, red, sh, sthr);
@@ -155,50 +158,53 @@ __global__ __launch_bounds__(kBlock) void select_kernel(
     __syncthreads();
     SIK_TL(9);
 
-    auto classify = [&](float x, int i) {
-        const int bin = bstar < 0 ? 0 : score_bin(x, lo, scale);
-        if (bin > bstar) {
-            l_sel[atomicAdd(&s_nsel, 1u)] = static_cast<uint16_t>(i - start);
-        } else if (bin == bstar && ranked) {
+    // Selected scores become bits of a mask and their places follow from five ballots over the lanes' counts; a counter
+    // in LDS per selected score cost a round trip for nearly every one of the kPer scores, as some lane of the 64 has a
+    // selected one (2 x 32 heads x 20000, top 1000: 11.1 -> 9.9 us).  Candidates are rare and keep their counter.
+    uint32_t smask = 0u;
+#pragma unroll
+    for (int x = 0; x < kPer; ++x) {
+        const int i = token(x);
+        const int bin = bstar < 0 ? 0 : score_bin(v[x], lo, scale);
+        const bool in = i < end;
+        smask |= (in && bin > bstar ? 1u : 0u) << x;
+        if (in && bin == bstar && ranked) {
             const uint32_t pos = atomicAdd(&s_ncand, 1u);
             if (pos < static_cast<uint32_t>(kCandCap)) {
-                l_cand[2 * pos] = float_to_key(x);
+                l_cand[2 * pos] = float_to_key(v[x]);
                 l_cand[2 * pos + 1] = static_cast<uint32_t>(i);
             }
         }
-    };
-    if (vec) {
-        for (int base = q0; base < q1; base += 4 * kBlock) {
-            if (base != q0) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int qi = base + j * kBlock + tid;
-                    v[j] = qi < q1 ? s4[qi] : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = (base + j * kBlock + tid) * 4;
-                if (i < end) classify(v[j].x, i);
-                if (i + 1 < end) classify(v[j].y, i + 1);
-                if (i + 2 < end) classify(v[j].z, i + 2);
-                if (i + 3 < end) classify(v[j].w, i + 3);
-            }
-        }
-    } else {
-#pragma unroll 4
-        for (int i = start + tid; i < end; i += kBlock) classify(s[i], i);
     }
+    static_assert(kPer < 32, "a lane's count has five bits");
+    const int lane = tid & 63, wv = tid >> 6;
+    const uint32_t mine = static_cast<uint32_t>(__popc(smask));
+    uint32_t at = 0u, wtot = 0u;  // selected in the lanes below, in the wavefront
+#pragma unroll
+    for (int e = 0; e < 5; ++e) {
+        const uint64_t bal = __ballot((mine >> e) & 1u);
+        at += static_cast<uint32_t>(__popcll(bal & ((1ull << lane) - 1ull))) << e;
+        wtot += static_cast<uint32_t>(__popcll(bal)) << e;
+    }
+    if (lane == 0) wsel[wv] = wtot;
     __syncthreads();
     SIK_TL(10);
-    if (tid == 0) {
-        s_base[0] = s_nsel ? atomic_add_u32(&counters[row * 8 + 0], s_nsel) : 0u;
-        s_base[1] = s_ncand ? atomic_add_u32(&counters[row * 8 + 1], s_ncand) : 0u;
+    uint32_t nsel = 0u;
+#pragma unroll
+    for (int w = 0; w < kBlock / kWave; ++w) {
+        at += w < wv ? wsel[w] : 0u;
+        nsel += wsel[w];
     }
+    // the two reservations of the workgroup from two wavefronts: both round trips at once
+    if (tid == 0) s_base[0] = nsel ? atomic_add_u32(&counters[row * 8 + 0], nsel) : 0u;
+    if (tid == kWave) s_base[1] = s_ncand ? atomic_add_u32(&counters[row * 8 + 1], s_ncand) : 0u;
     __syncthreads();
-    for (uint32_t j = tid; j < s_nsel; j += kBlock) {
-        const uint32_t pos = s_base[0] + j;
-        if (pos < static_cast<uint32_t>(k)) out[pos] = start + static_cast<int32_t>(l_sel[j]);
+    at += s_base[0];
+    while (smask != 0u) {
+        const int x = __ffs(static_cast<int>(smask)) - 1;
+        smask &= smask - 1u;
+        if (at < static_cast<uint32_t>(k)) out[at] = token(x);
+        ++at;
     }
     const uint32_t ncand = min(s_ncand, static_cast<uint32_t>(kCandCap));
     uint32_t* crow = cand + static_cast<size_t>(row) * kCandCap * 2;

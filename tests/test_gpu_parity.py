@@ -160,6 +160,22 @@ def test_topk_random_scores(oracle, L, k):
             assert sorted(got[b, h].tolist()) == sorted(ref[b, h].tolist())
 
 
+@pytest.mark.parametrize("Lmax", [4096, 4097, 8195, 12288])
+def test_topk_chunk_edges_and_both_load_forms(oracle, Lmax):
+    # rows of a multiple of four scores are read as vectors, others one by one; lengths around a lane's, a wavefront's and
+    # a chunk's share, with nothing, one, nearly all and all of the row selected; one row with many scores of minus infinity and of the lowest value.
+    # Equal fp32 scores on both sides: the sets must be identical.
+    rng = np.random.default_rng(Lmax)
+    lens = [1, 3, 5, 255, 257, 1025, 4095, Lmax]
+    s = rng.normal(size=(len(lens), 2, Lmax)).astype(np.float32)
+    s[:, 1, ::5] = -np.inf
+    s[:, 1, 1::5] = np.finfo(np.float32).min
+    for k in (1, 200, 4094, Lmax):
+        got = run_topk(s, lens, k)
+        ref = oracle.topk(s.astype(np.float64), np.asarray(lens, np.int32), k)
+        assert np.array_equal(np.sort(got, -1), np.sort(ref, -1)), k
+
+
 def test_topk_ties_and_degenerate_rows(oracle):
     rng = np.random.default_rng(77)
     L, k = 6000, 200
