@@ -170,8 +170,7 @@ __global__ __launch_bounds__(kBlock) void attn_q2_shared_kernel(
     const int32_t* __restrict__ idx, uint32_t dims0, uint32_t dims1, int k, int Lmax, int per, int nblk,
     float scale_log2e, uint32_t* __restrict__ counters, float* __restrict__ partial, void* __restrict__ out) {
     constexpr int NH = kSharedHeads;
-    __shared__ float sm[kBlock / kWave], sl[kBlock / kWave];
-    __shared__ float sacc[kBlock / kWave][kD];
+    __shared__ MergeLds<NH> lds;
     __shared__ int s_flag;
 
     const int Hkv = dims0 & 0xffffu, Hq = dims0 >> 16, R = dims1 & 0xffffu, nsplit = dims1 >> 16;
@@ -205,30 +204,19 @@ __global__ __launch_bounds__(kBlock) void attn_q2_shared_kernel(
     const int j0 = sp * per, j1 = min(k, j0 + per);
     attend_list_q2_multi<NH>([&](int j) { return ip[j0 + j]; }, j1 - j0, wv * 16, (kBlock / kWave) * 16, rp, qa,
                              scale_log2e, Lmax, st);
-    float M[NH], Lsum[NH], o[NH];
-#pragma unroll
-    for (int x = 0; x < NH; ++x) {
-        workgroup_merge(st[x], sm, sl, sacc, M[x], Lsum[x], o[x]);
-        __syncthreads();  // the LDS staging is reused by the next head
-    }
-    if (nsplit == 1) {
-#pragma unroll
-        for (int x = 0; x < NH; ++x)
-            if (x < nh && tid < kD)
-                store_out<ODT>(out, (row0 + x) * kD + tid, Lsum[x] > 0.0f ? o[x] / Lsum[x] : 0.0f);
-        return;
-    }
-#pragma unroll
-    for (int x = 0; x < NH; ++x) {
-        if (x < nh && tid < kD) {
-            float* pp = partial + ((row0 + x) * kMaxSplit + sp) * kPartStride;
-            st_agent(&pp[2 + tid], o[x]);
-            if (tid == 0) {
-                st_agent(&pp[0], M[x]);
-                st_agent(&pp[1], Lsum[x]);
-            }
+    workgroup_merge_multi<NH>(st, nh, lds, [&](int x, int d, float M, float Lsum, float o) {
+        if (nsplit == 1) {
+            store_out<ODT>(out, (row0 + x) * kD + d, Lsum > 0.0f ? o / Lsum : 0.0f);
+            return;
         }
-    }
+        float* pp = partial + ((row0 + x) * kMaxSplit + sp) * kPartStride;
+        st_agent(&pp[2 + d], o);
+        if (d == 0) {
+            st_agent(&pp[0], M);
+            st_agent(&pp[1], Lsum);
+        }
+    });
+    if (nsplit == 1) return;
     if (!last_arriver(&counters[row0 * 8 + 3], static_cast<uint32_t>(nsplit), &s_flag)) return;
     // two heads at a time: threads 0..127 and 128..255 each take a channel of one head
     for (int x = tid >> 7; x < nh; x += kBlock / kD)
