@@ -348,12 +348,19 @@ static int decode_step_impl(const sik_layout* layout, const void* q, const void*
     }
     const int q_sum = opt.group_shared ? d.R : 1;
     // Large launches select once per KV head with the stand-alone selector and let the attention kernels read that
-    // list (measured on 32 x 8 KV heads x 16K: 83 against 86 us; on 4 x 8 x 64K with 8:1 GQA: 57 against 71 us);
-    // small ones, and everything that needs the fused kernel's extras, go through the fused kernel, where the R
-    // query heads of a group each classify the shared scores (32K context, one sequence: 20 against 26 us).
+    // list; small ones, and everything that needs the fused kernel's extras, go through the fused kernel, where the R
+    // query heads of a group each classify the shared scores and gather the same rows (32K context, one sequence: 19
+    // against 29 us).  The line: the fused launch has more workgroups than a chip of 256 compute units holds (four
+    // each), or so many rows that the classification is mostly repeated.  Measured, selector against fused, 16-bit
+    // rows / 2-bit records: 4 x 8 x 64K with 8:1 GQA, 1536 selected (2048 workgroups) 47 / 47 against 54 / 63 us;
+    // 4 x 8 x 20000 with 8:1, 400 selected (1280) 28 / 28 against 31 / 32; 16 x 8 x 6000 with 5:1 (1280) 29 / 30
+    // against 42 / 38; 32 x 8 x 4096 with 4:1 (1024 rows) 29 / 33 against 41 / 36; below it 4 x 8 x 32K with 8:1, 600
+    // selected (1024 workgroups, 256 rows) 33 / 33 against 30 / 36.  An appended row costs the selector a launch of
+    // its own: those go by the number of keys alone.
     const bool plain = opt.n == 0 && opt.k_per_mille == 0 && !(kvq && k_new);
-    const bool shared_unfused =
-        opt.group_shared && (!fused || (plain && static_cast<int64_t>(d.units()) * d.Lmax > (2 << 20)));
+    const bool many = !k_new && d.R > 1 && (static_cast<int64_t>(fchunks) * d.rows() > 1024 || d.rows() >= 1024);
+    const bool shared_unfused = opt.group_shared &&
+        (!fused || (plain && (many || static_cast<int64_t>(d.units()) * d.Lmax > (2 << 20))));
     hipError_t e = hipSuccess;
     // One launch for the whole step whenever the plain step's grid fits the compute units (sik_step.hip): scores
     // stay in registers, chunks of a head exchange only histograms, partials and threshold-bin candidates.

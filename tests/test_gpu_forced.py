@@ -382,6 +382,17 @@ def test_shared_selection_beyond_the_fused_plan(oracle):
     check_attention(out.cpu().numpy().astype(np.float64), ref, True)
 
 
+@pytest.mark.parametrize("batch,n_kv,R,L,append", [(16, 8, 5, 2100, False),   # 1920 fused workgroups
+                                                   (43, 6, 4, 1000, False),   # 1032 rows
+                                                   (43, 6, 4, 1000, True),    # the same with an append: fused
+                                                   (128, 8, 1, 300, False)])  # one query head per KV head: fused
+@pytest.mark.parametrize("q2", [False, True])
+def test_shared_selection_on_both_sides_of_the_workgroup_line(oracle, batch, n_kv, R, L, append, q2):
+    cfg = cfg_small("C2", batch=batch, n_kv_heads=n_kv, n_q_heads=n_kv * R, context=L, top_k=70)
+    lens = [L - 37 * (b % 5) if b % 7 else b % 3 for b in range(batch)]
+    run_shared(oracle, cfg, L + 4, steps=1, append=append and not q2, q2=q2, seq_len=lens)
+
+
 @pytest.mark.parametrize("R,q2", [(5, False), (4, True), (6, True)])
 def test_shared_selection_large_launch_gathers_once(oracle, R, q2):
     # above 2 M keys the plain shared step selects once per KV head and the attention kernel feeds each gathered
