@@ -143,18 +143,22 @@ __global__ __launch_bounds__(kBlock) void colsum_kernel(const uint16_t* __restri
 
 // fit step 2: mu = (sum of partials, fixed order) / L; with colmm also alpha_d = max(|max_i K_id - mu_d|,
 // |min_i K_id - mu_d|) in binary32 (= max_i |K_id - mu_d|, see colsum_kernel), 0 for an empty sequence.
-// Bound by load latency (a unit's partials are a few KB): kMeanSlices threads share a channel, so that all of its at
+// Bound by load latency (a unit's partials are a few KB): S threads share a channel, so that all of its at
 // most kFitMaxWg partials are requested in one round trip (one thread per channel: eight round trips; with the encoder's
 // four wavefronts and codebook_kernel's slices, keys of 1 x 8 x 32K: 58.5 -> 47.0 us for the whole fit).
-constexpr int kMeanSlices = 8;
-constexpr int kMeanPer = kFitMaxWg / kMeanSlices;  // partials a thread adds up
-__global__ __launch_bounds__(kMeanSlices * kD) void mean_kernel(const double* __restrict__ colsum,
-                                                                const float* __restrict__ colmm,
-                                                                const int32_t* __restrict__ seq_len,
-                                                                float* __restrict__ mu, float* __restrict__ alpha,
-                                                                int Hkv, int Lmax, int nwg) {
-    __shared__ double ps[kMeanSlices][kD];
-    __shared__ float plo[kMeanSlices][kD], phi[kMeanSlices][kD];
+// Many units have few partials each: up to 2 * kSlicePartials of them take two slices, as the six idle ones of eight cost
+// more than they give there (152 units of 276 to 1104 keys: 35.8 -> 33.9 us for the fit; 144 units of 3641 to 14563:
+// 159.9 -> 158.5).  Every count adds up in the same order.
+constexpr int kSlicePartials = 8;  // partials a thread adds up
+constexpr int kSlicesMax = kFitMaxWg / kSlicePartials;
+template <int S>
+__global__ __launch_bounds__(S * kD) void mean_kernel(const double* __restrict__ colsum,
+                                                      const float* __restrict__ colmm,
+                                                      const int32_t* __restrict__ seq_len,
+                                                      float* __restrict__ mu, float* __restrict__ alpha,
+                                                      int Hkv, int Lmax, int nwg) {
+    __shared__ double ps[S][kD];
+    __shared__ float plo[S][kD], phi[S][kD];
     const int unit = blockIdx.x, d = threadIdx.x % kD, slice = threadIdx.x / kD;
     int L = seq_len[unit / Hkv];
     L = L < 0 ? 0 : (L > Lmax ? Lmax : L);
@@ -162,14 +166,14 @@ __global__ __launch_bounds__(kMeanSlices * kD) void mean_kernel(const double* __
     double s = 0.0;
     float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < kMeanPer; ++j) {
-        const int w = slice * kMeanPer + j;
+    for (int j = 0; j < kSlicePartials; ++j) {
+        const int w = slice * kSlicePartials + j;
         if (w < nwg) s += colsum[(slot0 + w) * kD + d];
     }
     if (colmm != nullptr) {
 #pragma unroll
-        for (int j = 0; j < kMeanPer; ++j) {
-            const int w = slice * kMeanPer + j;
+        for (int j = 0; j < kSlicePartials; ++j) {
+            const int w = slice * kSlicePartials + j;
             if (w < nwg) {
                 lo = fminf(lo, colmm[(slot0 + w) * 2 * kD + d]);
                 hi = fmaxf(hi, colmm[(slot0 + w) * 2 * kD + kD + d]);
@@ -182,7 +186,7 @@ __global__ __launch_bounds__(kMeanSlices * kD) void mean_kernel(const double* __
     __syncthreads();
     if (slice == 0) {
 #pragma unroll
-        for (int x = 1; x < kMeanSlices; ++x) {
+        for (int x = 1; x < S; ++x) {
             s += ps[x][d];
             lo = fminf(lo, plo[x][d]);
             hi = fmaxf(hi, phi[x][d]);
@@ -208,7 +212,7 @@ constexpr int kEncEntries = 16 * 5;  // per group: 16 codes x (4 sums + count)
 constexpr int kEncUnroll = 16;
 // NW encoding wavefronts per workgroup, two tokens each per step.  A lane's token costs one LDS round trip, so what
 // counts is how many encoding wavefronts a compute unit holds; their accumulators (20 KB each) allow eight.  Two per
-// workgroup reach that with four workgroups; launches of too few workgroups for that take four (encoder_waves).
+// workgroup reach that with four workgroups; launches of at most two per compute unit take four (encoder_waves).
 constexpr int kEncWavesMin = 2;
 
 // The encoder's per-lane state and token step, shared by encode_kernel and compress_kernel.
@@ -437,24 +441,23 @@ __global__ __launch_bounds__((NW + 4) * kWave, NW == 2 ? 5 : 4) void compress_ke
 }
 
 // fit step 4: centroid = (sum of the workgroup partials, fixed order, fp64) / member count; empty -> 0.
-// Bound by load latency like mean_kernel: kCbSlices threads share one (group, code) entry and each requests its at most
-// kFitMaxWg / kCbSlices partials at once.  Grid = units x kG * 16 / kCbEntries.
-constexpr int kCbSlices = 8;
-constexpr int kCbPer = kFitMaxWg / kCbSlices;
-constexpr int kCbEntries = kBlock / kCbSlices;
-constexpr int kCbBlocks = kG * 16 / kCbEntries;  // workgroups per unit
+// Bound by load latency like mean_kernel: S threads share one (group, code) entry and each requests its at most
+// kSlicePartials partials at once.  Grid = units x codebook_blocks(S).
+constexpr int codebook_blocks(int slices) { return kG * 16 * slices / kBlock; }  // workgroups per unit
+template <int S>
 __global__ __launch_bounds__(kBlock) void codebook_kernel(const float* __restrict__ part, int nwg,
                                                           int32_t* __restrict__ counts,
                                                           float* __restrict__ codebook) {
-    __shared__ double ps[kCbSlices][5][kCbEntries];
+    constexpr int kCbEntries = kBlock / S, kCbBlocks = codebook_blocks(S);
+    __shared__ double ps[S][5][kCbEntries];
     const size_t unit = blockIdx.x / kCbBlocks;
     const int x = threadIdx.x % kCbEntries, slice = threadIdx.x / kCbEntries;
     const int e = (blockIdx.x % kCbBlocks) * kCbEntries + x;  // e = g * 16 + code
     double s[5] = {0, 0, 0, 0, 0};
     const float* p = part + (unit * kFitMaxWg * kG * 16 + e) * 5;
 #pragma unroll
-    for (int j = 0; j < kCbPer; ++j) {
-        const int w = slice * kCbPer + j;
+    for (int j = 0; j < kSlicePartials; ++j) {
+        const int w = slice * kSlicePartials + j;
         if (w < nwg) {
 #pragma unroll
             for (int c = 0; c < 5; ++c) s[c] += static_cast<double>(p[static_cast<size_t>(w) * kG * 16 * 5 + c]);
@@ -465,7 +468,7 @@ __global__ __launch_bounds__(kBlock) void codebook_kernel(const float* __restric
     __syncthreads();
     if (slice != 0) return;
 #pragma unroll
-    for (int y = 1; y < kCbSlices; ++y)
+    for (int y = 1; y < S; ++y)
 #pragma unroll
         for (int c = 0; c < 5; ++c) s[c] += ps[y][c][x];
     const int32_t cnt = static_cast<int32_t>(s[4] + 0.5);
@@ -486,10 +489,11 @@ static int fit_workgroups(const Dims& d) {
     return nwg < by_len ? nwg : (by_len < 1 ? 1 : by_len);
 }
 
-// Encoding wavefronts per workgroup of a fit: four where two would leave a compute unit with fewer than the eight that
-// its LDS holds (fewer than four workgroups each).  Both entry points that fit go by it, so that their sums agree bit
-// for bit.
-static int encoder_waves(int workgroups) { return workgroups < 1024 ? 2 * kEncWavesMin : kEncWavesMin; }
+// Encoding wavefronts per workgroup of a fit: four where the launch has at most two workgroups per compute unit, which
+// then hold the eight that the LDS allows.  Above that the 80 KB of a workgroup with four leave the third one waiting
+// (7 x 4 units of 1842 to 7370 tokens into records, 812 workgroups: 55.7 us with four, 48.4 with two).  Both entry
+// points that fit go by it, so that their sums agree bit for bit.
+static int encoder_waves(int workgroups) { return workgroups <= 512 ? 2 * kEncWavesMin : kEncWavesMin; }
 
 hipError_t launch_prep(const Dims& d, const Workspace& w, const void* k_new, const void* v_new, void* K,
                        void* V, int32_t* seq_len, const float* mu, uint8_t* codes, hipStream_t s) {
@@ -523,8 +527,9 @@ hipError_t launch_fit(const Dims& d, const Workspace& w, const void* K, const vo
         e = launch_kernel(bf ? colsum_kernel<kBF16, false> : colsum_kernel<kF16, false>, units * nwg, kBlock, s, Kp,
                           seq_len, w.colsum, nullptr, d.Hkv, d.Lmax, nwg);
     if (e != hipSuccess) return e;
-    e = launch_kernel(mean_kernel, units, kMeanSlices * kD, s, w.colsum, V ? w.colmm : nullptr, seq_len, mu, alpha, d.Hkv,
-                      d.Lmax, nwg);
+    const bool few = nwg <= 2 * kSlicePartials;
+    e = launch_kernel(few ? mean_kernel<2> : mean_kernel<kSlicesMax>, units, (few ? 2 : kSlicesMax) * kD, s, w.colsum,
+                      V ? w.colmm : nullptr, seq_len, mu, alpha, d.Hkv, d.Lmax, nwg);
     if (e != hipSuccess) return e;
     const int nw = encoder_waves(units * nwg);
 #define SIK_FIT(NWV)                                                                                               \
@@ -535,7 +540,8 @@ hipError_t launch_fit(const Dims& d, const Workspace& w, const void* K, const vo
     e = nw == kEncWavesMin ? (SIK_FIT(kEncWavesMin)) : (SIK_FIT(2 * kEncWavesMin));
 #undef SIK_FIT
     if (e != hipSuccess) return e;
-    return launch_kernel(codebook_kernel, units * kCbBlocks, kBlock, s, w.cpart, nwg, counts, codebook);
+    return launch_kernel(few ? codebook_kernel<2> : codebook_kernel<kSlicesMax>,
+                         units * codebook_blocks(few ? 2 : kSlicesMax), kBlock, s, w.cpart, nwg, counts, codebook);
 }
 
 hipError_t launch_encode(const Dims& d, const void* K, int t0, int n, const float* mu, uint8_t* codes,
