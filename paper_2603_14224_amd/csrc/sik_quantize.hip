@@ -144,8 +144,8 @@ __global__ __launch_bounds__(kBlock) void colsum_kernel(const uint16_t* __restri
 // fit step 2: mu = (sum of partials, fixed order) / L; with colmm also alpha_d = max(|max_i K_id - mu_d|,
 // |min_i K_id - mu_d|) in binary32 (= max_i |K_id - mu_d|, see colsum_kernel), 0 for an empty sequence.
 // Bound by load latency (a unit's partials are a few KB): S threads share a channel, so that all of its at
-// most kFitMaxWg partials are requested in one round trip (one thread per channel: eight round trips; with the encoder's
-// four wavefronts and codebook_kernel's slices, keys of 1 x 8 x 32K: 58.5 -> 47.0 us for the whole fit).
+// most kFitMaxWg partials are requested in one round trip (one thread per channel: eight round trips; with
+// codebook_kernel's slices and colsum_kernel's loads, keys of 1 x 8 x 32K: 58.6 -> 54.0 us for the whole fit).
 // Many units have few partials each: up to 2 * kSlicePartials of them take two slices, as the six idle ones of eight cost
 // more than they give there (152 units of 276 to 1104 keys: 35.8 -> 33.9 us for the fit; 144 units of 3641 to 14563:
 // 159.9 -> 158.5).  Every count adds up in the same order.
@@ -208,12 +208,14 @@ __global__ __launch_bounds__(S * kD) void mean_kernel(const double* __restrict__
 // tabc[Code][lane] (the count), always on the lane's own banks - so they are updated with plain
 // read-add-write in token order: no atomics (LDS float atomics ran this kernel at 0.4 TB/s) and a
 // sum order that does not depend on scheduling.  Workgroup partials go to part[unit][wg][g][80].
-constexpr int kEncEntries = 16 * 5;  // per group: 16 codes x (4 sums + count)
+// Two wavefronts encode whatever the launch, two tokens each per step, so that the four chains in which a workgroup's
+// sums are added up, and with them the bits of the codebook, do not depend on the launch (eight chains, from four
+// wavefronts in launches of two workgroups per compute unit, moved centroids by an ulp and with them the tokens that
+// later steps select; keys of 1 x 8 x 32K took 47.0 us with them, 54.0 with four).
+constexpr int kEncThreads = 128;
+constexpr int kEncEntries = 16 * 5;              // per group: 16 codes x (4 sums + count)
+constexpr int kEncTokPerIter = kEncThreads / 32;  // tokens the two encoding wavefronts take per step
 constexpr int kEncUnroll = 16;
-// NW encoding wavefronts per workgroup, two tokens each per step.  A lane's token costs one LDS round trip, so what
-// counts is how many encoding wavefronts a compute unit holds; their accumulators (20 KB each) allow eight.  Two per
-// workgroup reach that with four workgroups; launches of at most two per compute unit take four (encoder_waves).
-constexpr int kEncWavesMin = 2;
 
 // The encoder's per-lane state and token step, shared by encode_kernel and compress_kernel.
 template <int DT, bool CLUSTER>
@@ -254,15 +256,14 @@ struct SignEncoder {
 };
 
 // Workgroup partial of the cluster sums: part[g][code][4 sums, count] from the accumulator columns of the
-// NW encoding wavefronts (the first of the workgroup); called by `nthreads` threads after a barrier.
-template <int NW>
+// encoding wavefronts (waves 0 and 1 of the workgroup); called by `nthreads` threads after a barrier.
 __device__ __forceinline__ void publish_cluster_partial(const float4* tabs, const float* tabc, float* pw, int tid,
                                                         int nthreads) {
     for (int e = tid; e < kG * kEncEntries; e += nthreads) {
         const int gg = e / kEncEntries, ent = e % kEncEntries, code = ent / 5, comp = ent % 5;
         float sum = 0.0f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
+        for (int w = 0; w < kEncThreads / kWave; ++w) {
             const int at = (w * 16 + code) * kWave + gg;
             sum += comp < 4 ? reinterpret_cast<const float*>(&tabs[at])[comp] +
                                   reinterpret_cast<const float*>(&tabs[at + 32])[comp]
@@ -272,18 +273,17 @@ __device__ __forceinline__ void publish_cluster_partial(const float4* tabs, cons
     }
 }
 
-template <int DT, bool CLUSTER, int NW>
-__global__ __launch_bounds__(NW * kWave) void encode_kernel(const uint16_t* __restrict__ K,
-                                                            const int32_t* __restrict__ seq_len, int t0, int n,
-                                                            const float* __restrict__ mu,
-                                                            uint8_t* __restrict__ codes,
-                                                            float* __restrict__ part, int Hkv, int Lmax,
-                                                            int nwg) {
-    constexpr int kEncTokPerIter = 2 * NW;
-    __shared__ float4 tabs[CLUSTER ? NW * 16 * kWave : 1];  // [wave][code][lane]: 4 sums
-    __shared__ float tabc[CLUSTER ? NW * 16 * kWave : 1];    // [wave][code][lane]: count
+template <int DT, bool CLUSTER>
+__global__ __launch_bounds__(kEncThreads) void encode_kernel(const uint16_t* __restrict__ K,
+                                                             const int32_t* __restrict__ seq_len, int t0, int n,
+                                                             const float* __restrict__ mu,
+                                                             uint8_t* __restrict__ codes,
+                                                             float* __restrict__ part, int Hkv, int Lmax,
+                                                             int nwg) {
+    __shared__ float4 tabs[CLUSTER ? (kEncThreads / kWave) * 16 * kWave : 1];  // [wave][code][lane]: 4 sums
+    __shared__ float tabc[CLUSTER ? (kEncThreads / kWave) * 16 * kWave : 1];    // [wave][code][lane]: count
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int g = lane & 31, sub = wv * 2 + (lane >> 5);  // sub: which token of a step
+    const int g = lane & 31, sub = wv * 2 + (lane >> 5);  // sub: which of the 4 tokens of a step
     const int unit = blockIdx.x / nwg, wg = blockIdx.x % nwg;
     int lo, hi;
     if constexpr (CLUSTER) {
@@ -332,8 +332,8 @@ __global__ __launch_bounds__(NW * kWave) void encode_kernel(const uint16_t* __re
     }
     if constexpr (CLUSTER) {
         __syncthreads();
-        publish_cluster_partial<NW>(tabs, tabc, part + (static_cast<size_t>(unit) * kFitMaxWg + wg) * kG * kEncEntries,
-                                    tid, NW * kWave);
+        publish_cluster_partial(tabs, tabc, part + (static_cast<size_t>(unit) * kFitMaxWg + wg) * kG * kEncEntries, tid,
+                                kEncThreads);
     }
 }
 
@@ -341,24 +341,24 @@ __global__ __launch_bounds__(NW * kWave) void encode_kernel(const uint16_t* __re
 // sweep over K and V (sections "One-Pass Sign-Based Clustering" and "Token-Wise Quantization Format").  The two
 // jobs want different things from the machine - the cluster sums are chains of dependent LDS updates that need
 // few instructions, the records are some 80 vector instructions per row and no LDS - so one workgroup runs both
-// side by side: the first NW wavefronts encode (one lane = one sign group of a token, as in encode_kernel), four
-// more build records (16 lanes = one row, as in quantize_kv_kernel).  Both sides walk the workgroup's token range
+// side by side: wavefronts 0 and 1 encode (one lane = one sign group of a token, as in encode_kernel), wavefronts
+// 2 to 5 build records (16 lanes = one row, as in quantize_kv_kernel).  Both sides walk the workgroup's token range
 // in blocks of kCmpBlock tokens and meet at a barrier after every block, so that the second reader of a key row
 // finds it in the L2 cache: HBM sees K once here and V once.  (Measured on 4 x 8 x 64K keys: without the barrier
 // 10 % slower; 64-token blocks need more registers than three workgroups per compute unit leave; the launch bound
 // of five wavefronts per SIMD, 102 registers, beats six, which spills.)
-constexpr int kCmpBlock = 32;  // tokens per block: 16 / NW steps of the encoders, 2 steps of the record builders
+constexpr int kCmpThreads = kEncThreads + 4 * kWave;
+constexpr int kCmpBlock = 32;       // tokens per block: 8 steps of the encoders, 2 steps of the record builders
+constexpr int kCmpEncSteps = kCmpBlock / kEncTokPerIter;
 constexpr int kCmpRecSteps = kCmpBlock / 16;
 
-template <int DT, int NW>
-__global__ __launch_bounds__((NW + 4) * kWave, NW == 2 ? 5 : 4) void compress_kernel(
+template <int DT>
+__global__ __launch_bounds__(kCmpThreads, 5) void compress_kernel(
     const uint16_t* __restrict__ K, const uint16_t* __restrict__ V, const int32_t* __restrict__ seq_len,
     const float* __restrict__ mu, const float* __restrict__ alpha, uint8_t* __restrict__ codes,
     float* __restrict__ part, uint2* __restrict__ rec, int Hkv, int Lmax, int nwg) {
-    constexpr int kEncTokPerIter = 2 * NW;
-    constexpr int kCmpEncSteps = kCmpBlock / kEncTokPerIter;
-    __shared__ float4 tabs[NW * 16 * kWave];
-    __shared__ float tabc[NW * 16 * kWave];
+    __shared__ float4 tabs[(kEncThreads / kWave) * 16 * kWave];
+    __shared__ float tabc[(kEncThreads / kWave) * 16 * kWave];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int unit = blockIdx.x / nwg, wg = blockIdx.x % nwg;
     int L = seq_len[unit / Hkv];
@@ -370,7 +370,7 @@ __global__ __launch_bounds__((NW + 4) * kWave, NW == 2 ? 5 : 4) void compress_ke
     const int end = min(L, start + chunk);
     const int last = end - 1;
     const size_t row0 = static_cast<size_t>(unit) * Lmax;
-    if (wv < NW) {
+    if (wv < kEncThreads / kWave) {
         // ---- encoders
         const int g = lane & 31, sub = wv * 2 + (lane >> 5);
         const uint2* base = reinterpret_cast<const uint2*>(K + row0 * kD);
@@ -402,7 +402,7 @@ __global__ __launch_bounds__((NW + 4) * kWave, NW == 2 ? 5 : 4) void compress_ke
         }
     } else {
         // ---- record builders
-        const int p = lane & 15, r = (lane >> 4) + 4 * (wv - NW);  // row of a 16-row step
+        const int p = lane & 15, r = (lane >> 4) + 4 * (wv - kEncThreads / kWave);  // row of a 16-row step
         const uint4* Kb = reinterpret_cast<const uint4*>(K + row0 * kD);
         const uint4* Vb = reinterpret_cast<const uint4*>(V + row0 * kD);
         float m[8], a[8];
@@ -436,8 +436,8 @@ __global__ __launch_bounds__((NW + 4) * kWave, NW == 2 ? 5 : 4) void compress_ke
         }
     }
     __syncthreads();
-    publish_cluster_partial<NW>(tabs, tabc, part + (static_cast<size_t>(unit) * kFitMaxWg + wg) * kG * kEncEntries, tid,
-                                (NW + 4) * kWave);
+    publish_cluster_partial(tabs, tabc, part + (static_cast<size_t>(unit) * kFitMaxWg + wg) * kG * kEncEntries, tid,
+                            kCmpThreads);
 }
 
 // fit step 4: centroid = (sum of the workgroup partials, fixed order, fp64) / member count; empty -> 0.
@@ -489,12 +489,6 @@ static int fit_workgroups(const Dims& d) {
     return nwg < by_len ? nwg : (by_len < 1 ? 1 : by_len);
 }
 
-// Encoding wavefronts per workgroup of a fit: four where the launch has at most two workgroups per compute unit, which
-// then hold the eight that the LDS allows.  Above that the 80 KB of a workgroup with four leave the third one waiting
-// (7 x 4 units of 1842 to 7370 tokens into records, 812 workgroups: 55.7 us with four, 48.4 with two).  Both entry
-// points that fit go by it, so that their sums agree bit for bit.
-static int encoder_waves(int workgroups) { return workgroups <= 512 ? 2 * kEncWavesMin : kEncWavesMin; }
-
 hipError_t launch_prep(const Dims& d, const Workspace& w, const void* k_new, const void* v_new, void* K,
                        void* V, int32_t* seq_len, const float* mu, uint8_t* codes, hipStream_t s) {
     int nzb = static_cast<int>((w.zero_words / 4 + kBlock * 4 - 1) / (kBlock * 4));
@@ -531,14 +525,12 @@ hipError_t launch_fit(const Dims& d, const Workspace& w, const void* K, const vo
     e = launch_kernel(few ? mean_kernel<2> : mean_kernel<kSlicesMax>, units, (few ? 2 : kSlicesMax) * kD, s, w.colsum,
                       V ? w.colmm : nullptr, seq_len, mu, alpha, d.Hkv, d.Lmax, nwg);
     if (e != hipSuccess) return e;
-    const int nw = encoder_waves(units * nwg);
-#define SIK_FIT(NWV)                                                                                               \
-    V ? launch_kernel(bf ? compress_kernel<kBF16, NWV> : compress_kernel<kF16, NWV>, units * nwg, (NWV + 4) * kWave, s, \
-                      Kp, Vp, seq_len, mu, alpha, codes, w.cpart, rp, d.Hkv, d.Lmax, nwg)                           \
-      : launch_kernel(bf ? encode_kernel<kBF16, true, NWV> : encode_kernel<kF16, true, NWV>, units * nwg,           \
-                      NWV * kWave, s, Kp, seq_len, 0, 0, mu, codes, w.cpart, d.Hkv, d.Lmax, nwg)
-    e = nw == kEncWavesMin ? (SIK_FIT(kEncWavesMin)) : (SIK_FIT(2 * kEncWavesMin));
-#undef SIK_FIT
+    if (V)
+        e = launch_kernel(bf ? compress_kernel<kBF16> : compress_kernel<kF16>, units * nwg, kCmpThreads, s, Kp, Vp,
+                          seq_len, mu, alpha, codes, w.cpart, rp, d.Hkv, d.Lmax, nwg);
+    else
+        e = launch_kernel(bf ? encode_kernel<kBF16, true> : encode_kernel<kF16, true>, units * nwg, kEncThreads, s,
+                          Kp, seq_len, 0, 0, mu, codes, w.cpart, d.Hkv, d.Lmax, nwg);
     if (e != hipSuccess) return e;
     return launch_kernel(few ? codebook_kernel<2> : codebook_kernel<kSlicesMax>,
                          units * codebook_blocks(few ? 2 : kSlicesMax), kBlock, s, w.cpart, nwg, counts, codebook);
@@ -551,9 +543,8 @@ hipError_t launch_encode(const Dims& d, const void* K, int t0, int n, const floa
     const int cap = 2048 / d.units() < 1 ? 1 : 2048 / d.units();
     if (nwg > cap) nwg = cap;
     auto Kp = static_cast<const uint16_t*>(K);
-    return launch_kernel(d.kv_dtype == kBF16 ? encode_kernel<kBF16, false, kEncWavesMin>
-                                             : encode_kernel<kF16, false, kEncWavesMin>,
-                         d.units() * nwg, kEncWavesMin * kWave, s, Kp, nullptr, t0, n, mu, codes, nullptr, d.Hkv, d.Lmax, nwg);
+    return launch_kernel(d.kv_dtype == kBF16 ? encode_kernel<kBF16, false> : encode_kernel<kF16, false>,
+                         d.units() * nwg, kEncThreads, s, Kp, nullptr, t0, n, mu, codes, nullptr, d.Hkv, d.Lmax, nwg);
 }
 
 }  // namespace sik

@@ -465,6 +465,52 @@ def test_fit_partials_and_encoder_widths(oracle, batch, lens):
             assert (np.abs(cb[b, :, :, c] - mean) <= 2050 * 2.0 ** -24 * peak + 1e-30).all()
 
 
+def fit_sums_reference(x, mu, nwg):
+    """Cluster sums of one (sequence, KV head) in the library's order of additions, x [n, 128] the keys and mu [128] the
+    means, both binary32: a workgroup's token range is walked by four chains (token mod 4) that add K - mu in binary32 in
+    token order, the chains join as (0 + 1) + (2 + 3), the workgroups in binary64."""
+    n = x.shape[0]
+    code = ((x >= mu).reshape(n, 32, 4) * [8, 4, 2, 1]).sum(-1)
+    y = (x - mu).reshape(n, 32, 1, 4)
+    masked = np.where((code[:, :, None] == np.arange(16))[..., None], y, np.float32(0))
+    chunk = -(-(-(-n // nwg)) // 4) * 4
+    total = np.zeros((32, 16, 4))
+    for start in range(0, n, chunk):
+        end = min(n, start + chunk)
+        c = [np.cumsum(masked[start + j:end:4], axis=0, dtype=np.float32)[-1] if start + j < end
+             else np.zeros((32, 16, 4), np.float32) for j in range(4)]
+        total += ((c[0] + c[1]) + (c[2] + c[3])).astype(np.float64)
+    return total
+
+
+@pytest.mark.parametrize("one_call", [False, True])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("units,n", [(1, 3), (3, 257), (2, 2055), (40, 1030)])
+def test_codebook_bits_follow_from_the_stated_order_of_additions(units, n, dtype, one_call):
+    # a codebook decides which tokens later steps select: it must not move by an ulp with the shape of a launch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(units * n)
+    lay = sik.make_layout(1, units, units, 128, n, dtype, dtype)
+    K, V = (torch.randn(1, units, n, 128, generator=gen, device="cuda").add_(0.3).to(dtype) for _ in range(2))
+    dsl = torch.tensor([n], dtype=torch.int32, device="cuda")
+    mu, al = torch.zeros(1, units, 128, device="cuda"), torch.zeros(1, units, 128, device="cuda")
+    cb = torch.zeros(1, units, 32, 16, 4, device="cuda")
+    cnt = torch.zeros(1, units, 32, 16, dtype=torch.int32, device="cuda")
+    codes = torch.zeros(1, units, n, 16, dtype=torch.uint8, device="cuda")
+    ws = sik.alloc_workspace(lay, 0)
+    if one_call:
+        sik.sik_prefill_compress(lay, K, V, dsl, mu, cb, cnt, codes, al, sik.alloc_kvq(lay), ws)
+    else:
+        sik.sik_quantize_keys(lay, K, dsl, 0, 0, sik.SIK_Q_FIT, mu, cb, cnt, codes, ws)
+    sync()
+    nwg = min(2048 // units, 64, -(-n // 256))
+    for h in {0, units - 1}:
+        m, c = mu[0, h].cpu().numpy(), cnt[0, h].cpu().numpy()
+        s = fit_sums_reference(K[0, h].cpu().float().numpy(), m, nwg)
+        want = np.where(c[..., None] > 0, s / np.maximum(c, 1)[..., None], 0.0).astype(np.float32)
+        assert np.array_equal(cb[0, h].cpu().numpy(), want)
+
+
 def test_prefill_compress_argument_errors():
     lay = sik.make_layout(1, 2, 4, 128, 512, torch.bfloat16)
     ws = sik.alloc_workspace(lay, 0)
