@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace sik {
 
 constexpr int kD = 128;           // head_dim the kernels are specialised for
@@ -212,6 +214,22 @@ __device__ __forceinline__ float row16_sum(float v) {
     v += row_ror<2>(v);
     v += row_ror<1>(v);
     return v;
+}
+
+// Sum over the 64 lanes of a wavefront; every lane gets the total.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+    auto ror = [](uint32_t x, auto n) {
+        return static_cast<uint32_t>(
+            __builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x120 + decltype(n)::value, 0xf, 0xf, false));
+    };
+    v += ror(v, std::integral_constant<int, 8>{});
+    v += ror(v, std::integral_constant<int, 4>{});
+    v += ror(v, std::integral_constant<int, 2>{});
+    v += ror(v, std::integral_constant<int, 1>{});
+    uint32_t t = 0u;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) t += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 16 * r));
+    return t;
 }
 
 }  // namespace sik

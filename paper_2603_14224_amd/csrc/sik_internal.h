@@ -23,8 +23,7 @@ struct Workspace {
     uint32_t* zero_begin;   // start of the zero-initialised region
     size_t zero_words;      // its length in 32-bit words
     uint32_t* sync;         // one-launch decode step: status word and self-clearing counters (sik_workspace_init)
-    uint32_t* counters;     // [rows][8]  0 index-output reservation, 1 candidate count (stand-alone selector),
-                            //            2 select ticket, 3 attention / fused ticket, 4 candidate-pool
+    uint32_t* counters;     // [rows][8]  0 index-output reservation (fused kernel), 2 select ticket, 3 attention / fused ticket, 4 candidate-pool
                             //            reservation (fused kernel), 7 of a sequence's first head: heads finished
     // plain scratch
     uint32_t* parthist;     // [rows][nchunk][kBins/2]  per-chunk histograms, two 16-bit counts per word
@@ -119,7 +118,6 @@ void score_plan(const Dims& d, int* nhb, int* nchunk, int* chunk);
 bool score_plan_ok(const Dims& d);
 void hist_plan(const Dims& d, int* nchunk, int* chunk);
 bool hist_plan_ok(const Dims& d);
-void select_plan(const Dims& d, int* nchunk, int* chunk);
 // hist_from_score: the chunk histograms come from the scoring kernel (else from launch_topk_hist)
 hipError_t launch_select(const Dims& d, const Workspace& w, bool hist_from_score, const float* scores,
                          const int32_t* seq_len, int k, int32_t* idx, hipStream_t s);

@@ -27,7 +27,8 @@ __device__ __forceinline__ void publish_hist(const uint32_t* lhist, uint32_t* pa
     part[t] = lhist[2 * t] | (lhist[2 * t + 1] << 16);
 }
 
-// Inclusive suffix sum over the 256 threads of the workgroup (thread t gets sum over u >= t).
+// Inclusive suffix sum over the first 256 threads of a workgroup of NT (thread t gets sum over u >= t); all call.
+template <int NT = kBlock>
 __device__ __forceinline__ uint32_t block_suffix_sum(uint32_t v, uint32_t* lds4) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -35,7 +36,7 @@ __device__ __forceinline__ uint32_t block_suffix_sum(uint32_t v, uint32_t* lds4)
         const uint32_t up = static_cast<uint32_t>(__shfl_down(static_cast<int>(v), o, 64));
         if (lane + o < 64) v += up;
     }
-    if (lane == 0) lds4[wv] = v;
+    if (lane == 0 && (NT == kBlock || wv < kBlock / kWave)) lds4[wv] = v;
     __syncthreads();
 #pragma unroll
     for (int w = 1; w < kBlock / kWave; ++w)
@@ -67,8 +68,37 @@ __device__ __forceinline__ HistLoads load_chunk_hists(const uint32_t* part_row, 
     return h;
 }
 
-// Called by all threads: add the chunk histograms up and find the bin where the count from the
+// The same with the chunks before chunk c also added up on their own, for the first four wavefronts of a workgroup of
+// any size; the others get zeros.
+struct PlacedHistLoads {
+    HistLoads all, before;
+};
+__device__ __forceinline__ PlacedHistLoads load_chunk_hists_before(const uint32_t* part_row, int nact, int c) {
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    PlacedHistLoads h;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) h.all.cnt[e] = h.before.cnt[e] = 0u;
+    if (wv >= kBlock / kWave) return h;
+    const uint4* p4 = reinterpret_cast<const uint4*>(part_row);
+#pragma unroll 8
+    for (int cc = wv; cc < nact; cc += kBlock / kWave) {
+        const uint4 v = p4[cc * (kHistWords / 4) + lane];
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        const uint32_t mask = cc < c ? 0xffffffffu : 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            h.all.cnt[2 * e] += w[e] & 0xffffu;
+            h.all.cnt[2 * e + 1] += w[e] >> 16;
+            h.before.cnt[2 * e] += w[e] & mask & 0xffffu;
+            h.before.cnt[2 * e + 1] += (w[e] & mask) >> 16;
+        }
+    }
+    return h;
+}
+
+// Called by all NT threads (the first 256 do the work): add the chunk histograms up and find the bin where the count from the
 // top reaches kk = min(k, L).  red: LDS [4][kBins] words, lds4: LDS [4], sthr: LDS [3].
+template <int NT = kBlock>
 __device__ __forceinline__ Threshold find_threshold(const HistLoads& h, int kk, int L, uint32_t* red,
                                                     uint32_t* lds4, int* sthr) {
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
@@ -79,17 +109,22 @@ __device__ __forceinline__ Threshold find_threshold(const HistLoads& h, int kk, 
         r.nb = 0;
         return r;
     }
+    const bool works = NT == kBlock || wv < kBlock / kWave;
+    if (works) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) red[wv * kBins + lane * 8 + e] = h.cnt[e];
+        for (int e = 0; e < 8; ++e) red[wv * kBins + lane * 8 + e] = h.cnt[e];
+    }
     __syncthreads();
     uint32_t c0 = 0, c1 = 0;
+    if (works) {
 #pragma unroll
-    for (int w = 0; w < kBlock / kWave; ++w) {
-        c0 += red[w * kBins + 2 * t];
-        c1 += red[w * kBins + 2 * t + 1];
+        for (int w = 0; w < kBlock / kWave; ++w) {
+            c0 += red[w * kBins + 2 * t];
+            c1 += red[w * kBins + 2 * t + 1];
+        }
     }
     const uint32_t own = c0 + c1;
-    uint32_t cum = block_suffix_sum(own, lds4) - own;  // tokens in bins owned by higher threads
+    uint32_t cum = block_suffix_sum<NT>(own, lds4) - own;  // tokens in bins owned by higher threads
     const uint32_t ukk = static_cast<uint32_t>(kk);
     if (cum < ukk && ukk <= cum + c1) {
         sthr[0] = 2 * t + 1;

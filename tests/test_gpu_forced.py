@@ -401,6 +401,37 @@ def test_shared_selection_large_launch_gathers_once(oracle, R, q2):
     run_shared(oracle, cfg, 33000, steps=1, append=False, q2=q2, seq_len=[33000, 20000, 5, 33000, 1000, 0, 33000, 777])
 
 
+@pytest.mark.parametrize("q2", [False, True])
+@pytest.mark.parametrize("B,H,R,L,k", [(8, 6, 13, 9000, 700), (8, 8, 5, 25000, 1200)])  # chunks of 2048 and of 7168
+def test_shared_selection_is_bit_reproducible_on_the_selector_route(B, H, R, L, k, q2):
+    # the selector's index list must have one order, whatever the arrival order of its workgroups: the softmax sums of
+    # the attention that reads it follow the list.  More than 1024 fused workgroups and fewer rows: the selector's route.
+    lay = sik.make_layout(B, H, H * R, 128, L, torch.bfloat16, torch.float32)
+    assert sik.sik_plan_info(lay)[5] * B * H * R > 1024
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    K, V = (torch.randn(B, H, L, 128, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(B, H * R, 128, generator=gen, device="cuda").to(torch.bfloat16)
+    sl = torch.tensor([L - 1111 * b for b in range(B)], dtype=torch.int32, device="cuda")
+    mu, al = torch.zeros(B, H, 128, device="cuda"), torch.zeros(B, H, 128, device="cuda")
+    cb = torch.zeros(B, H, 32, 16, 4, device="cuda")
+    cnt = torch.zeros(B, H, 32, 16, dtype=torch.int32, device="cuda")
+    codes, rec = torch.zeros(B, H, L, 16, dtype=torch.uint8, device="cuda"), sik.alloc_kvq(lay)
+    ws = sik.alloc_workspace(lay, k)
+    sik.sik_prefill_compress(lay, K, V, sl, mu, cb, cnt, codes, al, rec, ws)
+    cache = dict(kvq=rec, alpha=al) if q2 else dict(K=K, V=V)
+    first = None
+    for _ in range(20):
+        out = torch.zeros(B, H * R, 128, device="cuda")
+        idx = torch.zeros(B, H, k, dtype=torch.int32, device="cuda")
+        sik.sik_decode_step_ex(lay, q=q, seq_len=sl, mu=mu, codebook=cb, codes=codes, k=k, out=out, idx_out=idx,
+                               workspace=ws, group_shared=True, **cache)
+        sync()
+        if first is None:
+            first = out, idx
+        assert torch.equal(idx, first[1]) and torch.equal(out, first[0])
+
+
 def test_many_units_long_context_forced_set_and_equal_scores(oracle):
     """512 (sequence, KV head) units of 66000 tokens: a launch large enough for one scoring workgroup per unit,
     whose token range must still be cut into chunks of at most 64512 tokens (16-bit histogram counts, one forced
