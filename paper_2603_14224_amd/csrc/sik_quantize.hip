@@ -98,15 +98,27 @@ __global__ __launch_bounds__(kBlock) void colsum_kernel(const uint16_t* __restri
         }
     };
     int i = start + r;
-    // Independent loads in flight: eight, because a small launch (8 units: two workgroups per compute unit) has too few
-    // wavefronts to cover the HBM latency with four; four with MINMAX, which at eight takes 140 registers.
+    // Eight independent loads in flight per thread, where four leave too few bytes in flight (keys of 32 x 8 x 16K:
+    // 489 -> 482 us for the fit), then four, for ranges of fewer than 128 rows and what is left of longer ones (64 x 8 x
+    // 128 to 512: 36.9 us, 37.3 without).  Four alone with MINMAX, which at eight takes 140 registers.
     constexpr int kLoads = MINMAX ? 4 : 8;
     for (; i + 16 * (kLoads - 1) < end; i += 16 * kLoads) {
         uint4 v[kLoads];
 #pragma unroll
         for (int u = 0; u < kLoads; ++u) v[u] = ld_stream(&base[static_cast<size_t>(i + 16 * u) * 16 + p]);
+        __builtin_amdgcn_sched_barrier(0);  // (left to itself the compiler may wait for each load before the next)
 #pragma unroll
         for (int u = 0; u < kLoads; ++u) take(v[u]);
+    }
+    if constexpr (kLoads > 4) {
+        for (; i + 48 < end; i += 64) {
+            uint4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = ld_stream(&base[static_cast<size_t>(i + 16 * u) * 16 + p]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) take(v[u]);
+        }
     }
     for (; i < end; i += 16) take(base[static_cast<size_t>(i) * 16 + p]);
 #pragma unroll
@@ -143,15 +155,16 @@ __global__ __launch_bounds__(kBlock) void colsum_kernel(const uint16_t* __restri
 
 // fit step 2: mu = (sum of partials, fixed order) / L; with colmm also alpha_d = max(|max_i K_id - mu_d|,
 // |min_i K_id - mu_d|) in binary32 (= max_i |K_id - mu_d|, see colsum_kernel), 0 for an empty sequence.
-// Bound by load latency (a unit's partials are a few KB): S threads share a channel, so that all of its at
-// most kFitMaxWg partials are requested in one round trip (one thread per channel: eight round trips; with
-// codebook_kernel's slices and colsum_kernel's loads, keys of 1 x 8 x 32K: 58.6 -> 54.0 us for the whole fit).
-// Many units have few partials each: up to 2 * kSlicePartials of them take two slices, as the six idle ones of eight cost
-// more than they give there (152 units of 276 to 1104 keys: 35.8 -> 33.9 us for the fit; 144 units of 3641 to 14563:
-// 159.9 -> 158.5).  Every count adds up in the same order.
-constexpr int kSlicePartials = 8;  // partials a thread adds up
+// Bound by load latency (a unit's partials are a few KB): S threads share a channel and each requests its at most P
+// partials together, so that all of them arrive in one round trip (one thread per channel: eight round trips; with
+// codebook_kernel's slices, keys of 1 x 8 x 32K: 57.4 -> 50.0 us for the whole fit, into records 86.7 -> 64.7).
+// Many units have few partials each, and what is read for nothing costs more than it gives: one slice, without staging
+// or a barrier, for up to kSlicePartials of them (two partials per thread for one or two), two slices for up to twice
+// that (19 x 8 units of 276 to 1104 keys: 32.7 us with one thread per channel, 32.4 so; into records 38.2, 36.4).
+// Every count adds up in the same order.
+constexpr int kSlicePartials = 8;  // partials a thread adds up (P below), two where the unit has no more
 constexpr int kSlicesMax = kFitMaxWg / kSlicePartials;
-template <int S>
+template <int S, int P>
 __global__ __launch_bounds__(S * kD) void mean_kernel(const double* __restrict__ colsum,
                                                       const float* __restrict__ colmm,
                                                       const int32_t* __restrict__ seq_len,
@@ -163,27 +176,28 @@ __global__ __launch_bounds__(S * kD) void mean_kernel(const double* __restrict__
     int L = seq_len[unit / Hkv];
     L = L < 0 ? 0 : (L > Lmax ? Lmax : L);
     const size_t slot0 = static_cast<size_t>(unit) * kFitMaxWg;
-    double s = 0.0;
+    // (slots beyond the last partial read it again and count for nothing: under a condition of its own each load would
+    // be waited for before the next)
+    double s = 0.0, part[P];
     float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < kSlicePartials; ++j) {
-        const int w = slice * kSlicePartials + j;
-        if (w < nwg) s += colsum[(slot0 + w) * kD + d];
-    }
+    for (int j = 0; j < P; ++j) part[j] = colsum[(slot0 + min(slice * P + j, nwg - 1)) * kD + d];
     if (colmm != nullptr) {
 #pragma unroll
-        for (int j = 0; j < kSlicePartials; ++j) {
-            const int w = slice * kSlicePartials + j;
-            if (w < nwg) {
-                lo = fminf(lo, colmm[(slot0 + w) * 2 * kD + d]);
-                hi = fmaxf(hi, colmm[(slot0 + w) * 2 * kD + kD + d]);
-            }
+        for (int j = 0; j < P; ++j) {
+            const float* pm = colmm + (slot0 + min(slice * P + j, nwg - 1)) * 2 * kD;
+            lo = fminf(lo, pm[d]);
+            hi = fmaxf(hi, pm[kD + d]);
         }
     }
-    ps[slice][d] = s;
-    plo[slice][d] = lo;
-    phi[slice][d] = hi;
-    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < P; ++j) s += slice * P + j < nwg ? part[j] : 0.0;
+    if constexpr (S > 1) {
+        ps[slice][d] = s;
+        plo[slice][d] = lo;
+        phi[slice][d] = hi;
+        __syncthreads();
+    }
     if (slice == 0) {
 #pragma unroll
         for (int x = 1; x < S; ++x) {
@@ -211,7 +225,7 @@ __global__ __launch_bounds__(S * kD) void mean_kernel(const double* __restrict__
 // Two wavefronts encode whatever the launch, two tokens each per step, so that the four chains in which a workgroup's
 // sums are added up, and with them the bits of the codebook, do not depend on the launch (eight chains, from four
 // wavefronts in launches of two workgroups per compute unit, moved centroids by an ulp and with them the tokens that
-// later steps select; keys of 1 x 8 x 32K took 47.0 us with them, 54.0 with four).
+// later steps select; with them, all else equal, keys of 1 x 8 x 32K took 47 us against 54).
 constexpr int kEncThreads = 128;
 constexpr int kEncEntries = 16 * 5;              // per group: 16 codes x (4 sums + count)
 constexpr int kEncTokPerIter = kEncThreads / 32;  // tokens the two encoding wavefronts take per step
@@ -444,7 +458,7 @@ __global__ __launch_bounds__(kCmpThreads, 5) void compress_kernel(
 // Bound by load latency like mean_kernel: S threads share one (group, code) entry and each requests its at most
 // kSlicePartials partials at once.  Grid = units x codebook_blocks(S).
 constexpr int codebook_blocks(int slices) { return kG * 16 * slices / kBlock; }  // workgroups per unit
-template <int S>
+template <int S, int P>
 __global__ __launch_bounds__(kBlock) void codebook_kernel(const float* __restrict__ part, int nwg,
                                                           int32_t* __restrict__ counts,
                                                           float* __restrict__ codebook) {
@@ -455,18 +469,22 @@ __global__ __launch_bounds__(kBlock) void codebook_kernel(const float* __restric
     const int e = (blockIdx.x % kCbBlocks) * kCbEntries + x;  // e = g * 16 + code
     double s[5] = {0, 0, 0, 0, 0};
     const float* p = part + (unit * kFitMaxWg * kG * 16 + e) * 5;
+    float v[P][5];  // (slots beyond the last partial: as in mean_kernel)
 #pragma unroll
-    for (int j = 0; j < kSlicePartials; ++j) {
-        const int w = slice * kSlicePartials + j;
-        if (w < nwg) {
+    for (int j = 0; j < P; ++j)
 #pragma unroll
-            for (int c = 0; c < 5; ++c) s[c] += static_cast<double>(p[static_cast<size_t>(w) * kG * 16 * 5 + c]);
-        }
+        for (int c = 0; c < 5; ++c)
+            v[j][c] = p[static_cast<size_t>(min(slice * P + j, nwg - 1)) * kG * 16 * 5 + c];
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+        for (int c = 0; c < 5; ++c) s[c] += slice * P + j < nwg ? static_cast<double>(v[j][c]) : 0.0;
+    if constexpr (S > 1) {
+#pragma unroll
+        for (int c = 0; c < 5; ++c) ps[slice][c][x] = s[c];
+        __syncthreads();
+        if (slice != 0) return;
     }
-#pragma unroll
-    for (int c = 0; c < 5; ++c) ps[slice][c][x] = s[c];
-    __syncthreads();
-    if (slice != 0) return;
 #pragma unroll
     for (int y = 1; y < S; ++y)
 #pragma unroll
@@ -521,9 +539,13 @@ hipError_t launch_fit(const Dims& d, const Workspace& w, const void* K, const vo
         e = launch_kernel(bf ? colsum_kernel<kBF16, false> : colsum_kernel<kF16, false>, units * nwg, kBlock, s, Kp,
                           seq_len, w.colsum, nullptr, d.Hkv, d.Lmax, nwg);
     if (e != hipSuccess) return e;
-    const bool few = nwg <= 2 * kSlicePartials;
-    e = launch_kernel(few ? mean_kernel<2> : mean_kernel<kSlicesMax>, units, (few ? 2 : kSlicesMax) * kD, s, w.colsum,
-                      V ? w.colmm : nullptr, seq_len, mu, alpha, d.Hkv, d.Lmax, nwg);
+    const int slices = nwg <= kSlicePartials ? 1 : (nwg <= 2 * kSlicePartials ? 2 : kSlicesMax);
+#define SIK_SLICED(KERNEL)                                                                  \
+    (nwg <= 2 ? KERNEL<1, 2>                                                                \
+              : (slices == 1 ? KERNEL<1, kSlicePartials>                                    \
+                             : (slices == 2 ? KERNEL<2, kSlicePartials> : KERNEL<kSlicesMax, kSlicePartials>)))
+    e = launch_kernel(SIK_SLICED(mean_kernel), units, slices * kD, s, w.colsum, V ? w.colmm : nullptr, seq_len, mu,
+                      alpha, d.Hkv, d.Lmax, nwg);
     if (e != hipSuccess) return e;
     if (V)
         e = launch_kernel(bf ? compress_kernel<kBF16> : compress_kernel<kF16>, units * nwg, kCmpThreads, s, Kp, Vp,
@@ -532,8 +554,9 @@ hipError_t launch_fit(const Dims& d, const Workspace& w, const void* K, const vo
         e = launch_kernel(bf ? encode_kernel<kBF16, true> : encode_kernel<kF16, true>, units * nwg, kEncThreads, s,
                           Kp, seq_len, 0, 0, mu, codes, w.cpart, d.Hkv, d.Lmax, nwg);
     if (e != hipSuccess) return e;
-    return launch_kernel(few ? codebook_kernel<2> : codebook_kernel<kSlicesMax>,
-                         units * codebook_blocks(few ? 2 : kSlicesMax), kBlock, s, w.cpart, nwg, counts, codebook);
+    return launch_kernel(SIK_SLICED(codebook_kernel), units * codebook_blocks(slices), kBlock, s, w.cpart, nwg, counts,
+                         codebook);
+#undef SIK_SLICED
 }
 
 hipError_t launch_encode(const Dims& d, const void* K, int t0, int n, const float* mu, uint8_t* codes,

@@ -417,12 +417,12 @@ def test_prefill_compress_equals_the_separate_calls_and_the_oracle(oracle, dtype
         assert not got[b, :, L:].any() and not codes2[b, :, L:].any()
 
 
-@pytest.mark.parametrize("batch,lens", [(1, [16]), (1, [257]), (1, [16385]), (8, [5376]), (8, [5377, 65]),
-                                        (40, [8195, 77]), (42, [8195, 8100, 0]), (43, [6145, 1, 5000])])
-def test_fit_partials_and_encoder_widths(oracle, batch, lens):
-    # 1 to 64 partials per unit on both sides of 16 (two or eight slices in the reductions: 40 x 3 units have 17, 42 x 3
-    # have 16), and on both sides of the 512 workgroups above which the encoders go from four wavefronts to two (3 units
-    # per sequence, at least 256 rows per workgroup: 8 x 3 x 21 = 504 against 8 x 3 x 22 = 528)
+@pytest.mark.parametrize("batch,lens", [(1, [16]), (1, [257]), (1, [513]), (5, [2048]), (5, [2049, 300]), (1, [16385]),
+                                        (8, [5376]), (8, [5377, 65]), (40, [8195, 77]), (42, [8195, 8100, 0]),
+                                        (43, [6145, 1, 5000])])
+def test_fit_partials_and_slices(oracle, batch, lens):
+    # 1 to 64 partials per unit (at least 256 rows each): one slice with two per thread (1, 2) or eight (3, 8), two slices
+    # (9, 16: 42 x 3 units) and eight (17: 40 x 3 units, and more) in the reductions
     B, H, cap = batch, 3, max(lens)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(cap)
