@@ -350,15 +350,24 @@ static int decode_step_impl(const sik_layout* layout, const void* q, const void*
     // Large launches select once per KV head with the stand-alone selector and let the attention kernels read that
     // list; small ones, and everything that needs the fused kernel's extras, go through the fused kernel, where the R
     // query heads of a group each classify the shared scores and gather the same rows (32K context, one sequence: 19
-    // against 29 us).  The line: the fused launch has more workgroups than a chip of 256 compute units holds (four
-    // each), or so many rows that the classification is mostly repeated.  Measured, selector against fused, 16-bit
-    // rows / 2-bit records: 4 x 8 x 64K with 8:1 GQA, 1536 selected (2048 workgroups) 47 / 47 against 54 / 63 us;
-    // 4 x 8 x 20000 with 8:1, 400 selected (1280) 28 / 28 against 31 / 32; 16 x 8 x 6000 with 5:1 (1280) 29 / 30
-    // against 42 / 38; 32 x 8 x 4096 with 4:1 (1024 rows) 29 / 33 against 41 / 36; below it 4 x 8 x 32K with 8:1, 600
-    // selected (1024 workgroups, 256 rows) 33 / 33 against 30 / 36.  An appended row costs the selector a launch of
-    // its own: those go by the number of keys alone.
+    // against 29 us).  The line without an appended row (which costs the selector a launch of its own: those go by the
+    // number of keys alone): the fused launch has more than four workgroups per compute unit, or five rows per two
+    // compute units that share scores three and more ways, so that much of the classification is repeated.
+    // Measured on 256 units, selector against fused, 16-bit rows / 2-bit records, us:
+    //   4 x 8 x 64K with 8:1, 1536 selected (2048 workgroups, 256 rows)   43 / 44 against 53 / 63
+    //   8 x 8 x 25000 with 5:1, 500 (1280 workgroups, 320 rows)           33 / 37 against 40 / 47
+    //   128 x 8 x 1000 with 2:1, 64 (2048 workgroups and rows)            29 / 31 against 42 / 45
+    //   16 x 8 x 6000 with 5:1, 300 (640 workgroups and rows)             29 / 30 against 42 / 36
+    //   16 x 8 x 1500 with 5:1, 100 (640)                                 21 / 22 against 21 / 24
+    //   64 x 8 x 300 with 4:1, 64 (2048)                                  20 / 21 against 38 / 42
+    // below it
+    //   4 x 8 x 32K with 8:1, 600 (1024 workgroups, 256 rows)             30.5 / 31 against 29 / 36
+    //   24 x 8 x 2000 with 3:1, 100 (576)                                 22.0 / 23 against 21.6 / 25
+    //   64 x 8 x 2000 with 2:1, 100 (1024)                                27 / 30 against 26 / 30
     const bool plain = opt.n == 0 && opt.k_per_mille == 0 && !(kvq && k_new);
-    const bool many = !k_new && d.R > 1 && (static_cast<int64_t>(fchunks) * d.rows() > 1024 || d.rows() >= 1024);
+    const int cus = device_compute_units();
+    const bool many = !k_new && ((d.R > 1 && static_cast<int64_t>(fchunks) * d.rows() > 4 * cus) ||
+                                 (d.R > 2 && 2 * d.rows() >= 5 * cus));
     const bool shared_unfused = opt.group_shared &&
         (!fused || (plain && (many || static_cast<int64_t>(d.units()) * d.Lmax > (2 << 20))));
     hipError_t e = hipSuccess;
@@ -373,10 +382,10 @@ static int decode_step_impl(const sik_layout* layout, const void* q, const void*
     const bool first_pass_16 = opt.launches == 3 && !kvq && opt.n == 0;
     int step_T = 0;
     if (one_launch && first_pass_16)
-        step_T = step_plan(d, k, k_new != nullptr, device_compute_units(), true, false, &step_nchunk, &step_dyn,
+        step_T = step_plan(d, k, k_new != nullptr, cus, true, false, &step_nchunk, &step_dyn,
                            &step_listcap);
     if (one_launch && step_T == 0)
-        step_T = step_plan(d, k, k_new != nullptr, device_compute_units(), false, kvq != nullptr || opt.n > 0,
+        step_T = step_plan(d, k, k_new != nullptr, cus, false, kvq != nullptr || opt.n > 0,
                            &step_nchunk, &step_dyn, &step_listcap);
     if (step_T > 0) {
         const Append ap{static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new),

@@ -267,7 +267,7 @@ def test_sign_only_retrieval_is_a_codebook_of_signs(oracle):
 
 
 # --------------------------------------------------------------------------- group-shared selection
-def run_shared(oracle, cfg, capacity, steps, append, q2=False, seq_len=None):
+def run_shared(oracle, cfg, capacity, steps, append, q2=False, seq_len=None, profiled=False):
     B, Hkv, Hq, k = cfg.batch, cfg.n_kv_heads, cfg.n_q_heads, cfg.top_k
     R = Hq // Hkv
     if q2:
@@ -284,7 +284,7 @@ def run_shared(oracle, cfg, capacity, steps, append, q2=False, seq_len=None):
                   v_new=dev(vn, cfg.dtype) if append else None, seq_len=st.dsl, mu=st.dmu, codebook=st.dcb,
                   codes=st.dcodes, k=k, out=out, idx_out=idx, workspace=st.ws, group_shared=True)
         kw.update(dict(kvq=kvq, alpha=dal) if q2 else dict(K=st.dK, V=st.dV))
-        sik.sik_decode_step_ex(st.layout, **kw)
+        us = sik.sik_decode_step_ex(st.layout, profiled=profiled, **kw)
         sync()
         _, ref_idx = oracle.decode_step_shared(q, kn if append else None, vn if append else None, st.K, st.V,
                                                cfg.dtype, sl, st.mu, st.cb, st.codes, k)
@@ -300,6 +300,7 @@ def run_shared(oracle, cfg, capacity, steps, append, q2=False, seq_len=None):
         else:
             ref = oracle.sparse_attn(q, st.K, st.V, cfg.dtype, full)
         check_attention(out.cpu().numpy().astype(np.float64), ref, True)
+    return us
 
 
 def test_shared_selection_c2_shape_with_append(oracle):
@@ -382,15 +383,23 @@ def test_shared_selection_beyond_the_fused_plan(oracle):
     check_attention(out.cpu().numpy().astype(np.float64), ref, True)
 
 
-@pytest.mark.parametrize("batch,n_kv,R,L,append", [(16, 8, 5, 2100, False),   # 1920 fused workgroups
-                                                   (43, 6, 4, 1000, False),   # 1032 rows
-                                                   (43, 6, 4, 1000, True),    # the same with an append: fused
-                                                   (128, 8, 1, 300, False)])  # one query head per KV head: fused
-@pytest.mark.parametrize("q2", [False, True])
-def test_shared_selection_on_both_sides_of_the_workgroup_line(oracle, batch, n_kv, R, L, append, q2):
+@pytest.mark.parametrize("batch,n_kv,R,L,wgs,selector", [
+    (8, 6, 13, 9000, 1248, True),    # more than four fused workgroups per compute unit, 624 rows, blocks of 4 4 4 1 heads
+    (65, 8, 2, 300, 1040, True),     # the same with two query heads per KV head, whose rows alone do not count
+    (64, 8, 2, 300, 1024, False),
+    (32, 4, 5, 700, 640, True),      # five rows per two compute units
+    (53, 4, 3, 700, 636, False),
+    (43, 6, 4, 1000, 1032, True),    # both
+    (128, 8, 1, 300, 1024, False)])  # one query head per KV head: nothing is repeated
+@pytest.mark.parametrize("append,q2", [(False, False), (False, True), (True, False)])
+def test_shared_selection_on_both_sides_of_the_workgroup_line(oracle, batch, n_kv, R, L, wgs, selector, append, q2):
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256, "the line is stated for 256 compute units"
     cfg = cfg_small("C2", batch=batch, n_kv_heads=n_kv, n_q_heads=n_kv * R, context=L, top_k=70)
+    lay = sik.make_layout(batch, n_kv, n_kv * R, 128, L + 4, TDT[cfg.dtype], torch.float32)
+    assert sik.sik_plan_info(lay)[5] * batch * n_kv * R == wgs
     lens = [L - 37 * (b % 5) if b % 7 else b % 3 for b in range(batch)]
-    run_shared(oracle, cfg, L + 4, steps=1, append=append and not q2, q2=q2, seq_len=lens)
+    us = run_shared(oracle, cfg, L + 4, steps=1, append=append, q2=q2, seq_len=lens, profiled=True)
+    assert (us[2] > 0) == (selector and not append)  # the selection kernel of its own; an appended row: fused
 
 
 @pytest.mark.parametrize("R,q2", [(5, False), (4, True), (6, True)])
