@@ -162,15 +162,37 @@ def test_topk_random_scores(oracle, L, k):
 
 @pytest.mark.parametrize("Lmax", [4096, 4097, 8195, 12288])
 def test_topk_chunk_edges_and_both_load_forms(oracle, Lmax):
-    # rows of a multiple of four scores are read as vectors, others one by one; lengths around a lane's, a wavefront's and
-    # a chunk's share, with nothing, one, nearly all and all of the row selected; one row with many scores of minus infinity and of the lowest value.
-    # Equal fp32 scores on both sides: the sets must be identical.
+    # few rows: chunks of 2048 scores, eight per thread.  Rows of a multiple of four scores are read as vectors, others one
+    # by one; lengths around a lane's and a wavefront's share, with one, some, nearly all and all of the row selected; one
+    # row with many scores of minus infinity and of the lowest value.  Equal fp32 scores on both sides: the sets must be
+    # identical.
     rng = np.random.default_rng(Lmax)
     lens = [1, 3, 5, 255, 257, 1025, 4095, Lmax]
     s = rng.normal(size=(len(lens), 2, Lmax)).astype(np.float32)
     s[:, 1, ::5] = -np.inf
     s[:, 1, 1::5] = np.finfo(np.float32).min
     for k in (1, 200, 4094, Lmax):
+        got = run_topk(s, lens, k)
+        ref = oracle.topk(s.astype(np.float64), np.asarray(lens, np.int32), k)
+        assert np.array_equal(np.sort(got, -1), np.sort(ref, -1)), k
+
+
+@pytest.mark.parametrize("rows,Lmax,chunk", [
+    (256, 8192, 4096), (256, 8190, 4096),    # 256 threads with all sixteen scores, two chunks; vectors, one by one
+    (256, 8195, 4352), (512, 4100, 4352),    # 512 threads, up to nine scores
+    (512, 8192, 8192),                       # all sixteen
+    (512, 8193, 8448), (512, 20004, 20224)])  # two and three pieces of 8192
+def test_topk_full_lanes_long_chunks_and_pieces(oracle, rows, Lmax, chunk):
+    Hq = 32
+    lay = sik.make_layout(rows // Hq, 1, Hq, 128, Lmax, torch.bfloat16)
+    assert sik.sik_plan_info(lay)[4] == chunk
+    rng = np.random.default_rng(rows + Lmax)
+    s = rng.normal(size=(rows // Hq, Hq, Lmax)).astype(np.float32)
+    s[:, 1] = np.round(s[:, 1] * 8) / 8  # ties at the cut
+    s[:, 2] = np.sort(s[:, 2])           # the selected ones side by side: full lanes, then empty ones
+    edges = [Lmax, 4095, 4096, 4097, Lmax - 1, chunk - 1, min(chunk, Lmax), min(chunk + 1, Lmax), 8191, 8193, 1, 0]
+    lens = [min(edges[b % len(edges)], Lmax) for b in range(rows // Hq)]
+    for k in (1, Lmax // 20, Lmax // 2, Lmax - 1, Lmax):
         got = run_topk(s, lens, k)
         ref = oracle.topk(s.astype(np.float64), np.asarray(lens, np.int32), k)
         assert np.array_equal(np.sort(got, -1), np.sort(ref, -1)), k
