@@ -441,16 +441,19 @@ def test_fit_partials_and_slices(oracle, batch, lens):
             sik.sik_prefill_compress(lay, K, V, dsl, mu, cb, cnt, codes, al, rec, ws)
         else:
             sik.sik_quantize_keys(lay, K, dsl, 0, 0, sik.SIK_Q_FIT, mu, cb, cnt, codes, ws)
-        res.append((mu, cb, cnt, codes))
+            sik.sik_quantize_kv(lay, K, V, dsl, 0, 0, sik.SIK_Q_FIT, mu, al, rec)
+        res.append((mu, cb, cnt, codes, al, rec))
     sync()
     for a, b in zip(*res):
         assert torch.equal(a, b)
-    mu, cb, cnt, codes = (x.cpu().numpy() for x in res[0])
+    mu, cb, cnt, codes, al = (x.cpu().numpy() for x in res[0][:5])
     for b in {0, 1 % B, 2 % B, B - 1}:
         n = lens[b]
         x = K[b, :, :n].cpu().double().numpy()
         m = (x.sum(1) / n if n else np.zeros((H, 128))).astype(np.float32)
         assert np.array_equal(mu[b], m)
+        peak = np.abs(x.astype(np.float32) - m[:, None]).max(1) if n else np.zeros((H, 128), np.float32)
+        assert np.array_equal(al[b], peak)
         sign = x >= m[:, None]
         assert np.array_equal(codes[b, :, :n], np.packbits(sign, axis=-1))
         code = (sign.reshape(H, n, 32, 4) * [8, 4, 2, 1]).sum(-1)
