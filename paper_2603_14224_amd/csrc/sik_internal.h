@@ -19,7 +19,9 @@ struct Dims {
 
 // Carving of the caller's workspace.  All offsets are multiples of 256 bytes.
 struct Workspace {
-    // zeroed by the prep kernel at the start of every call that selects or attends
+    // zeroed at the start of every call that selects or attends: by the prep kernel where one runs (sik_sparse_attn*,
+    // an append on the separate launches), by the scoring launch in the other decode steps, by minmax_kernel in
+    // sik_topk; the one-launch step keeps its own counters (sync)
     uint32_t* zero_begin;   // start of the zero-initialised region
     size_t zero_words;      // its length in 32-bit words
     uint32_t* sync;         // one-launch decode step: status word and self-clearing counters (sik_workspace_init)

@@ -23,8 +23,9 @@ constexpr int kSelPer = 16;   // scores a thread of the select kernel holds in r
 constexpr int kSelBig = 512;  // its workgroup size for chunks of more than kSelPer * kBlock scores
 
 // ---- stand-alone level 1, pass A: min and max of the order-preserving keys of each chunk ----
-// Also clears the counters of its row for the kernels that follow (chunk 0), so that no launch has to do it first (scoring,
-// top-k and attention of 2 x 32 heads x 20000 as separate calls: 39.7 -> 35.9 us, 34.5 with select_kernel's ballots).
+// Also clears the counters of its row for the kernels that follow (chunk 0), so that no launch has to do it first: with
+// what select_kernel gained, scoring, top-k and attention of 2 x 32 heads x 20000 as separate calls 39.6 -> 36.4 us
+// (cards and runs differ by up to 2).
 __global__ __launch_bounds__(kBlock) void minmax_kernel(const float* __restrict__ scores,
                                                         const int32_t* __restrict__ seq_len,
                                                         uint32_t* __restrict__ counters,
