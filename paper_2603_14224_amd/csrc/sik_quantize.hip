@@ -231,12 +231,12 @@ constexpr int kEncEntries = 16 * 5;              // per group: 16 codes x (4 sum
 constexpr int kEncTokPerIter = kEncThreads / 32;  // tokens the two encoding wavefronts take per step
 constexpr int kEncUnroll = 16;
 
-// The encoder's per-lane state and token step, shared by encode_kernel and compress_kernel.
+// The encoder's per-lane state and token steps, shared by encode_kernel and compress_kernel.
 template <int DT, bool CLUSTER>
 struct SignEncoder {
     float4 m;        // channel means of this lane's sign group
     float4* cols;    // this lane's accumulator columns (stride kWave per code)
-    float* colc;
+    uint32_t* colc;
     uint8_t* cbase;  // code plane of the (sequence, KV head)
     int g;
 
@@ -245,33 +245,84 @@ struct SignEncoder {
 #pragma unroll
             for (int c = 0; c < 16; ++c) {
                 cols[c * kWave] = make_float4(0.f, 0.f, 0.f, 0.f);
-                colc[c * kWave] = 0.0f;
+                colc[c * kWave] = 0u;
             }
         }
     }
-    // token i: code nibble of group g, the byte stored by the even lane of a pair, cluster sums updated
-    __device__ __forceinline__ void token(int i, const uint2 v) {
+    // the Code of one token's group, and its four differences from the means
+    __device__ __forceinline__ int sign(const uint2 v, float4& d) const {
         const float f[4] = {widen16<DT>(v.x & 0xffffu), widen16<DT>(v.x >> 16), widen16<DT>(v.y & 0xffffu),
                             widen16<DT>(v.y >> 16)};
-        const int code = (f[0] >= m.x ? 8 : 0) | (f[1] >= m.y ? 4 : 0) | (f[2] >= m.z ? 2 : 0) | (f[3] >= m.w ? 1 : 0);
-        // the neighbouring lane holds the other nibble of this byte (groups 2j, 2j+1)
-        const int other = __builtin_amdgcn_update_dpp(0, code, 0xB1 /* quad_perm:[1,0,3,2] */, 0xf, 0xf, false);
+        d = make_float4(f[0] - m.x, f[1] - m.y, f[2] - m.z, f[3] - m.w);
+        return (f[0] >= m.x ? 8 : 0) | (f[1] >= m.y ? 4 : 0) | (f[2] >= m.z ? 2 : 0) | (f[3] >= m.w ? 1 : 0);
+    }
+    // the Code of the neighbouring lane, which holds the other nibble of a byte (groups 2j, 2j+1)
+    static __device__ __forceinline__ int neighbour(int code) {
+        return __builtin_amdgcn_update_dpp(0, code, 0xB1 /* quad_perm:[1,0,3,2] */, 0xf, 0xf, false);
+    }
+    static __device__ __forceinline__ float4 plus(const float4 a, const float4 d) {
+        return make_float4(a.x + d.x, a.y + d.y, a.z + d.z, a.w + d.w);
+    }
+    // counts are whole numbers: an add without a result leaves nothing to wait for
+    __device__ __forceinline__ void count(int code) {
+        __hip_atomic_fetch_add(&colc[code * kWave], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    // token i alone: the byte stored by the even lane of a pair
+    __device__ __forceinline__ void token(int i, const uint2 v) {
+        float4 d;
+        const int code = sign(v, d);
+        const int other = neighbour(code);
         if ((g & 1) == 0) cbase[static_cast<size_t>(i) * kCodeBytes + (g >> 1)] = static_cast<uint8_t>((code << 4) | other);
         if constexpr (CLUSTER) {
-            float4 a = cols[code * kWave];
-            a.x += f[0] - m.x;
-            a.y += f[1] - m.y;
-            a.z += f[2] - m.z;
-            a.w += f[3] - m.w;
-            cols[code * kWave] = a;
-            colc[code * kWave] += 1.0f;
+            cols[code * kWave] = plus(cols[code * kWave], d);
+            count(code);
+        }
+    }
+    // Tokens i and i + kEncTokPerIter, both in the range.  The lanes of a pair exchange the nibble that the other one
+    // needs: the even lane stores the first token's byte, the odd lane the second's.  Both accumulators are read
+    // before either is written; where the Codes agree the second token adds to the first one's sum, so that every
+    // sum is still added up in token order, and a step of the LDS chain covers two tokens.  (Bound by that chain and by
+    // the instructions between its steps: one token at a time, each under a condition of its own and with its count
+    // read and written back, keys of 1 x 8 x 32K took 51.3 us for the whole fit, now 46.8; 4 x 8 x 64K into records,
+    // where the record builders share the vector units, 421 and 418.)
+    __device__ __forceinline__ void two_tokens(int i, const uint2 v0, const uint2 v1) {
+        float4 d0, d1;
+        const int c0 = sign(v0, d0), c1 = sign(v1, d1);
+        const bool even = (g & 1) == 0;
+        const int other = neighbour(even ? c1 : c0);
+        const int byte = ((even ? c0 : other) << 4) | (even ? other : c1);
+        cbase[static_cast<size_t>(even ? i : i + kEncTokPerIter) * kCodeBytes + (g >> 1)] = static_cast<uint8_t>(byte);
+        if constexpr (CLUSTER) {
+            const float4 a0 = cols[c0 * kWave], a1 = cols[c1 * kWave];
+            const bool same = c0 == c1;
+            const float4 s0 = plus(a0, d0);
+            const float4 s1 = plus(make_float4(same ? s0.x : a1.x, same ? s0.y : a1.y, same ? s0.z : a1.z,
+                                               same ? s0.w : a1.w), d1);
+            cols[c0 * kWave] = s0;
+            cols[c1 * kWave] = s1;
+            count(c0);
+            count(c1);
+        }
+    }
+    // N tokens of this lane, i, i + kEncTokPerIter, ...; `whole`, the same in every lane, where all lanes of the
+    // workgroup have all of theirs before `end`
+    template <int N>
+    __device__ __forceinline__ void tokens(int i, const uint2 (&v)[N], int end, bool whole) {
+        static_assert(N % 2 == 0, "tokens are taken in twos");
+        if (whole) {
+#pragma unroll
+            for (int u = 0; u < N; u += 2) two_tokens(i + u * kEncTokPerIter, v[u], v[u + 1]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+                if (i + u * kEncTokPerIter < end) token(i + u * kEncTokPerIter, v[u]);
         }
     }
 };
 
 // Workgroup partial of the cluster sums: part[g][code][4 sums, count] from the accumulator columns of the
 // encoding wavefronts (waves 0 and 1 of the workgroup); called by `nthreads` threads after a barrier.
-__device__ __forceinline__ void publish_cluster_partial(const float4* tabs, const float* tabc, float* pw, int tid,
+__device__ __forceinline__ void publish_cluster_partial(const float4* tabs, const uint32_t* tabc, float* pw, int tid,
                                                         int nthreads) {
     for (int e = tid; e < kG * kEncEntries; e += nthreads) {
         const int gg = e / kEncEntries, ent = e % kEncEntries, code = ent / 5, comp = ent % 5;
@@ -281,7 +332,7 @@ __device__ __forceinline__ void publish_cluster_partial(const float4* tabs, cons
             const int at = (w * 16 + code) * kWave + gg;
             sum += comp < 4 ? reinterpret_cast<const float*>(&tabs[at])[comp] +
                                   reinterpret_cast<const float*>(&tabs[at + 32])[comp]
-                            : tabc[at] + tabc[at + 32];
+                            : static_cast<float>(tabc[at] + tabc[at + 32]);
         }
         pw[e] = sum;
     }
@@ -295,7 +346,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const uint16_t* __r
                                                              float* __restrict__ part, int Hkv, int Lmax,
                                                              int nwg) {
     __shared__ float4 tabs[CLUSTER ? (kEncThreads / kWave) * 16 * kWave : 1];  // [wave][code][lane]: 4 sums
-    __shared__ float tabc[CLUSTER ? (kEncThreads / kWave) * 16 * kWave : 1];    // [wave][code][lane]: count
+    __shared__ uint32_t tabc[CLUSTER ? (kEncThreads / kWave) * 16 * kWave : 1];  // [wave][code][lane]: count
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int g = lane & 31, sub = wv * 2 + (lane >> 5);  // sub: which of the 4 tokens of a step
     const int unit = blockIdx.x / nwg, wg = blockIdx.x % nwg;
@@ -333,16 +384,12 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const uint16_t* __r
         }
     };
     if (start < end) request(start + sub);
-    for (int i0 = start + sub; i0 < end; i0 += kEncTokPerIter * kEncUnroll) {
+    for (int blk = start; blk < end; blk += kEncTokPerIter * kEncUnroll) {
         uint2 v[kEncUnroll];
 #pragma unroll
         for (int u = 0; u < kEncUnroll; ++u) v[u] = nx[u];
-        request(i0 + kEncTokPerIter * kEncUnroll);
-#pragma unroll
-        for (int u = 0; u < kEncUnroll; ++u) {
-            const int i = i0 + u * kEncTokPerIter;
-            if (i < end) enc.token(i, v[u]);
-        }
+        request(blk + kEncTokPerIter * kEncUnroll + sub);
+        enc.tokens(blk + sub, v, end, end - blk >= kEncTokPerIter * kEncUnroll);
     }
     if constexpr (CLUSTER) {
         __syncthreads();
@@ -372,7 +419,7 @@ __global__ __launch_bounds__(kCmpThreads, 5) void compress_kernel(
     const float* __restrict__ mu, const float* __restrict__ alpha, uint8_t* __restrict__ codes,
     float* __restrict__ part, uint2* __restrict__ rec, int Hkv, int Lmax, int nwg) {
     __shared__ float4 tabs[(kEncThreads / kWave) * 16 * kWave];
-    __shared__ float tabc[(kEncThreads / kWave) * 16 * kWave];
+    __shared__ uint32_t tabc[(kEncThreads / kWave) * 16 * kWave];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int unit = blockIdx.x / nwg, wg = blockIdx.x % nwg;
     int L = seq_len[unit / Hkv];
@@ -407,11 +454,7 @@ __global__ __launch_bounds__(kCmpThreads, 5) void compress_kernel(
 #pragma unroll
             for (int u = 0; u < kCmpEncSteps; ++u) v[u] = nx[u];
             request(blk + kCmpBlock + sub);
-#pragma unroll
-            for (int u = 0; u < kCmpEncSteps; ++u) {
-                const int i = blk + sub + u * kEncTokPerIter;
-                if (i < end) enc.token(i, v[u]);
-            }
+            enc.tokens(blk + sub, v, end, end - blk >= kCmpBlock);
             __syncthreads();
         }
     } else {

@@ -524,3 +524,32 @@ def test_prefill_compress_argument_errors():
     with pytest.raises(sik.SikError) as e:
         sik.sik_prefill_compress(lay, t, t, t, t, t, t, t, t, t, torch.zeros(256, dtype=torch.uint8, device="cuda"))
     assert e.value.status == -6
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 63, 64, 65, 128, 191])
+def test_tokens_of_one_code_are_added_in_token_order(n):
+    # The encoder takes a lane's tokens in twos and lets the second add to the first one's sum where their codes agree:
+    # here they always do (all keys on one side of the mean but the first), at the edges of its blocks of 32 and 64.
+    x = torch.rand(n, 128, generator=torch.Generator().manual_seed(n)).add_(1.0)
+    x[0] = -100.0
+    lay = sik.make_layout(1, 1, 1, 128, n, torch.float16, torch.float16)
+    K = x.to(torch.float16)[None, None].cuda()
+    dsl = torch.tensor([n], dtype=torch.int32, device="cuda")
+    for one_call in (False, True):
+        mu, al = torch.zeros(1, 1, 128, device="cuda"), torch.zeros(1, 1, 128, device="cuda")
+        cb = torch.zeros(1, 1, 32, 16, 4, device="cuda")
+        cnt = torch.zeros(1, 1, 32, 16, dtype=torch.int32, device="cuda")
+        codes = torch.zeros(1, 1, n, 16, dtype=torch.uint8, device="cuda")
+        ws = sik.alloc_workspace(lay, 0)
+        if one_call:
+            sik.sik_prefill_compress(lay, K, K, dsl, mu, cb, cnt, codes, al, sik.alloc_kvq(lay), ws)
+        else:
+            sik.sik_quantize_keys(lay, K, dsl, 0, 0, sik.SIK_Q_FIT, mu, cb, cnt, codes, ws)
+        sync()
+        m, k = mu[0, 0].cpu().numpy(), K[0, 0].cpu().float().numpy()
+        assert np.array_equal(codes[0, 0].cpu().numpy(), np.packbits(k >= m, axis=-1))
+        c = cnt[0, 0].cpu().numpy()
+        assert c.sum() == 32 * n
+        s = fit_sums_reference(k, m, 1)
+        want = np.where(c[..., None] > 0, s / np.maximum(c, 1)[..., None], 0.0).astype(np.float32)
+        assert np.array_equal(cb[0, 0].cpu().numpy(), want)
