@@ -34,17 +34,24 @@ __device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {
     return static_cast<uint32_t>(
         __builtin_amdgcn_update_dpp(0, static_cast<int>(v), J * 0x55, 0xf, 0xf, false));
 }
-__device__ __forceinline__ float quad_min(float v) {
-    v = fminf(v, __uint_as_float(static_cast<uint32_t>(
-                     __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false))));  // lanes 1,0,3,2
-    return fminf(v, __uint_as_float(static_cast<uint32_t>(
-                        __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4e, 0xf, 0xf, false))));  // lanes 2,3,0,1
-}
-__device__ __forceinline__ float quad_max(float v) {
-    v = fmaxf(v, __uint_as_float(static_cast<uint32_t>(
-                     __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false))));
-    return fmaxf(v, __uint_as_float(static_cast<uint32_t>(
-                        __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4e, 0xf, 0xf, false))));
+// Minimum of lo and maximum of hi over the four lanes of a quad, all of them active, none a signalling NaN.  In
+// assembly because the compiler moves each neighbour's value to a register of its own and makes it a quiet one before
+// the comparison, four instructions where one does; the waits are those that a DPP operand needs after its register
+// is written.  (The record builders are bound by vector instructions; with this, and without the branches around
+// groups of step zero and around the parameter of a slot, 4 x 8 x 64K keys and values into records took 403 us where
+// they had taken 418.)
+__device__ __forceinline__ void quad_minmax(float& lo, float& hi) {
+    float a, b;
+    asm("s_nop 1\n\t"
+        "v_min_f32_dpp %0, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %3, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+        : "=&v"(a), "=&v"(b)
+        : "v"(lo), "v"(hi));
+    lo = a;
+    hi = b;
 }
 
 __device__ __forceinline__ uint32_t fp16_bits(float f) {
@@ -52,19 +59,6 @@ __device__ __forceinline__ uint32_t fp16_bits(float f) {
 }
 __device__ __forceinline__ float fp16_value(uint32_t h) {
     return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(h)));
-}
-
-// Minimum / maximum over the 8 lanes 8j .. 8j+7 (every lane gets it): the quad, then the other quad of the
-// half row (row_half_mirror: lane i of each 8 reads lane 7 - i, which holds its own quad's result).
-__device__ __forceinline__ float oct_min(float v) {
-    v = quad_min(v);
-    return fminf(v, __uint_as_float(static_cast<uint32_t>(
-                        __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, false))));
-}
-__device__ __forceinline__ float oct_max(float v) {
-    v = quad_max(v);
-    return fmaxf(v, __uint_as_float(static_cast<uint32_t>(
-                        __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, false))));
 }
 
 // x / 3 rounded to nearest, in three instructions: the product with the rounded 1/3 is at most one unit off, the
@@ -84,41 +78,34 @@ __device__ __forceinline__ float reciprocal(float x) {
     return fmaf(fmaf(-x, r, 1.0f), r, r);
 }
 
-// Parameters and 2-bit codes of this lane's N values of one 32-value group that 32 / N neighbouring lanes hold
-// together (all of them active); group_min / group_max reduce over those lanes.  Returns the 2 N code bits
-// (value e in bits 2e+1:2e); qs_h, zp_h = the stored fp16 bits.  One function for every lane mapping, so that
-// every kernel that builds records takes the same decisions.
-template <int N, class GroupMin, class GroupMax>
-__device__ __forceinline__ uint32_t quantize_lane(const float (&x)[N], GroupMin group_min, GroupMax group_max,
-                                                  uint32_t& qs_h, uint32_t& zp_h) {
-    float lo = x[0], hi = x[0];
+// Parameters and 2-bit codes of this lane's 8 values of one 32-value group that the four lanes of a quad hold
+// together (all of them active).  Returns the 16 code bits (value e in bits 2e+1:2e); qs_h, zp_h = the stored fp16
+// bits.  One function for every kernel that builds records, so that they all take the same decisions.
+__device__ __forceinline__ uint32_t quantize_octet(const float (&x)[8], uint32_t& qs_h, uint32_t& zp_h) {
+#pragma clang fp contract(off)  // x may be a product: x - zp is the difference from the rounded one
+    float lo = fminf(x[0], x[1]), hi = fmaxf(x[0], x[1]);
 #pragma unroll
-    for (int e = 1; e < N; ++e) {
+    for (int e = 2; e < 8; ++e) {
         lo = fminf(lo, x[e]);
         hi = fmaxf(hi, x[e]);
     }
-    lo = group_min(lo) + 0.0f;  // a zero minimum is stored as +0 whatever the signs of the zeros
-    hi = group_max(hi);
+    quad_minmax(lo, hi);
+    lo += 0.0f;  // a zero minimum is stored as +0 whatever the signs of the zeros
     qs_h = fp16_bits(third(hi - lo));
     zp_h = fp16_bits(lo);
     const float qs = fp16_value(qs_h), zp = fp16_value(zp_h);
+    // A step of zero (or none, of NaN) has the factor zero: every code is then zero, that of an infinite or undefined
+    // difference too, because the clamp takes NaN to its lower bound.
+    const float rqs = qs > 0.0f ? reciprocal(qs) : 0.0f;
     // The code word is assembled in floating point: sum_e c_e 4^e with c_e in {0, 1, 2, 3} stays below 2^16 and is
     // exact in binary32, so one fused multiply-add per value replaces a conversion, a shift and an OR.
-    float word = 0.0f;
-    if (qs > 0.0f) {
-        const float rqs = reciprocal(qs);
+    float word = __builtin_amdgcn_fmed3f(rintf((x[0] - zp) * rqs), 0.0f, 3.0f);  // clamp to [0, 3]
 #pragma unroll
-        for (int e = 0; e < N; ++e) {
-            const float c = __builtin_amdgcn_fmed3f(rintf((x[e] - zp) * rqs), 0.0f, 3.0f);  // clamp to [0, 3]
-            word = fmaf(c, static_cast<float>(1u << (2 * e)), word);
-        }
+    for (int e = 1; e < 8; ++e) {
+        const float c = __builtin_amdgcn_fmed3f(rintf((x[e] - zp) * rqs), 0.0f, 3.0f);
+        word = fmaf(c, static_cast<float>(1u << (2 * e)), word);
     }
     return static_cast<uint32_t>(word);
-}
-
-// 8 values per lane, the group in the 4 lanes of a quad (the 16-lanes-per-row mapping).
-__device__ __forceinline__ uint32_t quantize_octet(const float (&x)[8], uint32_t& qs_h, uint32_t& zp_h) {
-    return quantize_lane<8>(x, [](float v) { return quad_min(v); }, [](float v) { return quad_max(v); }, qs_h, zp_h);
 }
 
 // 1 / alpha, and 0 for a channel that never leaves its mean.
@@ -143,9 +130,8 @@ __device__ __forceinline__ uint2 kvq_make_slot(const uint4 kraw, const uint4 vra
     uint32_t kqs, kzp, vqs, vzp;
     const uint32_t kbits = quantize_octet(kh, kqs, kzp);
     const uint32_t vbits = quantize_octet(vf, vqs, vzp);
-    const int which = p & 3;
-    const uint32_t par = which == 0 ? kqs : (which == 1 ? kzp : (which == 2 ? vqs : vzp));
-    return make_uint2(sign | (kbits << 16), vbits | (par << 16));
+    const uint32_t kpar = p & 1 ? kzp : kqs, vpar = p & 1 ? vzp : vqs;
+    return make_uint2(sign | (kbits << 16), vbits | ((p & 2 ? vpar : kpar) << 16));
 }
 
 // What a lane keeps of the query for logits against records: |q_e alpha_e| and, packed like a sign byte

@@ -553,3 +553,50 @@ def test_tokens_of_one_code_are_added_in_token_order(n):
         s = fit_sums_reference(k, m, 1)
         want = np.where(c[..., None] > 0, s / np.maximum(c, 1)[..., None], 0.0).astype(np.float32)
         assert np.array_equal(cb[0, 0].cpu().numpy(), want)
+
+
+def test_records_of_degenerate_groups_in_16_bits(oracle):
+    # groups whose step is zero, or whose extremes leave binary16, at every place of a quad's four lanes
+    gen = torch.Generator().manual_seed(5)
+    n = 48
+    V = torch.randn(1, 1, n, 128, generator=gen)
+    V[0, 0, 1] = 0.0
+    V[0, 0, 2, 32:64] = -0.0
+    V[0, 0, 3] = 7.0
+    V[0, 0, 4, 5] = 3.0e38        # the step is infinite
+    V[0, 0, 5, 33] = -3.0e38
+    V[0, 0, 6] = 1.0e38           # a constant whose zero point is infinite and whose step is zero
+    for lane in range(4):         # an extreme held by each of the four lanes
+        V[0, 0, 8 + lane, 8 * lane] = 50.0
+        V[0, 0, 12 + lane, 8 * lane + 7] = -50.0
+    V = V.to(torch.bfloat16).cuda()
+    K = torch.randn(1, 1, n, 128, generator=gen).to(torch.bfloat16).cuda()
+    lay = sik.make_layout(1, 1, 1, 128, n, torch.bfloat16, torch.bfloat16)
+    dsl = torch.tensor([n], dtype=torch.int32, device="cuda")
+    mu, al = torch.zeros(1, 1, 128, device="cuda"), torch.zeros(1, 1, 128, device="cuda")
+    cb = torch.zeros(1, 1, 32, 16, 4, device="cuda")
+    cnt = torch.zeros(1, 1, 32, 16, dtype=torch.int32, device="cuda")
+    codes = torch.zeros(1, 1, n, 16, dtype=torch.uint8, device="cuda")
+    kvq = sik.alloc_kvq(lay)
+    sik.sik_prefill_compress(lay, K, V, dsl, mu, cb, cnt, codes, al, kvq, sik.alloc_workspace(lay, 0))
+    sync()
+    slots = kvq.cpu().numpy().reshape(n, 4, 4, 8)                  # token, group, lane of the quad, bytes
+    bits = slots[..., 4:6].copy().view(np.uint16).reshape(n, 4, 4)
+    par = slots[..., 6:8].copy().view(np.float16).reshape(n, 4, 4)
+    x = V[0, 0].cpu().float().numpy().reshape(n, 4, 32)
+    with np.errstate(all="ignore"):
+        lo, hi = x.min(-1) + np.float32(0), x.max(-1)
+        zp = lo.astype(np.float16)
+        qs = ((hi - lo) / np.float32(3) + np.float32(0)).astype(np.float16)  # a zero step is +0
+    assert np.array_equal(par[..., 3].view(np.uint16), zp.view(np.uint16))
+    assert np.array_equal(par[..., 2].view(np.uint16), qs.view(np.uint16))
+    q = ((bits[..., None] >> (2 * np.arange(8, dtype=np.uint16))) & 3).reshape(n, 4, 32)
+    assert not q[~((qs > 0) & np.isfinite(qs))].any()              # no step, or an infinite one: every code is zero
+    with np.errstate(all="ignore"):
+        want = np.clip(np.rint((x - zp.astype(np.float32)[..., None])
+                               * (np.float32(1) / qs.astype(np.float32))[..., None]), 0, 3)
+    # (the factor is the reciprocal up to its last place: a quotient that close to a half may go either way)
+    ok = (qs > 0) & np.isfinite(qs) & np.isfinite(zp)
+    t = (x - zp.astype(np.float32)[..., None])[ok] / qs.astype(np.float32)[ok][:, None]
+    clear = np.abs(t - np.floor(t) - 0.5) > 1e-6
+    assert np.array_equal(q[ok][clear], want[ok][clear])
