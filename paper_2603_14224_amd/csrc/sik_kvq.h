@@ -22,6 +22,7 @@
 
 #include "sik_attn_core.h"
 #include "sik_device.h"
+#include "sik_select.h"
 
 namespace sik {
 
@@ -156,6 +157,46 @@ __device__ __forceinline__ Q2Query q2_prepare(const uint4 qraw, const float (&al
     return r;
 }
 
+// The 2-bit codes of two records side by side, K or V, as the four bytes of a word, and from it all 16 of them as
+// floats: value e of the first record in c[0][e], of the second in c[1][e].  Masks take code e mod 4 of every byte at
+// once and a conversion picks its byte, 24 instructions where an extraction and a conversion per code are 32.  (The
+// attention over records is bound by this arithmetic: with the parameters widened before they cross the quad and
+// 32-bit offsets, 32 x 8 x 16K with 512 records per query head took 64.7 us, 66.1 without the three; 10 x 8 x 16K with
+// 1229 and 64 forced rows 66.2 per step, 68.0 without.)
+__device__ __forceinline__ void widen_codes(uint32_t two, float (&c)[2][8]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        uint32_t m = (two >> (2 * j)) & 0x03030303u;
+        asm("" : "+v"(m));  // (seen through, each code is extracted by itself again)
+        c[0][j] = static_cast<float>(m & 0xffu);
+        c[0][4 + j] = static_cast<float>((m >> 8) & 0xffu);
+        c[1][j] = static_cast<float>((m >> 16) & 0xffu);
+        c[1][4 + j] = static_cast<float>(m >> 24);
+    }
+}
+__device__ __forceinline__ uint32_t two_k_codes(const uint2 r0, const uint2 r1) {
+    return __builtin_amdgcn_perm(r1.x, r0.x, 0x07060302u);
+}
+__device__ __forceinline__ uint32_t two_v_codes(const uint2 r0, const uint2 r1) {
+    return __builtin_amdgcn_perm(r1.y, r0.y, 0x05040100u);
+}
+
+// The four parameters of a record's group: each lane of the quad widens the one that its slot holds.
+__device__ __forceinline__ void group_parameters(const uint2 r, float& kqs, float& kzp, float& vqs, float& vzp) {
+    const uint32_t par = __float_as_uint(fp16_value(r.y >> 16));
+    kqs = __uint_as_float(quad_bcast<0>(par));
+    kzp = __uint_as_float(quad_bcast<1>(par));
+    vqs = __uint_as_float(quad_bcast<2>(par));
+    vzp = __uint_as_float(quad_bcast<3>(par));
+}
+
+// Slot p of record t (t < kMaxLen, so that the offset fits 32 bits beside a base that is the same in every lane).
+__device__ __forceinline__ uint2 load_slot(const uint2* __restrict__ rec, uint32_t t, int p) {
+    static_assert(static_cast<uint64_t>(kMaxLen) * kRecBytes < (1ull << 32), "32-bit offsets");
+    return *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(rec) +
+                                           (t * static_cast<uint32_t>(kRecBytes) + static_cast<uint32_t>(p) * 8u));
+}
+
 // attend_list over records: same contract as attend_list (entries first + it * step + 0..31 per wavefront
 // iteration, 8 rows per 16-lane group so that 8 x 8 B loads are in flight per lane).  rec = the (sequence,
 // KV head)'s records as uint2 slots.
@@ -175,31 +216,32 @@ __device__ __forceinline__ void attend_list_q2(Fetch fetch, int n, int first, in
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             id[u] = __shfl(mine, 4 * u + slot, 64);
-            const bool ok = id[u] >= 0 && id[u] < Lmax;
-            const size_t t = ok ? static_cast<size_t>(id[u]) : 0;
+            const bool ok = static_cast<uint32_t>(id[u]) < static_cast<uint32_t>(Lmax);
+            r[u] = load_slot(rec, ok ? static_cast<uint32_t>(id[u]) : 0u, p);
             id[u] = ok ? id[u] : -1;
-            r[u] = rec[t * kRecSlots + p];
         }
         float z[U], vqs[U], vzp[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t par = r[u].y >> 16;
-            const float kqs = fp16_value(quad_bcast<0>(par)), kzp = fp16_value(quad_bcast<1>(par));
-            vqs[u] = fp16_value(quad_bcast<2>(par));
-            vzp[u] = fp16_value(quad_bcast<3>(par));
-            // sign of the product q_e alpha_e K'_e: minus where exactly one of (code bit clear, q alpha < 0)
-            const uint32_t flip = ((~r[u].x) ^ qq.neg) << 24;  // bit 31-e = flip channel e
-            const uint32_t kb = r[u].x >> 16;
-            float a = 0.0f, bsum = 0.0f;
+        for (int u0 = 0; u0 < U; u0 += 2) {
+            float c[2][8];
+            widen_codes(two_k_codes(r[u0], r[u0 + 1]), c);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float t = __uint_as_float(__float_as_uint(qq.absqa[e]) | ((flip << e) & 0x80000000u));
-                const float c = static_cast<float>((kb >> (2 * e)) & 3u);
-                a = fmaf(t, c, a);
-                bsum += t;
+            for (int x = 0; x < 2; ++x) {
+                const int u = u0 + x;
+                float kqs, kzp;
+                group_parameters(r[u], kqs, kzp, vqs[u], vzp[u]);
+                // sign of the product q_e alpha_e K'_e: minus where exactly one of (code bit clear, q alpha < 0)
+                const uint32_t flip = ((~r[u].x) ^ qq.neg) << 24;  // bit 31-e = flip channel e
+                float a = 0.0f, bsum = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float t = __uint_as_float(__float_as_uint(qq.absqa[e]) | ((flip << e) & 0x80000000u));
+                    a = fmaf(t, c[x][e], a);
+                    bsum += t;
+                }
+                const float dot = row16_sum(fmaf(kqs, a, kzp * bsum)) * scale_log2e;
+                z[u] = id[u] >= 0 ? dot : kNegBig;
             }
-            const float dot = row16_sum(fmaf(kqs, a, kzp * bsum)) * scale_log2e;
-            z[u] = id[u] >= 0 ? dot : kNegBig;
         }
         float mnew = st.m;
 #pragma unroll
@@ -210,15 +252,19 @@ __device__ __forceinline__ void attend_list_q2(Fetch fetch, int n, int first, in
 #pragma unroll
         for (int e = 0; e < 8; ++e) st.acc[e] *= corr;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float pu = id[u] >= 0 ? fast_exp2(z[u] - mnew) : 0.0f;
-            st.l += pu;
-            const float ps = pu * vqs[u];
-            zsum = fmaf(pu, vzp[u], zsum);
-            const uint32_t vb = r[u].y;
+        for (int u0 = 0; u0 < U; u0 += 2) {
+            float c[2][8];
+            widen_codes(two_v_codes(r[u0], r[u0 + 1]), c);
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                st.acc[e] = fmaf(ps, static_cast<float>((vb >> (2 * e)) & 3u), st.acc[e]);
+            for (int x = 0; x < 2; ++x) {
+                const int u = u0 + x;
+                const float pu = id[u] >= 0 ? fast_exp2(z[u] - mnew) : 0.0f;
+                st.l += pu;
+                const float ps = pu * vqs[u];
+                zsum = fmaf(pu, vzp[u], zsum);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) st.acc[e] = fmaf(ps, c[x][e], st.acc[e]);
+            }
         }
         st.m = mnew;
     }
