@@ -339,7 +339,11 @@ __global__ __launch_bounds__(kBlock, 4) void select_attend_kernel(
 
     // ---- 5. last workgroup of the head: candidates, merge, output ------------------------------
     // All exchange loads go out together: the (m, l) pair of every chunk (thread c), the first 8
-    // chunks' o[d] (thread d), and one candidate region per thread.
+    // chunks' o[d] (thread d), and one candidate region per thread, which goes into the list in LDS before anything
+    // else is done.  (Its 33 registers used to stay live across the block that stores the (m, l) pairs and the branch
+    // to the fallback; the compiler then kept 4 of them in scratch memory in the 2-bit kernels, with a wait after each
+    // of these loads.  8 layers of 1 x 8 x 32K records: 201.8 us per pass with that, now 197.3; 16-bit rows, where
+    // nothing was spilled: 196.9, now 195.5; 16 steps on 1 x 8 x 128K rows: 689, now 679.)
     const int need = kk - min(cgt, kk);
     int32_t* olist = orow ? orow : idx_ws + static_cast<size_t>(row) * k;
     constexpr int kOPre = 8;
@@ -352,15 +356,27 @@ __global__ __launch_bounds__(kBlock, 4) void select_attend_kernel(
 #pragma unroll
     for (int s2 = 0; s2 < kOPre; ++s2)
         o_pre[s2] = (tid < kD && s2 < nact) ? ld_agent(&prow[static_cast<size_t>(s2) * kPartStride + 2 + tid]) : 0.0f;
-    const bool want_cands = need > 0 && ranked;
-    uint32_t cn = 0u, ent[2 * kWaveCand];
-    if (want_cands && tid < nact * 4) {
-        cn = ld_agent(&crow[tid]);
+    SIK_TL_ANY(32);
+    if (need > 0 && ranked && tid < nact * 4) {
+        uint32_t cn = ld_agent(&crow[tid]);
+        uint64_t ent[kWaveCand];
 #pragma unroll
-        for (int e = 0; e < kWaveCand; ++e) {
-            const uint64_t pr = ld_agent(&cpairs[e * regions + tid]);
-            ent[2 * e] = static_cast<uint32_t>(pr);
-            ent[2 * e + 1] = static_cast<uint32_t>(pr >> 32);
+        for (int e = 0; e < kWaveCand; ++e) ent[e] = ld_agent(&cpairs[e * regions + tid]);
+        if (cn > 0u) {
+            if (cn > static_cast<uint32_t>(kWaveCand)) {
+                s_over = 1;  // the rest of this wavefront's candidates is in the pool
+                cn = kWaveCand;
+            }
+            const uint32_t base = atomicAdd(&s_ncand, cn);
+#pragma unroll
+            for (int e = 0; e < kWaveCand; ++e) {
+                if (static_cast<uint32_t>(e) < cn && base + e < static_cast<uint32_t>(kCandCap)) {
+                    // one 64-bit sort key per candidate: score key above, inverted index below, so
+                    // that "larger" means better score, then smaller index
+                    l_cand[2 * (base + e)] = ~static_cast<uint32_t>(ent[e] >> 32);
+                    l_cand[2 * (base + e) + 1] = static_cast<uint32_t>(ent[e]);
+                }
+            }
         }
     }
     float* pml = reinterpret_cast<float*>(l_sel[0]);  // [2][kMaxChunks] in LDS (l_sel is free by now)
@@ -369,26 +385,9 @@ __global__ __launch_bounds__(kBlock, 4) void select_attend_kernel(
         pml[kMaxChunks + tid] = pl;
     }
     init_state(st);
-    SIK_TL_ANY(32);
     if (need > 0) {
         bool use_radix = !ranked;
         if (ranked) {
-            if (tid < nact * 4 && cn > 0u) {
-                if (cn > static_cast<uint32_t>(kWaveCand)) {
-                    s_over = 1;  // the rest of this wavefront's candidates is in the pool
-                    cn = kWaveCand;
-                }
-                const uint32_t base = atomicAdd(&s_ncand, cn);
-#pragma unroll
-                for (int e = 0; e < kWaveCand; ++e) {
-                    if (static_cast<uint32_t>(e) < cn && base + e < static_cast<uint32_t>(kCandCap)) {
-                        // one 64-bit sort key per candidate: score key above, inverted index below, so
-                        // that "larger" means better score, then smaller index
-                        l_cand[2 * (base + e)] = ~ent[2 * e + 1];
-                        l_cand[2 * (base + e) + 1] = ent[2 * e];
-                    }
-                }
-            }
             __syncthreads();
             if (s_over != 0) {
                 const uint32_t np = min(ld_agent(&counters[row * 8 + 4]), static_cast<uint32_t>(kCandCap));

@@ -1,0 +1,57 @@
+"""Registers and scratch memory of the built kernels, as the compiler recorded them in the library (no GPU needed)."""
+import struct
+
+import pytest
+
+import paper_2603_14224_amd as sik
+from paper_2603_14224_amd.build import LIB
+
+msgpack = pytest.importorskip("msgpack")
+
+
+def _sections(elf):
+    """name -> (offset, size) of a 64-bit little-endian ELF image."""
+    off, = struct.unpack_from("<Q", elf, 0x28)
+    size, count, names = struct.unpack_from("<HHH", elf, 0x3A)
+    heads = [struct.unpack_from("<IIQQQQIIQQ", elf, off + i * size) for i in range(count)]
+    at = heads[names][4]
+    return {elf[at + h[0]:elf.index(b"\0", at + h[0])].decode(): (h[4], h[5]) for h in heads}
+
+
+def _kernels():
+    """Mangled name -> metadata record of every gfx950 kernel in the library: each source file's code object lies in a
+    bundle of its own, and its notes hold the records as one MessagePack map."""
+    sik.lib()  # builds the library if there is none
+    with open(LIB, "rb") as f:
+        image = f.read()
+    off, size = _sections(image)[".hip_fatbin"]
+    fat, found = image[off:off + size], {}
+    at = fat.find(b"__CLANG_OFFLOAD_BUNDLE__")
+    while at >= 0:
+        entries, = struct.unpack_from("<Q", fat, at + 24)
+        p = at + 32
+        for _ in range(entries):
+            begin, length, name = struct.unpack_from("<QQQ", fat, p)
+            target = fat[p + 24:p + 24 + name]
+            p += 24 + name
+            if b"gfx950" not in target:
+                continue
+            code = fat[at + begin:at + begin + length]
+            note, _ = _sections(code)[".note"]
+            owner, desc, _ = struct.unpack_from("<III", code, note)
+            start = note + 12 + (owner + 3) // 4 * 4
+            for k in msgpack.unpackb(code[start:start + desc], strict_map_key=False)["amdhsa.kernels"]:
+                found[k[".name"]] = k
+        at = fat.find(b"__CLANG_OFFLOAD_BUNDLE__", at + 1)
+    return found
+
+
+@pytest.mark.parametrize("part", ["select_attend_kernel", "attn_q2_kernel", "compress_kernel", "quantize_kv_kernel",
+                                  "encode_kernel"])
+def test_no_scratch_memory(part):
+    # a spilled register in the last workgroup's exchange puts a wait in front of loads that are meant to go out together
+    some = {n: k for n, k in _kernels().items() if part in n}
+    assert some
+    bad = {n: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for n, k in some.items()
+           if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
+    assert not bad
