@@ -120,7 +120,6 @@ __device__ __forceinline__ uint2 kvq_make_slot(const uint4 kraw, const uint4 vra
                                                const float (&ralpha)[8], int p) {
     float kf[8], vf[8], kh[8];
     widen8<DT>(kraw, kf);
-    widen8<DT>(vraw, vf);
     uint32_t sign = 0u;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -130,6 +129,7 @@ __device__ __forceinline__ uint2 kvq_make_slot(const uint4 kraw, const uint4 vra
     }
     uint32_t kqs, kzp, vqs, vzp;
     const uint32_t kbits = quantize_octet(kh, kqs, kzp);
+    widen8<DT>(vraw, vf);  // not before the key is done with: 8 registers less at the peak (compress_kernel)
     const uint32_t vbits = quantize_octet(vf, vqs, vzp);
     const uint32_t kpar = p & 1 ? kzp : kqs, vpar = p & 1 ? vzp : vqs;
     return make_uint2(sign | (kbits << 16), vbits | ((p & 2 ? vpar : kpar) << 16));

@@ -407,7 +407,10 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const uint16_t* __r
 // in blocks of kCmpBlock tokens and meet at a barrier after every block, so that the second reader of a key row
 // finds it in the L2 cache: HBM sees K once here and V once.  (Measured on 4 x 8 x 64K keys: without the barrier
 // 10 % slower; 64-token blocks need more registers than three workgroups per compute unit leave; the launch bound
-// of five wavefronts per SIMD, 102 registers, beats six, which spills.)
+// of five wavefronts per SIMD, 102 registers, beats six, which spills.)  With at most 80 registers four workgroups
+// share a compute unit, as many as their LDS allows, and a test holds the kernel to that: with 83 for fp16, three
+// workgroups, 32 x 8 x 1024 fp16 keys and values took 66.7 us for the whole fit, with 79 they take 63.2; 4 x 8 x 64K
+// 423.9 and 412.5 (bf16, 77 and 74 registers: 61.5 and 61.3, 403.2 and 400.9).
 constexpr int kCmpThreads = kEncThreads + 4 * kWave;
 constexpr int kCmpBlock = 32;       // tokens per block: 8 steps of the encoders, 2 steps of the record builders
 constexpr int kCmpEncSteps = kCmpBlock / kEncTokPerIter;

@@ -55,3 +55,12 @@ def test_no_scratch_memory(part):
     bad = {n: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for n, k in some.items()
            if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
     assert not bad
+
+
+def test_registers_leave_room_for_four_compressing_workgroups():
+    # 4 workgroups x 6 wavefronts on 4 SIMDs with 512 registers each, in steps of 8: 80 registers per lane
+    some = {n: k for n, k in _kernels().items() if "compress_kernel" in n}
+    assert len(some) == 2
+    assert all(k[".max_flat_workgroup_size"] == 384 and k[".group_segment_fixed_size"] <= 160 * 1024 // 4
+               for k in some.values())
+    assert all(k[".vgpr_count"] <= 80 for k in some.values()), {n: k[".vgpr_count"] for n, k in some.items()}
