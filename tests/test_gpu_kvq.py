@@ -526,14 +526,15 @@ def test_prefill_compress_argument_errors():
     assert e.value.status == -6
 
 
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 63, 64, 65, 128, 191])
-def test_tokens_of_one_code_are_added_in_token_order(n):
+def test_tokens_of_one_code_are_added_in_token_order(n, dtype):
     # The encoder takes a lane's tokens in twos and lets the second add to the first one's sum where their codes agree:
-    # here they always do (all keys on one side of the mean but the first), at the edges of its blocks of 32 and 64.
+    # here they always do (all keys but the first lie above the mean), at the edges of its blocks of 32 and 64.
     x = torch.rand(n, 128, generator=torch.Generator().manual_seed(n)).add_(1.0)
-    x[0] = -100.0
-    lay = sik.make_layout(1, 1, 1, 128, n, torch.float16, torch.float16)
-    K = x.to(torch.float16)[None, None].cuda()
+    x[0] = -100.0 - 2.0 * n
+    lay = sik.make_layout(1, 1, 1, 128, n, dtype, dtype)
+    K = x.to(dtype)[None, None].cuda()
     dsl = torch.tensor([n], dtype=torch.int32, device="cuda")
     for one_call in (False, True):
         mu, al = torch.zeros(1, 1, 128, device="cuda"), torch.zeros(1, 1, 128, device="cuda")
@@ -547,6 +548,7 @@ def test_tokens_of_one_code_are_added_in_token_order(n):
             sik.sik_quantize_keys(lay, K, dsl, 0, 0, sik.SIK_Q_FIT, mu, cb, cnt, codes, ws)
         sync()
         m, k = mu[0, 0].cpu().numpy(), K[0, 0].cpu().float().numpy()
+        assert (k[1:] >= m).all()
         assert np.array_equal(codes[0, 0].cpu().numpy(), np.packbits(k >= m, axis=-1))
         c = cnt[0, 0].cpu().numpy()
         assert c.sum() == 32 * n
@@ -555,8 +557,32 @@ def test_tokens_of_one_code_are_added_in_token_order(n):
         assert np.array_equal(cb[0, 0].cpu().numpy(), want)
 
 
-def test_records_of_degenerate_groups_in_16_bits(oracle):
-    # groups whose step is zero, or whose extremes leave binary16, at every place of a quad's four lanes
+def check_groups(x, bits, par):
+    """Records of groups x [n, 4, 32] (binary32, as the builder sees them) against the quantisation function: bits
+    [n, 4, 4] the code words of a group's four lanes, par [n, 4, 2] its step and zero point.  A NaN among the values is
+    left out of the extremes and has the code zero."""
+    with np.errstate(all="ignore"):
+        lo, hi = np.fmin.reduce(x, -1) + np.float32(0), np.fmax.reduce(x, -1)   # a zero minimum is +0
+        zp = lo.astype(np.float16)
+        # a zero step is +0; a span beyond binary32 has no third
+        qs = np.where(np.isinf(hi - lo), np.float32(np.nan), (hi - lo) / np.float32(3) + np.float32(0)).astype(np.float16)
+        for got, want in ((par[..., 0], qs), (par[..., 1], zp)):
+            assert np.array_equal(np.isnan(got), np.isnan(want))
+            assert np.array_equal(got.view(np.uint16)[~np.isnan(want)], want.view(np.uint16)[~np.isnan(want)])
+        q = ((bits[..., None] >> (2 * np.arange(8, dtype=np.uint16))) & 3).reshape(x.shape)
+        step = (qs > 0) & np.isfinite(qs)
+        assert not q[~step].any()          # no step, or none that is a number: every code is zero
+        assert not q[np.isnan(x)].any()
+        t = (x - zp.astype(np.float32)[..., None]) / qs.astype(np.float32)[..., None]
+        want = np.clip(np.rint((x - zp.astype(np.float32)[..., None])
+                               * (np.float32(1) / qs.astype(np.float32))[..., None]), 0, 3)
+        # (the factor is the reciprocal up to its last place: a quotient that close to a half may go either way)
+        clear = (step & np.isfinite(zp))[..., None] & ~np.isnan(x) & (np.abs(t - np.floor(t) - 0.5) > 1e-6)
+    assert np.array_equal(q[clear], want[clear])
+
+
+def test_records_of_degenerate_groups_in_16_bits():
+    # groups without a step, with extremes beyond binary16 or binary32, and with NaN, at every place of a quad's lanes
     gen = torch.Generator().manual_seed(5)
     n = 48
     V = torch.randn(1, 1, n, 128, generator=gen)
@@ -566,11 +592,22 @@ def test_records_of_degenerate_groups_in_16_bits(oracle):
     V[0, 0, 4, 5] = 3.0e38        # the step is infinite
     V[0, 0, 5, 33] = -3.0e38
     V[0, 0, 6] = 1.0e38           # a constant whose zero point is infinite and whose step is zero
-    for lane in range(4):         # an extreme held by each of the four lanes
+    for lane in range(4):         # an extreme held by each of the four lanes, and a value that is none
         V[0, 0, 8 + lane, 8 * lane] = 50.0
         V[0, 0, 12 + lane, 8 * lane + 7] = -50.0
-    V = V.to(torch.bfloat16).cuda()
-    K = torch.randn(1, 1, n, 128, generator=gen).to(torch.bfloat16).cuda()
+        V[0, 0, 16 + lane, 8 * lane + lane] = float("nan")
+        V[0, 0, 20 + lane, 32 + 8 * lane:40 + 8 * lane] = float("nan")  # all eight of a lane
+    V[0, 0, 24, 64:96] = float("nan")
+    V[0, 0, 25, 3], V[0, 0, 25, 30] = 3.0e38, -3.0e38  # their difference overflows: the step is NaN
+    V[0, 0, 26, 100] = float("inf")
+    V[0, 0, 27, 100] = float("-inf")
+    V = V.to(torch.bfloat16)
+    V.view(torch.int16)[0, 0, 28, 8] = 0x7f81          # a signalling NaN
+    K = torch.randn(1, 1, n, 128, generator=gen).to(torch.bfloat16)
+    K[0, 0, :, 32:64] = 0.75      # a group of channels that never leave their mean
+    K[0, 0, 7, 70] = float("nan")  # its channel has no mean and no scale
+    K[0, 0, 9, 96:104] = 40.0
+    K, V = K.cuda(), V.cuda()
     lay = sik.make_layout(1, 1, 1, 128, n, torch.bfloat16, torch.bfloat16)
     dsl = torch.tensor([n], dtype=torch.int32, device="cuda")
     mu, al = torch.zeros(1, 1, 128, device="cuda"), torch.zeros(1, 1, 128, device="cuda")
@@ -581,22 +618,28 @@ def test_records_of_degenerate_groups_in_16_bits(oracle):
     sik.sik_prefill_compress(lay, K, V, dsl, mu, cb, cnt, codes, al, kvq, sik.alloc_workspace(lay, 0))
     sync()
     slots = kvq.cpu().numpy().reshape(n, 4, 4, 8)                  # token, group, lane of the quad, bytes
-    bits = slots[..., 4:6].copy().view(np.uint16).reshape(n, 4, 4)
+    kbits, vbits = (slots[..., a:a + 2].copy().view(np.uint16).reshape(n, 4, 4) for a in (2, 4))
     par = slots[..., 6:8].copy().view(np.float16).reshape(n, 4, 4)
-    x = V[0, 0].cpu().float().numpy().reshape(n, 4, 32)
+    m, a = mu[0, 0].cpu().numpy(), al[0, 0].cpu().numpy()
+    assert np.isnan(m[70]) and np.isfinite(np.delete(m, 70)).all() and not a[32:64].any()
     with np.errstate(all="ignore"):
-        lo, hi = x.min(-1) + np.float32(0), x.max(-1)
-        zp = lo.astype(np.float16)
-        qs = ((hi - lo) / np.float32(3) + np.float32(0)).astype(np.float16)  # a zero step is +0
-    assert np.array_equal(par[..., 3].view(np.uint16), zp.view(np.uint16))
-    assert np.array_equal(par[..., 2].view(np.uint16), qs.view(np.uint16))
-    q = ((bits[..., None] >> (2 * np.arange(8, dtype=np.uint16))) & 3).reshape(n, 4, 32)
-    assert not q[~((qs > 0) & np.isfinite(qs))].any()              # no step, or an infinite one: every code is zero
-    with np.errstate(all="ignore"):
-        want = np.clip(np.rint((x - zp.astype(np.float32)[..., None])
-                               * (np.float32(1) / qs.astype(np.float32))[..., None]), 0, 3)
-    # (the factor is the reciprocal up to its last place: a quotient that close to a half may go either way)
-    ok = (qs > 0) & np.isfinite(qs) & np.isfinite(zp)
-    t = (x - zp.astype(np.float32)[..., None])[ok] / qs.astype(np.float32)[ok][:, None]
-    clear = np.abs(t - np.floor(t) - 0.5) > 1e-6
-    assert np.array_equal(q[ok][clear], want[ok][clear])
+        x = np.abs(K[0, 0].cpu().float().numpy() - m) * np.where(a > 0, np.float32(1) / a, np.float32(0))
+    check_groups(x.reshape(n, 4, 32), kbits, par[..., 0:2])
+    check_groups(V[0, 0].cpu().float().numpy().reshape(n, 4, 32), vbits, par[..., 2:4])
+
+
+def test_attention_over_few_records_with_gaps(oracle):
+    # two records are unpacked side by side: the first, the second or both of a pair missing, up to one gather step
+    cfg = cfg_small(batch=1, n_kv_heads=1, n_q_heads=33, context=40, top_k=33, seed=46)
+    st = Q2State(cfg, oracle, out_dtype=torch.float32)
+    q, _, _ = W.make_step_inputs(cfg, 1)
+    idx = np.full((1, 33, 33), -1, np.int32)
+    rng = np.random.default_rng(46)
+    for h in range(33):  # head h attends h + 1 records at places of the list drawn at random
+        idx[0, h, rng.permutation(33)[:h + 1]] = rng.permutation(40)[:h + 1]
+    out = torch.empty(1, 33, 128, device="cuda")
+    sik.sik_sparse_attn_q2(st.layout, dev(q, cfg.dtype), torch.from_numpy(st.records()).cuda(),
+                           torch.from_numpy(st.alpha).cuda(), torch.from_numpy(idx).cuda(), 33, 0.0, out, st.ws)
+    sync()
+    ref = oracle.sparse_attn_q2(q, cfg.dtype, st.codes, st.qkv, st.alpha, idx)
+    check_attention(out.cpu().numpy().astype(np.float64), ref, True)
