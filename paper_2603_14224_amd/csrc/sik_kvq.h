@@ -16,8 +16,8 @@
 // V: x = the value.  K: x = |K - mu| * (1 / alpha) (alpha = per-channel max of |K - mu| over the fitted
 // tokens; alpha = 0 gives x = 0), the sign travels as the code bit: K' ~ s alpha D.
 // The codes are decided in binary32 in exactly this operation order: the two divisions of the paper's
-// formulas are multiplications by a correctly rounded reciprocal (one per channel, one per group), which keeps
-// the quantiser bound by memory instead of by per-element divisions.
+// formulas are multiplications by a correctly rounded reciprocal (one per channel, one per group), which spares
+// the quantiser a division per element.
 #pragma once
 
 #include "sik_attn_core.h"
@@ -162,7 +162,7 @@ __device__ __forceinline__ Q2Query q2_prepare(const uint4 qraw, const float (&al
 // once and a conversion picks its byte, 24 instructions where an extraction and a conversion per code are 32.  (The
 // attention over records is bound by this arithmetic: with the parameters widened before they cross the quad and
 // 32-bit offsets, 32 x 8 x 16K with 512 records per query head took 64.7 us, 66.1 without the three; 10 x 8 x 16K with
-// 1229 and 64 forced rows 66.2 per step, 68.0 without.)
+// 1229 and 64 forced rows 66.2 per step, 68.0 without; 65.4 since the exchange there no longer spills.)
 __device__ __forceinline__ void widen_codes(uint32_t two, float (&c)[2][8]) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {

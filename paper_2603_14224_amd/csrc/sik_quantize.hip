@@ -219,9 +219,10 @@ __global__ __launch_bounds__(S * kD) void mean_kernel(const double* __restrict__
 // 4g .. 4g+3 (a wavefront load covers two complete 256 B rows) and derives the group's 4-bit Code.
 // The cluster accumulators are private to the lane - LDS columns tabs[Code][lane] (the four sums as one
 // float4: a 16-lane phase of the 128-bit access covers all 64 banks once, whatever the Codes) and
-// tabc[Code][lane] (the count), always on the lane's own banks - so they are updated with plain
-// read-add-write in token order: no atomics (LDS float atomics ran this kernel at 0.4 TB/s) and a
-// sum order that does not depend on scheduling.  Workgroup partials go to part[unit][wg][g][80].
+// tabc[Code][lane] (the count), always on the lane's own banks.  The sums are updated with plain
+// read-add-write, two tokens per step and in token order: no float atomics (in LDS they ran this kernel at
+// 0.4 TB/s) and a sum order that does not depend on scheduling.  The counts are LDS integer adds without a
+// result, where order does not matter.  Workgroup partials go to part[unit][wg][g][80].
 // Two wavefronts encode whatever the launch, two tokens each per step, so that the four chains in which a workgroup's
 // sums are added up, and with them the bits of the codebook, do not depend on the launch (eight chains, from four
 // wavefronts in launches of two workgroups per compute unit, moved centroids by an ulp and with them the tokens that
@@ -305,7 +306,8 @@ struct SignEncoder {
         }
     }
     // N tokens of this lane, i, i + kEncTokPerIter, ...; `whole`, the same in every lane, where all lanes of the
-    // workgroup have all of theirs before `end`
+    // workgroup have all of theirs before `end`.  The tokens of a block that is not whole go one at a time: 60 of the
+    // 252 in a workgroup's range at 8 x 2000 to 12345 keys, where the pairs give 5 to 6 % of the whole fit instead of 9.
     template <int N>
     __device__ __forceinline__ void tokens(int i, const uint2 (&v)[N], int end, bool whole) {
         static_assert(N % 2 == 0, "tokens are taken in twos");
