@@ -143,7 +143,7 @@ int sik_plan_info(const sik_layout* layout, int32_t* info) {
     size_t dyn;
     int listcap, snc;
     const int tt = step_plan(d, 1, false, device_compute_units(), false, false, &snc, &dyn, &listcap);
-    info[7] = tt / 100 + tt % 100;
+    info[7] = step_chunk_k(tt);
     return SIK_OK;
 }
 

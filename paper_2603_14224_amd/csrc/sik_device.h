@@ -232,4 +232,22 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     return t;
 }
 
+// Inclusive sums over the lanes at or below this one: of its 16-lane DPP row, of the wavefront (rows of 16 by shifted
+// moves, then the last lane of the rows before: no LDS traffic).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t plus_dpp(uint32_t v) {
+    return v + static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ uint32_t row16_inclusive_sum(uint32_t v) {
+    v = plus_dpp<0x111, 0xf>(v);  // row_shr:1 (a lane without a source adds zero)
+    v = plus_dpp<0x112, 0xf>(v);
+    v = plus_dpp<0x114, 0xf>(v);
+    return plus_dpp<0x118, 0xf>(v);
+}
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
+    v = row16_inclusive_sum(v);
+    v = plus_dpp<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    return plus_dpp<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+}
+
 }  // namespace sik

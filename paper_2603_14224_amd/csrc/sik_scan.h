@@ -7,6 +7,7 @@
 namespace sik {
 
 constexpr int kHB = 4;  // query heads per workgroup = components of one float4 table entry
+constexpr int kHBPair = 2;  // the same where two workgroups of the one-launch step share a compute unit
 
 // (byte BY of w) & mask in one instruction (sub-dword operand select), for any BY; the compiler finds this form
 // for the upper byte and the upper half only.
@@ -28,8 +29,8 @@ __device__ __forceinline__ uint32_t byte_and(uint32_t w, uint32_t mask) {
     return r;
 }
 
-// Table lookups.  HB = 4: float4 entries (four query heads at once), 256 B per group; HB = 1: scalar entries,
-// 64 B per group (one query head per KV head: multi-head attention, or the summed query of a group-shared
+// Table lookups.  HB = 4: float4 entries (four query heads at once), 256 B per group; HB = 2: float2 entries, 128 B;
+// HB = 1: scalar entries, 64 B per group (one query head per KV head: multi-head attention, or the summed query of a group-shared
 // selection) - a quarter of the LDS traffic, the 16 entries of a group on 16 different banks.
 // A batch = the 8 lookups of one 32-bit word of a token's code (groups 8 dw .. 8 dw + 7).  A table offset costs
 // one instruction: byte b of the code word, or of the word shifted by one nibble, under the mask that leaves
@@ -43,14 +44,19 @@ struct TableEntry<4> {
     using type = float4;
 };
 
+template <>
+struct TableEntry<2> {
+    using type = float2;
+};
+
 template <int HB>
 __device__ __forceinline__ void lookup_batch(uint32_t word, int dw, const float* lut,
                                              typename TableEntry<HB>::type (&v)[8]) {
     using T = typename TableEntry<HB>::type;
     constexpr int kEnt = 4 * HB;            // bytes per table entry
     constexpr uint32_t kMask = 15u * kEnt;  // Code * kEnt
-    constexpr int kUp = HB == 4 ? 0 : 2;    // high nibble (Code * 16) -> Code * kEnt: shift right by kUp
-    constexpr int kDown = HB == 4 ? 4 : 2;  // low nibble -> Code * kEnt: shift left by kDown
+    constexpr int kUp = HB == 4 ? 0 : (HB == 2 ? 1 : 2);    // high nibble (Code * 16) -> Code * kEnt: shift right by kUp
+    constexpr int kDown = HB == 4 ? 4 : (HB == 2 ? 3 : 2);  // low nibble -> Code * kEnt: shift left by kDown
     // byte `by` of the word: high nibble = Code of group 8 dw + 2 by, low nibble = Code of the next group
     const uint32_t whi = kUp ? word >> kUp : word;
     const uint32_t wlo = word << kDown;
@@ -150,6 +156,9 @@ __device__ __forceinline__ void add_batch(bool first, const typename TableEntry<
                 acc[2] += v[n].z;
                 acc[3] += v[n].w;
             }
+        } else if constexpr (HB == 2) {
+            acc[0] = (first && n == 0) ? v[n].x : acc[0] + v[n].x;
+            acc[1] = (first && n == 0) ? v[n].y : acc[1] + v[n].y;
         } else {
             acc[0] = (first && n == 0) ? v[n] : acc[0] + v[n];
         }

@@ -13,6 +13,8 @@ namespace sik {
 constexpr int kStepT[][2] = {{1, 0}, {2, 0}, {3, 0}, {4, 0}, {6, 0}, {8, 0}, {12, 0}, {12, 4}, {14, 4}, {16, 4}};
 // instantiated tokens per thread of the variant with the 16-bit first pass (two registers per token)
 constexpr int kStepFx[] = {4, 8, 12, 16, 20};
+// the same for the variant with two heads to a workgroup of 512 threads; chunk = 512 x sum
+constexpr int kStepPair[][2] = {{16, 0}, {24, 0}, {24, 8}, {28, 8}, {32, 8}};
 // the pairs instantiated for the 2-bit cache as well
 constexpr int kStepQ2[][2] = {{1, 0}, {4, 0}, {12, 0}, {12, 4}, {14, 4}, {16, 4}};
 
@@ -27,50 +29,73 @@ int step_max_chunks(const Dims& d) {
     return byc < 1 ? 1 : (byc > kMaxChunks ? kMaxChunks : byc);
 }
 
-static size_t step_dyn_bytes(int chunk, int TL, int k, int* listcap) {
+static size_t step_dyn_bytes(int heads, int chunk, int TL, int k, int* listcap) {
+    const size_t hb = static_cast<size_t>(heads);
     const int cap = ((chunk < k ? chunk : k) + 7) & ~7;
     *listcap = cap;
-    const size_t lists = ((static_cast<size_t>(kHB) * cap * 2 + 15) & ~size_t(15)) +
-                         static_cast<size_t>(kHB) * kCandCap * 8 + static_cast<size_t>(TL) * kStepThreads * 16;
-    const size_t tail = static_cast<size_t>(kHB) * (kCandCap + 8) * 8 + static_cast<size_t>(kHB) * 2 * kCandCap * 4;
+    const size_t lists = ((hb * cap * 2 + 15) & ~size_t(15)) + hb * kCandCap * 8 +
+                         static_cast<size_t>(TL) * step_threads(heads) * hb * 4;
+    const size_t tail = hb * (kCandCap + 8) * 8 + hb * 2 * kCandCap * 4;
     return lists > tail ? lists : tail;
 }
 
 // Tokens per thread of the one-launch step for this layout, or 0 when it does not apply: the smallest T whose
 // grid fits the compute units (workgroups of a head block wait for each other, so they must all be resident);
 // a single chunk per head block needs no wait and may exceed them.
-int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool kvq, int* nchunk_out, size_t* dyn_out,
+//
+// Chunks of 8192 tokens and more on 16-bit rows go to the variant with two heads to a workgroup, two workgroups to a
+// compute unit: the scan is bound by LDS reads and vector instructions, the gather by HBM, and with one workgroup on
+// every compute unit they ran one after the other over the whole chip.  Of two workgroups the one dispatched first is served
+// first, by age, so it gathers while the other one still scans.  Scanning the codes once per pair instead of once per four
+// heads costs less than that gives, and groups of 3, 5 or 6 heads leave fewer table entries empty.  Us, four heads against
+// two: 32 x 8 x 16K with 4:1 (512 selected) 75.7 -> 69.7 ragged; 32 x 8 x 12K with 4:1 70.8 -> 66.0; 33 x 8 x 8K with 3:1
+// 78.5 -> 62.8; 16 x 8 x 16K with 5:1 71.2 -> 61.7, 7:1 79.8 -> 72.6, 8:1 84.9 -> 77.1; 16 x 8 x 20K with 8:1 115 -> 106;
+// 8 x 8 x 40K with 6:1 92.9 -> 86.6; 4 x 8 x 128K with 4:1 93.3 -> 90.7; 64 x 4 x 16K with 2:1 57.9 -> 53.7; none slower.
+// On 2-bit records the gather is bound by vector instructions too and there is little to overlap: 32 x 8 x 16K 60.7 us with
+// four heads, 64.2 with two.  Budgets whose lists do not fit the smaller LDS share (about 4000) keep four heads.
+int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool special, int* nchunk_out, size_t* dyn_out,
               int* listcap_out) {
     if (d.R < 2 || d.R > 255 || cus < 1) return 0;
-    const int hbs = d.units() * ((d.R + kHB - 1) / kHB);
-    auto fits = [&](int tokens, int tl) {
-        const int chunk = kStepThreads * tokens;
+    auto fits = [&](int heads, int tokens, int tl) {
+        const int hbs = d.units() * ((d.R + heads - 1) / heads);
+        const int chunk = step_threads(heads) * tokens;
         const int nchunk = (d.Lmax + chunk - 1) / chunk;
         if (nchunk > kMaxChunks || nchunk > step_max_chunks(d)) return false;
-        const bool resident = static_cast<int64_t>(hbs) * nchunk <= cus;
+        const bool resident = static_cast<int64_t>(hbs) * nchunk <= static_cast<int64_t>(cus) * (heads == kHB ? 1 : 2);
         if (!resident && nchunk != 1) return false;
         int listcap;
-        const size_t dyn = step_dyn_bytes(chunk, tl, k, &listcap);
-        if (dyn > kStepLdsBudget) return false;
+        const size_t dyn = step_dyn_bytes(heads, chunk, tl, k, &listcap);
+        if (dyn > step_lds_budget(heads)) return false;
         *nchunk_out = nchunk;
         *dyn_out = dyn;
         *listcap_out = listcap;
         return true;
     };
     if (fx) {
-        if (kvq) return 0;
+        if (special) return 0;
         for (const int t : kStepFx)
-            if (fits(t, 0)) return kStepFxCode + t * 100;
+            if (fits(kHB, t, 0)) return kStepFxCode + t * 100;
         return 0;
     }
-    if (kvq) {  // (the pairs instantiated for the 2-bit cache and for forced sets)
+    if (special) {  // (the pairs instantiated for the 2-bit cache and for forced sets)
         for (const auto& tt : kStepQ2)
-            if (fits(tt[0] + tt[1], tt[1])) return tt[0] * 100 + tt[1];
+            if (fits(kHB, tt[0] + tt[1], tt[1])) return tt[0] * 100 + tt[1];
         return 0;
     }
-    for (const auto& tt : kStepT)
-        if (fits(tt[0] + tt[1], tt[1])) return tt[0] * 100 + tt[1];  // both numbers in one: T * 100 + TL
+    for (const auto& tt : kStepT) {
+        if (!fits(kHB, tt[0] + tt[1], tt[1])) continue;
+        if (tt[0] + tt[1] >= 8)
+            for (const auto& pp : kStepPair)
+                if (fits(kHBPair, pp[0] + pp[1], pp[1])) return kStepPairCode + pp[0] * 100 + pp[1];
+        return tt[0] * 100 + tt[1];  // both numbers in one: T * 100 + TL
+    }
     return 0;
+}
+
+// Tokens of a chunk, in units of 1024, of the variant that a plan code names.
+int step_chunk_k(int code) {
+    const int tokens = code % 100000 / 100 + code % 100;
+    return code >= kStepPairCode ? tokens / 2 : tokens;
 }
 
 int device_compute_units() {
@@ -113,6 +138,10 @@ hipError_t launch_step(const Dims& d, const Workspace& w, int T, int nchunk, siz
     a.sstride = w.sstride, a.k = k, a.spin_limit = spin_limit > 0 ? spin_limit : (1 << 20), a.listcap = listcap;
     a.scale_log2e = (scale > 0.0f ? scale : 1.0f / sqrtf(static_cast<float>(d.D))) * 1.4426950408889634f;
     const bool out_f32 = d.out_dtype == kF32;
+    if (T >= kStepPairCode)
+        return d.kv_dtype == kBF16
+                   ? launch_step_pair_bf16(d, T, nchunk, dyn, q, codebook, codes, seq_len, K, V, a, out_f32, s)
+                   : launch_step_pair_f16(d, T, nchunk, dyn, q, codebook, codes, seq_len, K, V, a, out_f32, s);
     return d.kv_dtype == kBF16 ? launch_step_bf16(d, T, nchunk, dyn, q, codebook, codes, seq_len, K, V, a, out_f32, s)
                                : launch_step_f16(d, T, nchunk, dyn, q, codebook, codes, seq_len, K, V, a, out_f32, s);
 }

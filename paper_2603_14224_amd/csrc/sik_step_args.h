@@ -7,9 +7,8 @@
 
 namespace sik {
 
-constexpr int kStepThreads = 1024;
-constexpr int kStepWaves = kStepThreads / kWave;
 constexpr int kGroupThreads = 256;  // one group of four wavefronts per query head of the block
+constexpr int step_threads(int heads) { return heads * kGroupThreads; }  // workgroup of a block of 4 or 2 heads
 
 struct StepArgs {
     // appended row (all null: nothing is appended)
@@ -48,7 +47,10 @@ constexpr int kSyncPerRow = 4;  // ticket, index-output reservation, candidate r
 constexpr int kSyncPerSeq = 2;  // workgroups of the sequence that have left the kernel; one spare word
 
 constexpr int kStepFxCode = 100000;   // added to T * 100 in the plan's return value: the 16-bit first pass
-constexpr size_t kStepLdsBudget = 120 * 1024;  // dynamic LDS the kernel may ask for beside its static LDS
+constexpr int kStepPairCode = 800000;  // added likewise: two heads to a workgroup
+// Dynamic LDS the kernel may ask for beside its static LDS: a workgroup of four heads has a compute unit (160 KB) to
+// itself, two workgroups of two heads share one.
+constexpr size_t step_lds_budget(int heads) { return (heads == 4 ? 120 : 64) * 1024; }
 
 // The launch of the kernel variant that plan code T names (step_plan), for bf16 / fp16 K, V and q; out_f32: fp32
 // output rows instead of the storage type.
@@ -58,5 +60,13 @@ hipError_t launch_step_bf16(const Dims& d, int T, int nchunk, size_t dyn, const 
 hipError_t launch_step_f16(const Dims& d, int T, int nchunk, size_t dyn, const void* q, const float* codebook,
                            const uint8_t* codes, int32_t* seq_len, const void* K, const void* V, const StepArgs& a,
                            bool out_f32, hipStream_t s);
+
+// The same for the variants with two heads to a workgroup (kStepPairCode).
+hipError_t launch_step_pair_bf16(const Dims& d, int T, int nchunk, size_t dyn, const void* q, const float* codebook,
+                                 const uint8_t* codes, int32_t* seq_len, const void* K, const void* V, const StepArgs& a,
+                                 bool out_f32, hipStream_t s);
+hipError_t launch_step_pair_f16(const Dims& d, int T, int nchunk, size_t dyn, const void* q, const float* codebook,
+                                const uint8_t* codes, int32_t* seq_len, const void* K, const void* V, const StepArgs& a,
+                                bool out_f32, hipStream_t s);
 
 }  // namespace sik

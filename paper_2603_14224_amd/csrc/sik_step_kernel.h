@@ -2,16 +2,17 @@
 // sparse attention ("Compressed-Domain Top-k Retrieval" followed by softmax(q K_S^T / sqrt(d)) V_S of "Background
 // and Preliminaries"), with the scores never leaving the chip.
 //
-// Workgroup (1024 threads, one per compute unit) = (sequence, KV head, block of up to 4 query heads, token chunk
-// of 1024 (T + TL) tokens).  A thread scores T + TL tokens for the block's heads and KEEPS the fp32 scores on the
-// chip: T tokens' in registers, TL tokens' in LDS.
+// Workgroup = (sequence, KV head, block of up to HB query heads, token chunk): HB = 4 with 1024 threads, one workgroup
+// per compute unit and chunks of 1024 (T + TL) tokens, or HB = 2 with 512 threads, two workgroups per compute unit and
+// chunks of 512 (T + TL) tokens (which of the two: step_plan).  A thread scores T + TL tokens for the block's heads and
+// KEEPS the fp32 scores on the chip: T tokens' in registers, TL tokens' in LDS.
 //   1. tables in LDS, scan of the chunk's codes, one 512-bin LDS histogram per head (as in the scoring kernel);
 //   2. chunks of one head block exchange their histograms through memory: publish, arrive on a counter, wait
 //      until all active chunks arrived (a BOUNDED spin: on give-up the status word of the workspace is set and the
 //      workgroup leaves), read the others' histograms; with a single chunk per head block there is nothing to
 //      exchange and no wait;
 //   3. every workgroup derives the head's threshold bin, classifies its scores from the registers, compacts the
-//      selected tokens of each head into an LDS list (deterministic order) and gathers them at once: 16
+//      selected tokens of each head into an LDS list (deterministic order) and gathers them at once: its
 //      wavefronts = (head, slice of the list); with one chunk the threshold bin's candidates are ranked before
 //      the gather and join the list;
 //   4. several chunks: chunk partials (m, l, o[D]) and the threshold-bin candidates go to memory; the last
@@ -20,7 +21,7 @@
 // Variants: KVQ gathers 128-byte records of the 2-bit cache and dequantises them in registers; FX runs the scan in
 // 16-bit fixed point and gives exact scores only to the tokens within a guard band of the threshold bin.
 // The launch must be co-resident when a head block has more than one chunk (its workgroups wait for each other):
-// the host only takes this path when the grid fits the compute units.  An appended row needs no wait: its new
+// the host only takes this path when the grid fits the compute units (HB = 2: twice their number).  An appended row needs no wait: its new
 // length is published by the last workgroup of the sequence to leave.  Every counter the kernel uses is left at
 // zero by its last user, so the workspace's sync words need zeroing only once (sik_workspace_init).
 #include <atomic>
@@ -96,54 +97,77 @@ __device__ __forceinline__ uint32_t group_suffix_sum(uint32_t v, uint32_t* lds4)
     return v;
 }
 
-template <int DT, int ODT, int T, int TL, bool FX = false, bool KVQ = false, bool FORCED = false>
-__global__ __launch_bounds__(kStepThreads) void step_kernel(
+__device__ __forceinline__ float uniform(float x) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+// mask = 2 mask + (x >= bound; false for a NaN): one compare, one add with carry.  bound: the same in every lane
+__device__ __forceinline__ void push_ge(uint32_t& mask, float x, float bound) {
+    asm("v_cmp_le_f32 vcc, %2, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(mask) : "v"(x), "s"(bound) : "vcc");
+}
+
+// The token slot of the lowest bit of word w of a mask that push_ge filled: slots 32 w .. min(TT, 32 w + 32) - 1, the last
+// one in bit 0.
+template <int TT>
+__device__ __forceinline__ int mask_slot(int w, uint32_t mask) {
+    return (TT < 32 * w + 32 ? TT : 32 * w + 32) - __ffs(static_cast<int>(mask));
+}
+__device__ __forceinline__ float4 make_entry(const float (&x)[4]) { return make_float4(x[0], x[1], x[2], x[3]); }
+__device__ __forceinline__ float2 make_entry(const float (&x)[2]) { return make_float2(x[0], x[1]); }
+
+template <int DT, int ODT, int T, int TL, bool FX = false, bool KVQ = false, bool FORCED = false, int HB = kHB>
+__global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
     // (the first 14 dwords arrive in scalar registers with the wavefront: what the first loads need comes first;
     // dims0 = Hkv | Hq << 16, dims1 = R | nhb << 8 | nchunk << 16 | stream << 24)
     const uint16_t* __restrict__ q, const float* __restrict__ codebook, const uint8_t* __restrict__ codes,
     uint32_t dims0, uint32_t dims1, int Lmax, int32_t* __restrict__ seq_len, const uint16_t* K, const uint16_t* V,
     const StepArgs a) {
     constexpr int TT = T + TL;  // tokens per thread: T with their scores in registers, TL with their scores in LDS
-    constexpr int kChunk = kStepThreads * TT;
-    static_assert(TT <= 32, "one mask bit per token of a thread");
-    static_assert(!FX || TL == 0, "the 16-bit sums of the first pass all stay in registers");
+    constexpr int NT = step_threads(HB), NW = NT / kWave;
+    constexpr int kChunk = NT * TT;
+    constexpr int MW = (TT + 31) / 32;  // mask words of a thread and head, one bit per token
+    static_assert(!FX || (TL == 0 && HB == kHB && MW == 1), "the 16-bit sums of the first pass all stay in registers");
+    using Entry = typename TableEntry<HB>::type;  // the scores, or table entries, of a workgroup's heads
     const int Hkv = dims0 & 0xffffu, Hq = dims0 >> 16;
     const int R = dims1 & 0xffu, nhb = (dims1 >> 8) & 0xffu, nchunk = (dims1 >> 16) & 0xffu;
     const bool stream = (dims1 >> 24) & 1u;
     extern __shared__ __align__(16) unsigned char dyn[];  // selected-token lists, then the arrays of the last phase
-    __shared__ __align__(16) float lut[kG * 16 * kHB];
-    __shared__ float qs[kHB][kD];
-    __shared__ float bp[kHB][2];
+    __shared__ __align__(16) float lut[kG * 16 * HB];
+    __shared__ float qs[HB][kD];
+    __shared__ float bp[HB][2];
     // first pass in 16-bit fixed point (FX): entries at the float4 table's stride, bin base and band per head
     __shared__ __align__(16) uint16_t lutx[FX ? kG * 16 * 8 : 8];
-    __shared__ int bpx[kHB][3], sband[kHB][2];
-    __shared__ uint32_t lhist[kHB * kBins];  // this chunk's histograms, later the heads' totals
+    __shared__ int bpx[HB][3], sband[HB][2];
+    __shared__ uint32_t lhist[HB * kBins];  // this chunk's histograms, later the heads' totals
     __shared__ __align__(16) uint8_t newcode[kCodeBytes];
-    __shared__ uint32_t wcnt[kHB][kStepWaves];
-    __shared__ uint32_t s_nsel[kHB], s_ncand[kHB], lds4[kHB][4];
-    __shared__ int sthr[kHB][3], s_last[kHB], s_flag;
-    __shared__ float sm[kStepWaves], sl[kStepWaves];
-    __shared__ float sacc[kStepWaves][kD];
-    __shared__ float pml[kHB][2][kMaxChunks];
-    __shared__ uint32_t fbits[FORCED ? 20 * kStepThreads / 32 : 1];  // forced tokens of this chunk, one bit per token
+    __shared__ uint32_t wcnt[HB][NW];
+    __shared__ uint32_t s_nsel[HB], s_ncand[HB], lds4[HB][4];
+    __shared__ int sthr[HB][3], s_last[HB], s_flag;
+    __shared__ float sm[NW], sl[NW];
+    __shared__ float sacc[NW][kD];
+    __shared__ float pml[HB][2][kMaxChunks];
+    __shared__ uint32_t fbits[FORCED ? kChunk / 32 : 1];  // forced tokens of this chunk, one bit per token
     __shared__ int32_t s_fidx[FORCED ? kMaxForced : 1];              // forced tokens of the KV head, -1: names no token
     __shared__ uint32_t s_fcnt;
 
     SIK_TL(36);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, p = lane & 15;
+    const int wv_u = __builtin_amdgcn_readfirstlane(wv);
     const int g = tid >> 8, gt = tid & (kGroupThreads - 1), wl = wv & 3;  // group = head slot of the last phases
     const int c = blockIdx.x % nchunk;
     const int u = blockIdx.x / nchunk;
-    const int hb = u % nhb;
-    const int unit = u / nhb;
+    // Two heads to a workgroup: the first half of the grid, which is dispatched first, takes the first head blocks of all
+    // KV heads, so that every compute unit gets one early and one late workgroup.
+    const int nunits = gridDim.x / (nchunk * nhb);
+    const int hb = HB == kHB ? u % nhb : u / nunits;
+    const int unit = HB == kHB ? u / nhb : u % nunits;
     const int h = unit % Hkv, b = unit / Hkv;
     const int start = c * kChunk;
-    const int hq0 = h * R + hb * kHB;
-    const int nh = min(kHB, R - hb * kHB);
+    const int hq0 = h * R + hb * HB;
+    const int nh = min(HB, R - hb * HB);
     const size_t row0 = static_cast<size_t>(b) * Hq + hq0;
     uint32_t* const status = a.sync;
     uint32_t* const rsync = a.sync + kSyncHeader + row0 * kSyncPerRow;  // this block's first head
-    uint32_t* const ssync = a.sync + kSyncHeader + static_cast<size_t>(gridDim.x / (nchunk * nhb * Hkv)) * Hq * kSyncPerRow +
+    uint32_t* const ssync = a.sync + kSyncHeader + static_cast<size_t>(nunits / Hkv) * Hq * kSyncPerRow +
                             static_cast<size_t>(b) * kSyncPerSeq;
 
     // ---- 0. every global load that does not depend on another goes out now -----------------------------------
@@ -152,12 +176,12 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
     uint4 cur[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        const int i = start + j * kStepThreads + tid;
+        const int i = start + j * NT + tid;
         cur[j] = (j < TT && i < cap_end) ? cp[i] : make_uint4(0u, 0u, 0u, 0u);
     }
     const float4 cj = tid < kG * 16 ? reinterpret_cast<const float4*>(codebook)[static_cast<size_t>(unit) * kG * 16 + tid]
                                     : make_float4(0.f, 0.f, 0.f, 0.f);
-    if (tid < kHB * 16) {  // 16 lanes x 16 B per query row
+    if (tid < HB * 16) {  // 16 lanes x 16 B per query row
         const int s = tid >> 4;
         float f[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         if (s < nh) widen8<DT>(reinterpret_cast<const uint4*>(q + (row0 + s) * kD)[p], f);
@@ -165,15 +189,9 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
         for (int e = 0; e < 8; ++e) qs[s][8 * p + e] = f[e];
     }
     // gather role of this wavefront: head gs, slice gj of its list (see step 3)
-    const int nslice = kStepWaves / nh;
+    const int nslice = NW / nh;
     const int gs = wv % nh, gj = wv / nh;
-    const uint4 qraw = reinterpret_cast<const uint4*>(q + (row0 + gs) * kD)[p];
-    float4 al0 = make_float4(0.f, 0.f, 0.f, 0.f), al1 = al0;  // KVQ: alpha of this lane's 8 channels
-    if constexpr (KVQ) {
-        al0 = reinterpret_cast<const float4*>(a.alpha + static_cast<size_t>(unit) * kD)[2 * p];
-        al1 = reinterpret_cast<const float4*>(a.alpha + static_cast<size_t>(unit) * kD)[2 * p + 1];
-    }
-    for (int e = tid; e < kHB * kBins; e += kStepThreads) lhist[e] = 0u;
+    for (int e = tid; e < HB * kBins; e += NT) lhist[e] = 0u;
     uint4 knew = make_uint4(0u, 0u, 0u, 0u), vnew = make_uint4(0u, 0u, 0u, 0u);
     float m8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (a.k_new && tid < 16) {
@@ -222,7 +240,9 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
         for (int e = 0; e < 8; ++e) byte |= (f[e] >= m8[e] ? 1u : 0u) << (7 - e);
         newcode[tid] = static_cast<uint8_t>(byte);
         const size_t rowi = static_cast<size_t>(unit) * Lmax + t_new;
-        if constexpr (KVQ) {  // the row is stored as one record (tid = p here: alpha of the same 8 channels)
+        if constexpr (KVQ) {  // the row is stored as one record
+            const float4 al0 = reinterpret_cast<const float4*>(a.alpha + static_cast<size_t>(unit) * kD)[2 * tid];
+            const float4 al1 = reinterpret_cast<const float4*>(a.alpha + static_cast<size_t>(unit) * kD)[2 * tid + 1];
             const float ra[8] = {alpha_reciprocal(al0.x), alpha_reciprocal(al0.y), alpha_reciprocal(al0.z),
                                  alpha_reciprocal(al0.w), alpha_reciprocal(al1.x), alpha_reciprocal(al1.y),
                                  alpha_reciprocal(al1.z), alpha_reciprocal(al1.w)};
@@ -240,7 +260,7 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
     // the budget and the competing population shrink by their number, and chunk 0 attends them.
     int nfv = 0, fpos = 0;
     if (n_forced > 0) {  // uniform
-        for (int e = tid; e < kChunk / 32; e += kStepThreads) fbits[e] = 0u;
+        for (int e = tid; e < kChunk / 32; e += NT) fbits[e] = 0u;
         const bool fv = fi >= 0 && fi < L;
         fi = fv ? fi : -1;
         if (tid < kMaxForced) s_fidx[FORCED ? tid : 0] = fi;
@@ -257,9 +277,9 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
     // ---- 1. Table^(g)[j] for the block's heads, bin bounds, scan ------------------------------------------------
     if (tid < kG * 16) {
         const int gg = tid >> 4;
-        float o[kHB];
+        float o[HB];
 #pragma unroll
-        for (int s = 0; s < kHB; ++s) {
+        for (int s = 0; s < HB; ++s) {
             const float* qq = &qs[s][4 * gg];
             float x = qq[0] * cj.x;
             x = fmaf(qq[1], cj.y, x);
@@ -267,16 +287,16 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
             x = fmaf(qq[3], cj.w, x);
             o[s] = x;
         }
-        *reinterpret_cast<float4*>(&lut[tid * 4]) = make_float4(o[0], o[1], o[2], o[3]);
+        *reinterpret_cast<Entry*>(&lut[tid * HB]) = make_entry(o);
     }
     __syncthreads();
-    if (tid < kHB * 32) {  // bins over mean +- 4.5 sigma of the score of a key with uniform independent codes
+    if (tid < HB * 32) {  // bins over mean +- 4.5 sigma of the score of a key with uniform independent codes
         const int s = tid >> 5, gg = tid & 31;
-        const float* lf = &lut[gg * 16 * kHB + s];
+        const float* lf = &lut[gg * 16 * HB + s];
         float sum = 0.0f, sq = 0.0f;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const float x = lf[((j + gg) & 15) * kHB];
+            const float x = lf[((j + gg) & 15) * HB];
             sum += x;
             sq = fmaf(x, x, sq);
         }
@@ -301,7 +321,7 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
             float mn = 3.4028235e38f, mx = -3.4028235e38f, ma = 0.0f;
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
-                const float x = lf[((j + gg) & 15) * kHB];
+                const float x = lf[((j + gg) & 15) * HB];
                 mn = fminf(mn, x);
                 mx = fmaxf(mx, x);
                 ma = fmaxf(ma, fabsf(x));
@@ -317,7 +337,7 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
                 const int jj = (j + gg) & 15;
-                const float e = rintf((lf[jj * kHB] - mn) * inv);
+                const float e = rintf((lf[jj * HB] - mn) * inv);
                 lutx[(gg * 16 + jj) * 8 + s] = static_cast<uint16_t>(static_cast<int>(e));
                 sumE += e;
                 sqE = fmaf(e, e, sqE);
@@ -345,10 +365,10 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
         }
     }
     __syncthreads();
-    float blo[kHB], bscale[kHB], bshift[kHB];
-    int base6[kHB], shx[kHB];  // FX: bin = (F >> shx) - base6
+    float blo[HB], bscale[HB], bshift[HB];
+    int base6[HB], shx[HB];  // FX: bin = (F >> shx) - base6
 #pragma unroll
-    for (int s = 0; s < kHB; ++s) {
+    for (int s = 0; s < HB; ++s) {
         blo[s] = bp[s][0];
         bscale[s] = bp[s][1];
         bshift[s] = bin_shift(bp[s][0], bp[s][1]);
@@ -357,27 +377,92 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
     }
     SIK_TL(38);
     // The scores of this thread's tokens stay on the chip: the first T tokens' in registers, the other TL tokens'
-    // in LDS (one float4 = four heads per token; large batches need more tokens per thread than the registers hold).
+    // in LDS (one entry = all heads of a token; large batches need more tokens per thread than the registers hold).
     // dyn: [lists][candidate stage][LDS scores]; the arrays of the last phase reuse it from the start.
     uint16_t* const lists = reinterpret_cast<uint16_t*>(dyn);
-    const size_t lists_bytes = (static_cast<size_t>(kHB) * a.listcap * 2 + 15) & ~size_t(15);
+    const size_t lists_bytes = (static_cast<size_t>(HB) * a.listcap * 2 + 15) & ~size_t(15);
     uint64_t* const cstage = reinterpret_cast<uint64_t*>(dyn + lists_bytes);
-    float4* const lsc = reinterpret_cast<float4*>(dyn + lists_bytes + static_cast<size_t>(kHB) * kCandCap * 8);
-    float sc[T][kHB];
+    Entry* const lsc = reinterpret_cast<Entry*>(dyn + lists_bytes + static_cast<size_t>(HB) * kCandCap * 8);
+    // (HB = 4: sc[token slot][head], every index a constant; HB = 2: a register bank per head, indexed by the loop counter:
+    // 32 to 40 tokens one after the other in the code would be more than half of what the instruction cache holds)
+    typedef float Bank __attribute__((ext_vector_type(T <= 16 ? 16 : 32)));
+    constexpr bool kRolled = HB == kHBPair;
+    static_assert(!kRolled || (T <= 32 && T % 2 == 0 && TL % 2 == 0), "register banks, token slots taken in twos");
+    float sc[kRolled ? 1 : T][HB];
+    Bank bank[kRolled ? HB : 1];
     uint32_t fx[FX ? TT : 1][2];  // FX: the 16-bit sums of a token, heads 0 | 1 << 16 and 2 | 3 << 16
     uint32_t livemask = 0u;       // FX: token slots that hold a competing token
+    if constexpr (kRolled) {
+        const int last = max(end - 1, 0);  // (slots past the end load the last token's code again; they count for nothing)
+        auto scan_token = [&](int it, uint4& next, float (&acc)[HB]) __attribute__((always_inline)) {
+            const int tok = start + it * NT + tid;
+            uint4 code = next;
+            next = cp[min(tok + 2 * NT, last)];
+            if (tok == t_new) code = *reinterpret_cast<const uint4*>(newcode);
+            if constexpr (T <= 16) {  // the lookups run one 8-group batch ahead of the adds
+                Entry v[2][8];
+                lookup_batch<HB>(code.x, 0, lut, v[0]);
+#pragma unroll
+                for (int dw = 0; dw < 4; ++dw) {
+                    if (dw < 3)
+                        lookup_batch<HB>(dw == 0 ? code.y : (dw == 1 ? code.z : code.w), dw + 1, lut, v[(dw + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    add_batch<HB>(dw == 0, v[dw & 1], acc);
+#pragma unroll
+                    for (int s = 0; s < HB; ++s) asm volatile("" : "+v"(acc[s]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {  // a batch at a time: the wavefronts of two workgroups hide the latency between them
+                Entry v[8];
+#pragma unroll
+                for (int dw = 0; dw < 4; ++dw) {
+                    lookup_batch<HB>(dw == 0 ? code.x : (dw == 1 ? code.y : (dw == 2 ? code.z : code.w)), dw, lut, v);
+                    __builtin_amdgcn_sched_barrier(0);
+                    add_batch<HB>(dw == 0, v, acc);
+#pragma unroll
+                    for (int s = 0; s < HB; ++s) asm volatile("" : "+v"(acc[s]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            // slots at or beyond the sequence's end and forced tokens hold NaN: every comparison of the classification fails
+            const bool live = tok < end && !(n_forced > 0 &&
+                                             ((fbits[FORCED ? it * (NT / 32) + (tid >> 5) : 0] >> (tid & 31)) & 1u));
+#pragma unroll
+            for (int s = 0; s < HB; ++s) {
+                if (live && s < nh)
+                    atomicAdd(&lhist[s * kBins + bin_of_coord(bin_coord_shifted(acc[s], bscale[s], bshift[s]))], 1u);
+                acc[s] = live ? acc[s] : __builtin_nanf("");
+            }
+        };
+#pragma unroll 1
+        for (int it = 0; it < T; it += 2) {
+            float x0[HB], x1[HB];
+            scan_token(it, cur[0], x0);
+            scan_token(it + 1, cur[1], x1);
+#pragma unroll
+            for (int s = 0; s < HB; ++s) bank[s][it] = x0[s], bank[s][it + 1] = x1[s];
+        }
+#pragma unroll 1
+        for (int it = T; it < TT; it += 2) {
+            float x0[HB], x1[HB];
+            scan_token(it, cur[0], x0);
+            lsc[(it - T) * NT + tid] = make_entry(x0);
+            scan_token(it + 1, cur[1], x1);
+            lsc[(it + 1 - T) * NT + tid] = make_entry(x1);
+        }
+    } else {
 #pragma unroll
     for (int it = 0; it < TT; ++it) {
-        const int tok = start + it * kStepThreads + tid;
+        const int tok = start + it * NT + tid;
         uint4 code = cur[it & 1];
         if (it + 2 < TT) {
-            const int i = tok + 2 * kStepThreads;
+            const int i = tok + 2 * NT;
             cur[it & 1] = i < end ? cp[i] : make_uint4(0u, 0u, 0u, 0u);
         }
         if (tok == t_new) code = *reinterpret_cast<const uint4*>(newcode);
-        // (token slot it of thread tid is token it * 1024 + tid of the chunk)
+        // (token slot it of thread tid is token it * NT + tid of the chunk)
         const bool live =
-            tok < end && !(n_forced > 0 && ((fbits[FORCED ? it * 32 + (tid >> 5) : 0] >> (tid & 31)) & 1u));
+            tok < end && !(n_forced > 0 && ((fbits[FORCED ? it * (NT / 32) + (tid >> 5) : 0] >> (tid & 31)) & 1u));
         if constexpr (FX) {
             // 8-byte entries, two packed 16-bit adds per lookup: half the adds and half the LDS bytes of the
             // fp32 scan; the sums only place the token in a bin (exact scores follow for the band, below)
@@ -402,7 +487,7 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
             livemask |= (live ? 1u : 0u) << it;
             if (live) {
 #pragma unroll
-                for (int s = 0; s < kHB; ++s) {
+                for (int s = 0; s < HB; ++s) {
                     const uint32_t w = s < 2 ? w01 : w23;
                     const int f6 = static_cast<int>(((s & 1) ? w >> 16 : w & 0xffffu) >> shx[s]);
                     if (s < nh) atomicAdd(&lhist[s * kBins + min(max(f6 - base6[s], 0), kBins - 1)], 1u);
@@ -410,25 +495,25 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
             }
             continue;
         }
-        float acc[kHB];
+        float acc[HB];
         if constexpr (TT < 6) {
             // the lookups run one 8-group batch ahead of the adds (8 to 16 LDS reads in flight per wavefront)
-            float4 v[2][8];
-            lookup_batch<kHB>(code.x, 0, lut, v[0]);
+            Entry v[2][8];
+            lookup_batch<HB>(code.x, 0, lut, v[0]);
 #pragma unroll
             for (int dw = 0; dw < 4; ++dw) {
                 if (dw < 3)
-                    lookup_batch<kHB>(dw == 0 ? code.y : (dw == 1 ? code.z : code.w), dw + 1, lut, v[(dw + 1) & 1]);
+                    lookup_batch<HB>(dw == 0 ? code.y : (dw == 1 ? code.z : code.w), dw + 1, lut, v[(dw + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
-                add_batch<kHB>(dw == 0, v[dw & 1], acc);
+                add_batch<HB>(dw == 0, v[dw & 1], acc);
 #pragma unroll
-                for (int s = 0; s < kHB; ++s) asm volatile("" : "+v"(acc[s]));
+                for (int s = 0; s < HB; ++s) asm volatile("" : "+v"(acc[s]));
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else {
             // many tokens per thread: their scores take half the registers, so half a batch at a time (the 16
             // wavefronts of the workgroup hide the LDS latency between them)
-            float4 v[4];
+            Entry v[4];
 #pragma unroll
             for (int dw = 0; dw < 4; ++dw) {
                 const uint32_t word = dw == 0 ? code.x : (dw == 1 ? code.y : (dw == 2 ? code.z : code.w));
@@ -436,26 +521,25 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
                 __builtin_amdgcn_sched_barrier(0);
                 add_half(dw == 0, v, acc);
 #pragma unroll
-                for (int s = 0; s < kHB; ++s) asm volatile("" : "+v"(acc[s]));
+                for (int s = 0; s < HB; ++s) asm volatile("" : "+v"(acc[s]));
                 __builtin_amdgcn_sched_barrier(0);
                 lookup_half<1>(word, dw, lut, v);
                 __builtin_amdgcn_sched_barrier(0);
                 add_half(false, v, acc);
 #pragma unroll
-                for (int s = 0; s < kHB; ++s) asm volatile("" : "+v"(acc[s]));
+                for (int s = 0; s < HB; ++s) asm volatile("" : "+v"(acc[s]));
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
 #pragma unroll
-        for (int s = 0; s < kHB; ++s) {
+        for (int s = 0; s < HB; ++s) {
             if (live && s < nh)
                 atomicAdd(&lhist[s * kBins + bin_of_coord(bin_coord_shifted(acc[s], bscale[s], bshift[s]))], 1u);
-            // slots at or beyond the sequence's end and forced tokens hold NaN: every comparison of the
-            // classification fails
             acc[s] = live ? acc[s] : __builtin_nanf("");
             if (it < T) sc[it < T ? it : 0][s] = acc[s];
         }
-        if (it >= T) lsc[(it - T) * kStepThreads + tid] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        if (it >= T) lsc[(it - T) * NT + tid] = make_entry(acc);
+    }
     }
     __syncthreads();
 
@@ -476,7 +560,7 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
         __syncthreads();
         if (tid == 0) atomic_add_u32(&rsync[3], 1u);
         SIK_TL(40);
-        for (int e = tid; e < kHB * kBins; e += kStepThreads) lhist[e] = 0u;
+        for (int e = tid; e < HB * kBins; e += NT) lhist[e] = 0u;
         alive = bounded_wait(&rsync[3], static_cast<uint32_t>(nact), a.spin_limit, status, 1u, &s_flag);
         if (!alive) {  // uniform: the launch is lost, the status word says so
             leave();
@@ -541,36 +625,47 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
             sthr[g][1] = kk > 0 ? Lc : 0;
             sthr[g][2] = 0;
         }
-        if (tid < kHB) s_nsel[tid] = 0u, s_ncand[tid] = 0u;
+        if (tid < HB) s_nsel[tid] = 0u, s_ncand[tid] = 0u;
     }
     __syncthreads();
 
     SIK_TL(42);
     // ---- 3. classify from the registers, compact per head, gather ---------------------------------------------------
-    float hi_f[kHB], lo_f[kHB];
-    bool has_cand[kHB], crowded[kHB];
+    float hi_f[HB], lo_f[HB];
+    bool has_cand[HB], crowded[HB];
+    int bst[HB], cgts[HB], nbs[HB];
 #pragma unroll
-    for (int s = 0; s < kHB; ++s) {
-        const int bstar = sthr[s][0];
+    for (int s = 0; s < HB; ++s) {  // (the same in every lane: kept in scalar registers)
+        bst[s] = __builtin_amdgcn_readfirstlane(sthr[s][0]);
+        cgts[s] = __builtin_amdgcn_readfirstlane(sthr[s][1]);
+        nbs[s] = __builtin_amdgcn_readfirstlane(sthr[s][2]);
         // bin(s) > b*  <=>  x >= b* + 1 and bin(s) == b*  <=>  b* <= x < b* + 1 with x = bin_coord(s), the clamped
         // end bins taking everything beyond them
-        hi_f[s] = bstar < 0 ? -3.4028235e38f : (bstar >= kBins - 1 ? INFINITY : static_cast<float>(bstar + 1));
-        lo_f[s] = bstar <= 0 ? -3.4028235e38f : (bstar >= kBins ? INFINITY : static_cast<float>(bstar));
-        has_cand[s] = s < nh && bstar >= 0 && bstar < kBins && sthr[s][2] <= kCandCap;
-        crowded[s] = s < nh && bstar >= 0 && bstar < kBins && sthr[s][2] > kCandCap;
+        hi_f[s] = bst[s] < 0 ? -3.4028235e38f : (bst[s] >= kBins - 1 ? INFINITY : static_cast<float>(bst[s] + 1));
+        lo_f[s] = bst[s] <= 0 ? -3.4028235e38f : (bst[s] >= kBins ? INFINITY : static_cast<float>(bst[s]));
+        hi_f[s] = uniform(hi_f[s]);
+        lo_f[s] = uniform(lo_f[s]);
+        has_cand[s] = s < nh && bst[s] >= 0 && bst[s] < kBins && nbs[s] <= kCandCap;
+        crowded[s] = s < nh && bst[s] >= 0 && bst[s] < kBins && nbs[s] > kCandCap;
     }
+    bool any_crowded = false;  // uniform
+#pragma unroll
+    for (int s = 0; s < HB; ++s) any_crowded |= crowded[s];
     // Stage A: one branch-free pass over the thread's tokens marks, per head, the selected ones and the ones at or
-    // above the candidate bound in two bit masks (bit = token slot): a few instructions per score (a branch per
-    // score for the rare candidates measured 3 us slower on 16 tokens per thread).  A threshold bin too crowded to
-    // rank (e.g. all scores equal) sends the head's scores to memory for the radix selection of the last phase.
-    uint32_t smask[kHB] = {0u, 0u, 0u, 0u}, gmask[kHB] = {0u, 0u, 0u, 0u};
+    // above the candidate bound in two bit masks (a branch per score for the rare candidates measured 3 us slower on 16
+    // tokens per thread).  Bound by vector-instruction issue, 64 scores per thread at 16K tokens: a mask grows by a
+    // compare and an add with carry, mask = 2 mask + (x >= bound), so that a word's last token slot ends up
+    // in bit 0 (mask_slot).  With places from bit counts and DPP sums instead of a ballot per round, counted and then
+    // written, one barrier less before the lists and the ranking beside their writing, threshold to lists takes 8.8 us
+    // instead of 13 at 16K tokens and four heads; 32 x 8 x 16K records: 64.3 -> 60.7 us for the whole step.
+    uint32_t smask[HB][MW] = {}, gmask[HB][MW] = {};
     if constexpr (FX) {
         // the same two masks from the 16-bit sums: selected = a bin above the band, candidate = a bin of the band
         // (compared as F >> sh against the bins' lower edges; the clamped end bins take everything beyond them)
-        int thr_s[kHB], thr_c[kHB];
+        int thr_s[HB], thr_c[HB];
 #pragma unroll
-        for (int s = 0; s < kHB; ++s) {
-            const int bstar = sthr[s][0];
+        for (int s = 0; s < HB; ++s) {
+            const int bstar = bst[s];
             const bool in = bstar >= 0 && bstar < kBins;
             thr_s[s] = bstar < 0 ? INT_MIN : ((!in || sband[s][1] >= kBins - 1) ? INT_MAX : sband[s][1] + 1 + base6[s]);
             thr_c[s] = !in ? INT_MAX : (sband[s][0] <= 0 ? INT_MIN : sband[s][0] + base6[s]);
@@ -578,30 +673,30 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
 #pragma unroll
         for (int it = 0; it < TT; ++it) {
 #pragma unroll
-            for (int s = 0; s < kHB; ++s) {
+            for (int s = 0; s < HB; ++s) {
                 const uint32_t w = fx[it][s >> 1];
                 const int f6 = static_cast<int>(((s & 1) ? w >> 16 : w & 0xffffu) >> shx[s]);
-                smask[s] |= (f6 >= thr_s[s] ? 1u : 0u) << it;
-                gmask[s] |= (f6 >= thr_c[s] ? 1u : 0u) << it;
+                smask[s][0] |= (f6 >= thr_s[s] ? 1u : 0u) << (TT - 1 - it);
+                gmask[s][0] |= (f6 >= thr_c[s] ? 1u : 0u) << (TT - 1 - it);
             }
         }
         // token slots at or beyond the sequence's end, and forced tokens, are in no mask
 #pragma unroll
-        for (int s = 0; s < kHB; ++s) {
-            smask[s] &= livemask;
-            gmask[s] &= livemask;
+        for (int s = 0; s < HB; ++s) {
+            smask[s][0] &= __brev(livemask) >> (32 - TT);
+            gmask[s][0] &= __brev(livemask) >> (32 - TT);
         }
         // a band too crowded to rank: the exact scores of its members go to memory for the radix selection of the
         // last phase, minus infinity for everything else
-        if (crowded[0] || crowded[1] || crowded[2] || crowded[3]) {  // uniform
+        if (any_crowded) {
             for (int it = 0; it < TT; ++it) {
-                const int tok = start + it * kStepThreads + tid;
+                const int tok = start + it * NT + tid;
                 if (tok < end) {
                     const uint4 code = tok == t_new ? *reinterpret_cast<const uint4*>(newcode) : cp[tok];
 #pragma unroll
-                    for (int s = 0; s < kHB; ++s) {
+                    for (int s = 0; s < HB; ++s) {
                         if (crowded[s]) {
-                            const bool member = ((gmask[s] & ~smask[s]) >> it) & 1u;
+                            const bool member = ((gmask[s][0] & ~smask[s][0]) >> (TT - 1 - it)) & 1u;
                             st_agent(&a.scores[(row0 + s) * a.sstride + tok], member ? exact_score(lut, code, s) : -INFINITY);
                         }
                     }
@@ -609,66 +704,121 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
             }
         }
     } else {
+        // every token slot with its scores, f(slot, mask word, scores); a slot's mask word is a constant
+        auto each_slot = [&](auto f) __attribute__((always_inline)) {
+            if constexpr (kRolled) {
+                auto range = [&](int from, int to, auto word, auto of) __attribute__((always_inline)) {
+#pragma unroll 4
+                    for (int it = from; it < to; ++it) {
+                        float v[HB];
+                        of(it, v);
+                        f(it, word, v);
+                    }
+                };
+                auto from_lds = [&](int it, float (&v)[HB]) __attribute__((always_inline)) {
+                    const Entry x = lsc[(it - T) * NT + tid];
+                    v[0] = x.x, v[1] = x.y;
+                };
+                range(0, T, std::integral_constant<int, 0>{}, [&](int it, float (&v)[HB]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int it = 0; it < TT; ++it) {
-        float v4[kHB];
-        if (it < T) {
+                    for (int s = 0; s < HB; ++s) v[s] = bank[s][it];
+                });
+                range(T, TT < 32 ? TT : 32, std::integral_constant<int, 0>{}, from_lds);
+                if constexpr (TT > 32) range(32, TT, std::integral_constant<int, 1>{}, from_lds);
+            } else {
 #pragma unroll
-            for (int s = 0; s < kHB; ++s) v4[s] = sc[it < T ? it : 0][s];
-        } else {
-            const float4 f = lsc[(it - T) * kStepThreads + tid];
-            v4[0] = f.x, v4[1] = f.y, v4[2] = f.z, v4[3] = f.w;
+                for (int it = 0; it < TT; ++it) {
+                    if (it < T) {
+                        f(it, std::integral_constant<int, 0>{}, sc[it < T ? it : 0]);
+                    } else {
+                        const Entry x = lsc[(it - T) * NT + tid];
+                        const float v[HB] = {x.x, x.y, x.z, x.w};
+                        f(it, std::integral_constant<int, 0>{}, v);
+                    }
+                }
+            }
+        };
+        each_slot([&](auto, auto word, const float (&v)[HB]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = 0; s < HB; ++s) {
+                const float x = bin_coord(v[s], blo[s], bscale[s]);
+                push_ge(smask[s][decltype(word)::value], x, hi_f[s]);
+                push_ge(gmask[s][decltype(word)::value], x, lo_f[s]);
+            }
+        });
+        // a threshold bin too crowded to rank (e.g. all scores equal) sends the head's scores to memory for the radix
+        // selection of the last phase (a forced token's NaN goes out as minus infinity: it does not compete)
+        if (any_crowded) {
+            each_slot([&](auto slot, auto, const float (&v)[HB]) __attribute__((always_inline)) {
+                const int tok = start + slot * NT + tid;
+#pragma unroll
+                for (int s = 0; s < HB; ++s)
+                    if (crowded[s] && tok < end)
+                        st_agent(&a.scores[(row0 + s) * a.sstride + tok], v[s] == v[s] ? v[s] : -INFINITY);
+            });
         }
-        const int tok = start + it * kStepThreads + tid;
-#pragma unroll
-        for (int s = 0; s < kHB; ++s) {
-            const float x = bin_coord(v4[s], blo[s], bscale[s]);
-            smask[s] |= (x >= hi_f[s] ? 1u : 0u) << it;
-            gmask[s] |= (x >= lo_f[s] ? 1u : 0u) << it;
-            if (crowded[s] && tok < end)  // (a forced token's NaN goes out as minus infinity: it does not compete)
-                st_agent(&a.scores[(row0 + s) * a.sstride + tok], v4[s] == v4[s] ? v4[s] : -INFINITY);
-        }
-    }
     }
     SIK_TL(8);
-    // Stage B: selected tokens per wavefront, in rounds of "every lane pops one mask bit" (as many rounds as the
-    // busiest lane has selected tokens): ballots and scalar counts only
-    const uint64_t lt_mask = (1ull << lane) - 1ull;
+    // Stage B: every lane's place in its wavefront's share of each list, from the lanes' bit counts (two heads to a
+    // word, one DPP scan each), and the candidates into the stage.
+    uint32_t place[HB / 2];  // marked tokens of the lanes below: heads 2x | 2x + 1 << 16
 #pragma unroll
-    for (int s = 0; s < kHB; ++s) {
-        if (s >= nh) smask[s] = 0u;
-        uint32_t m = smask[s], tot = 0u;
-        while (true) {
-            const uint64_t bal = __ballot(m != 0u);
-            if (bal == 0ull) break;
-            tot += static_cast<uint32_t>(__popcll(bal));
-            m &= m - 1u;
+    for (int x = 0; x < HB / 2; ++x) {
+        uint32_t own = 0u;
+#pragma unroll
+        for (int w = 0; w < MW; ++w) {
+            if (2 * x >= nh) smask[2 * x][w] = 0u;
+            if (2 * x + 1 >= nh) smask[2 * x + 1][w] = 0u;
+            own += static_cast<uint32_t>(__popc(smask[2 * x][w])) |
+                   static_cast<uint32_t>(__popc(smask[2 * x + 1][w])) << 16;
         }
-        if (lane == 0) wcnt[s][wv] = tot;
+        const uint32_t incl = wave_inclusive_sum(own);
+        place[x] = incl - own;
+        if (lane == kWave - 1) {
+            wcnt[2 * x][wv] = incl & 0xffffu;
+            wcnt[2 * x + 1][wv] = incl >> 16;
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < HB; ++s) {
         // candidates (about one token in a thousand): popped from the mask one by one (a wavefront-uniform loop
         // over the holders with scalar branches to the score's register was measured slower: the scalar unit is
         // shared by the 16 wavefronts)
-        uint32_t cm = has_cand[s] ? (gmask[s] & ~smask[s]) : 0u;
-        while (cm != 0u) {
-            const int it = __ffs(static_cast<int>(cm)) - 1;
-            cm &= cm - 1u;
-            const uint32_t tok = static_cast<uint32_t>(start + it * kStepThreads + tid);
-            if constexpr (FX) {  // only the token is staged: its exact score follows below
-                const uint32_t at = atomicAdd(&s_ncand[s], 1u);
-                if (at < static_cast<uint32_t>(kCandCap)) cstage[s * kCandCap + at] = tok;
-            } else {
-                float v = 0.0f;
-                if (it < T) {
 #pragma unroll
-                    for (int j = 0; j < T; ++j) v = it == j ? sc[j][s] : v;
-                } else {
-                    v = reinterpret_cast<const float*>(&lsc[(it - T) * kStepThreads + tid])[s];
-                }
-                const uint32_t at = atomicAdd(&s_ncand[s], 1u);
-                if (at < static_cast<uint32_t>(kCandCap))
-                    cstage[s * kCandCap + at] = static_cast<uint64_t>(float_to_key(v)) << 32 | (~tok);
+        for (int w = 0; w < MW; ++w) {
+            uint32_t cm = has_cand[s] ? (gmask[s][w] & ~smask[s][w]) : 0u;
+            if (cm != 0u) {
+                uint32_t at = atomicAdd(&s_ncand[s], static_cast<uint32_t>(__popc(cm)));
+                do {
+                    const int it = mask_slot<TT>(w, cm);
+                    cm &= cm - 1u;
+                    const uint32_t tok = static_cast<uint32_t>(start + it * NT + tid);
+                    if constexpr (FX) {  // only the token is staged: its exact score follows below
+                        if (at < static_cast<uint32_t>(kCandCap)) cstage[s * kCandCap + at] = tok;
+                    } else {
+                        float v = 0.0f;
+                        if (it < T) {
+#pragma unroll
+                            for (int j = 32 * w; j < (T < 32 * w + 32 ? T : 32 * w + 32); ++j)
+                                v = it == j ? (kRolled ? bank[kRolled ? s : 0][j] : sc[kRolled ? 0 : j][s]) : v;
+                        } else {
+                            v = reinterpret_cast<const float*>(&lsc[(it - T) * NT + tid])[s];
+                        }
+                        if (at < static_cast<uint32_t>(kCandCap))
+                            cstage[s * kCandCap + at] = static_cast<uint64_t>(float_to_key(v)) << 32 | (~tok);
+                    }
+                    ++at;
+                } while (cm != 0u);
             }
         }
+    }
+    // What the gather needs besides the lists is requested now, when the scores have left their registers (held through the
+    // scan it put 8 to 12 of them into scratch memory).
+    const uint4 qraw = reinterpret_cast<const uint4*>(q + (row0 + gs) * kD)[p];
+    float4 al0 = make_float4(0.f, 0.f, 0.f, 0.f), al1 = al0;  // KVQ: alpha of this lane's 8 channels
+    if constexpr (KVQ) {
+        al0 = reinterpret_cast<const float4*>(a.alpha + static_cast<size_t>(unit) * kD)[2 * p];
+        al1 = reinterpret_cast<const float4*>(a.alpha + static_cast<size_t>(unit) * kD)[2 * p + 1];
     }
     SIK_TL(9);
     __syncthreads();
@@ -684,33 +834,49 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
         rtok = static_cast<int>(cstage[g * kCandCap + gt]);
         rcode = rtok == t_new ? *reinterpret_cast<const uint4*>(newcode) : cp[rtok];
     }
-    if (tid < kHB * kStepWaves) {  // per head: offsets of the wavefronts (one 16-lane row per head)
-        const int s = tid >> 4, w = tid & 15;
-        const uint32_t cnt = wcnt[s][w];
-        uint32_t incl = cnt;
+    // Every wavefront adds up the counts of the wavefronts before it by itself (lane = head, wavefront; a scan within
+    // the 16 lanes of a head): no second barrier before the lists are written.
+    const uint32_t incl =
+        row16_inclusive_sum(lane < 16 * HB && (lane & 15) < NW ? wcnt[(lane >> 4) % HB][(lane & 15) % NW] : 0u);
+    // One active chunk: this workgroup owns its heads outright.  The threshold-bin candidates are ranked now (by
+    // counting, keys are distinct) and the winners join the lists, so that one gather covers the head and the last
+    // phase has nothing left to select.
+    const bool sole = nact == 1;  // uniform
+    const bool fast = sole && !any_crowded;
+    uint32_t at4[HB], nsel[HB];
 #pragma unroll
-        for (int o = 1; o < 16; o <<= 1) {
-            const uint32_t dn = static_cast<uint32_t>(__shfl_up(static_cast<int>(incl), o, 16));
-            if (w >= o) incl += dn;
-        }
-        wcnt[s][w] = incl - cnt;
-        if (w == 15) s_nsel[s] = incl;
+    for (int s = 0; s < HB; ++s) {
+        const uint32_t before = wv == 0 ? 0u : static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 16 * s + wv_u - 1));
+        at4[s] = before + ((s & 1) ? place[s >> 1] >> 16 : place[s >> 1] & 0xffffu);
+        nsel[s] = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 16 * s + 15));
     }
-    __syncthreads();
-    // Stage C: the same rounds again, now writing (order: wavefront, round, lane: deterministic)
+    if (tid < HB) {  // tokens to gather: the selected ones and, where they are ranked below, the winners
+        uint32_t n = nsel[0];
 #pragma unroll
-    for (int s = 0; s < kHB; ++s) {
-        uint32_t m = smask[s];
-        uint32_t base = wcnt[s][wv];
+        for (int s = 1; s < HB; ++s) n = tid == s ? nsel[s] : n;
+        if (sole && tid < nh && sthr[tid][0] >= 0 && sthr[tid][0] < kBins && sthr[tid][2] <= kCandCap)
+            n += static_cast<uint32_t>(min(kk - min(sthr[tid][1], kk),
+                                           static_cast<int>(min(s_ncand[tid], static_cast<uint32_t>(kCandCap)))));
+        s_nsel[tid] = n;
+    }
+    // Stage C: the lists (order: wavefront, lane, slot from the last to the first: deterministic), one mask bit per
+    // lane, head and round
+#pragma unroll
+    for (int w = 0; w < MW; ++w) {
         while (true) {
-            const bool has = m != 0u;
-            const uint64_t bal = __ballot(has);
-            if (bal == 0ull) break;
-            const uint32_t at = base + static_cast<uint32_t>(__popcll(bal & lt_mask));
-            if (has && at < static_cast<uint32_t>(a.listcap))
-                lists[s * a.listcap + at] = static_cast<uint16_t>((__ffs(static_cast<int>(m)) - 1) * kStepThreads + tid);
-            base += static_cast<uint32_t>(__popcll(bal));
-            m &= m - 1u;
+            uint32_t any = 0u;
+#pragma unroll
+            for (int s = 0; s < HB; ++s) any |= smask[s][w];
+            if (__ballot(any != 0u) == 0ull) break;
+#pragma unroll
+            for (int s = 0; s < HB; ++s) {
+                if (smask[s][w] != 0u) {
+                    if (at4[s] < static_cast<uint32_t>(a.listcap))
+                        lists[s * a.listcap + at4[s]] = static_cast<uint16_t>(mask_slot<TT>(w, smask[s][w]) * NT + tid);
+                    ++at4[s];
+                    smask[s][w] &= smask[s][w] - 1u;
+                }
+            }
         }
     }
     if constexpr (FX) {
@@ -722,43 +888,32 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
             cstage[g * kCandCap + j] = static_cast<uint64_t>(float_to_key(exact_score(lut, rcode, g))) << 32 |
                                        (~static_cast<uint32_t>(rtok));
         }
+        __syncthreads();  // the ranking reads what other threads have scored
     }
-    __syncthreads();
     SIK_TL(11);
-    // One active chunk: this workgroup owns its heads outright.  The threshold-bin candidates are ranked now (by
-    // counting, keys are distinct) and the winners join the lists, so that one gather covers the head and the last
-    // phase has nothing left to select.
-    const bool sole = nact == 1;  // uniform
-    const bool fast = sole && !(crowded[0] || crowded[1] || crowded[2] || crowded[3]);
-    if (sole) {
-        uint32_t add = 0u;
-        if (g < nh) {
-            const int bstar = sthr[g][0], need = kk - min(sthr[g][1], kk);
-            if (bstar >= 0 && bstar < kBins && need > 0 && sthr[g][2] <= kCandCap) {
-                const int ncand = static_cast<int>(min(s_ncand[g], static_cast<uint32_t>(kCandCap)));
-                const uint64_t* const cg = cstage + g * kCandCap;
-                const uint32_t nsel = s_nsel[g];
-                for (int x0 = gt; x0 < ncand; x0 += kGroupThreads) {
-                    const uint64_t me = cg[x0];
-                    uint32_t rank = 0u;
-                    for (int x = 0; x < ncand; x += 8) {  // (kCandCap is a multiple of 8: the reads stay inside cg)
-                        uint64_t o8[8];
+    if (sole && g < nh) {
+        const int bstar = sthr[g][0], need = kk - min(sthr[g][1], kk);
+        if (bstar >= 0 && bstar < kBins && need > 0 && sthr[g][2] <= kCandCap) {
+            const int ncand = static_cast<int>(min(s_ncand[g], static_cast<uint32_t>(kCandCap)));
+            const uint64_t* const cg = cstage + g * kCandCap;
+            const uint32_t sel = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 16 * (wv_u >> 2) + 15));
+            for (int x0 = gt; x0 < ncand; x0 += kGroupThreads) {
+                const uint64_t me = cg[x0];
+                uint32_t rank = 0u;
+                for (int x = 0; x < ncand; x += 8) {  // (kCandCap is a multiple of 8: the reads stay inside cg)
+                    uint64_t o8[8];
 #pragma unroll
-                        for (int y = 0; y < 8; ++y) o8[y] = cg[x + y];
+                    for (int y = 0; y < 8; ++y) o8[y] = cg[x + y];
 #pragma unroll
-                        for (int y = 0; y < 8; ++y) rank += (x + y < ncand && o8[y] > me) ? 1u : 0u;
-                    }
-                    if (rank < static_cast<uint32_t>(need) && nsel + rank < static_cast<uint32_t>(a.listcap))
-                        lists[g * a.listcap + nsel + rank] =
-                            static_cast<uint16_t>(static_cast<int>(~static_cast<uint32_t>(me)) - start);
+                    for (int y = 0; y < 8; ++y) rank += (x + y < ncand && o8[y] > me) ? 1u : 0u;
                 }
-                add = static_cast<uint32_t>(min(need, ncand));
+                if (rank < static_cast<uint32_t>(need) && sel + rank < static_cast<uint32_t>(a.listcap))
+                    lists[g * a.listcap + sel + rank] =
+                        static_cast<uint16_t>(static_cast<int>(~static_cast<uint32_t>(me)) - start);
             }
         }
-        __syncthreads();
-        if (g < nh && gt == 0) s_nsel[g] += add;
-        __syncthreads();
     }
+    __syncthreads();
     SIK_TL(43);
     // reservations in the head's index output and candidate area (several chunks only), issued before the gather
     // hides their round trip
@@ -897,7 +1052,7 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
     // barrier below is reached by all 1024 threads) ---------------------------------------------------------------
     // LDS of this phase (the lists are dead): per group kCandCap + 8 sort keys, kCandCap ranks, kCandCap winners
     uint64_t* const lc = reinterpret_cast<uint64_t*>(dyn) + g * (kCandCap + 8);
-    uint32_t* const rank_base = reinterpret_cast<uint32_t*>(reinterpret_cast<uint64_t*>(dyn) + kHB * (kCandCap + 8));
+    uint32_t* const rank_base = reinterpret_cast<uint32_t*>(reinterpret_cast<uint64_t*>(dyn) + HB * (kCandCap + 8));
     uint32_t* const rank_of = rank_base + g * 2 * kCandCap;
     int32_t* const chosen = reinterpret_cast<int32_t*>(rank_of + kCandCap);
     const bool do_rank = !sole && mine && need_g > 0 && ranked_g && bstar_g >= 0 && bstar_g < kBins;
@@ -982,11 +1137,11 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
             if constexpr (FX)
-                radix_select_members<kStepThreads, true>(a.scores + (row0 + s) * a.sstride, L,
+                radix_select_members<NT, true>(a.scores + (row0 + s) * a.sstride, L,
                                                          [](float v) { return v > -INFINITY; }, need_s, dst, lhist,
                                                          &lds4[0][0]);
             else
-                radix_select_members<kStepThreads, true>(
+                radix_select_members<NT, true>(
                     a.scores + (row0 + s) * a.sstride, L,
                     [lo = blo[s], sc_ = bscale[s], bst = sthr[s][0]](float v) {
                         return v > -INFINITY && score_bin(v, lo, sc_) == bst;
@@ -1086,7 +1241,13 @@ template <int DT, int ODT>
 static hipError_t launch_step_t(const Dims& d, int T, int nchunk, size_t dyn, const void* q, const float* codebook,
                                 const uint8_t* codes, int32_t* seq_len, const void* K, const void* V,
                                 const StepArgs& a, hipStream_t s) {
-    const int nhb = (d.R + kHB - 1) / kHB;
+    // SIK_STEP_PAIRS: the including file instantiates the variants with two heads to a workgroup
+#ifdef SIK_STEP_PAIRS
+    constexpr int HB = kHBPair;
+#else
+    constexpr int HB = kHB;
+#endif
+    const int nhb = (d.R + HB - 1) / HB;
     const int grid = d.units() * nhb * nchunk;
     const uint32_t dims0 = static_cast<uint32_t>(d.Hkv) | static_cast<uint32_t>(d.Hq) << 16;
     const uint32_t dims1 = static_cast<uint32_t>(d.R) | static_cast<uint32_t>(nhb) << 8 |
@@ -1094,28 +1255,39 @@ static hipError_t launch_step_t(const Dims& d, int T, int nchunk, size_t dyn, co
     auto qp = static_cast<const uint16_t*>(q);
     auto Kp = static_cast<const uint16_t*>(K);
     auto Vp = static_cast<const uint16_t*>(V);
+#ifdef SIK_STEP_PAIRS
+#define SIK_STEP2(TV, TLV) SIK_STEP_(kStepPairCode + TV * 100 + TLV, TV, TLV, false, false, false)
+#else
 #define SIK_STEP(TV, TLV) SIK_STEP_(TV * 100 + TLV, TV, TLV, false, false, false)
 #define SIK_STEP_Q2(TV, TLV) SIK_STEP_(kStepQ2Code + TV * 100 + TLV, TV, TLV, false, true, false)
 #define SIK_STEP_F(TV, TLV)                                                 \
     SIK_STEP_(kStepFCode + TV * 100 + TLV, TV, TLV, false, false, true)     \
     SIK_STEP_(kStepFCode + kStepQ2Code + TV * 100 + TLV, TV, TLV, false, true, true)
 #define SIK_STEP_FX(TV) SIK_STEP_(kStepFxCode + TV * 100, TV, 0, true, false, false)
+#endif
 #define SIK_STEP_(CODE, TV, TLV, FXV, Q2V, FV)                                                                  \
     case CODE: {                                                                                                \
-        auto kern = step_kernel<DT, ODT, TV, TLV, FXV, Q2V, FV>;                                                  \
+        auto kern = step_kernel<DT, ODT, TV, TLV, FXV, Q2V, FV, HB>;                                                  \
         static std::atomic<size_t> allowed{0};                                                                  \
         if (dyn > allowed.load(std::memory_order_relaxed)) {                                                    \
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                       \
                                                      hipFuncAttributeMaxDynamicSharedMemorySize,                \
-                                                     static_cast<int>(kStepLdsBudget));                         \
+                                                     static_cast<int>(step_lds_budget(HB)));                    \
             if (e != hipSuccess) return e;                                                                      \
-            allowed.store(kStepLdsBudget, std::memory_order_relaxed);                                           \
+            allowed.store(step_lds_budget(HB), std::memory_order_relaxed);                                      \
         }                                                                                                       \
-        return launch_kernel(kern, grid, kStepThreads, s, qp, codebook, codes, dims0, dims1, d.Lmax, seq_len, Kp, Vp, \
+        return launch_kernel(kern, grid, step_threads(HB), s, qp, codebook, codes, dims0, dims1, d.Lmax, seq_len, Kp, Vp, \
                              a, dyn);                                                                           \
     }
     constexpr int kStepQ2Code = 200000, kStepFCode = 400000;
     switch ((a.kvq ? kStepQ2Code : 0) + (a.n_forced > 0 ? kStepFCode : 0) + T) {
+#ifdef SIK_STEP_PAIRS
+        SIK_STEP2(16, 0)
+        SIK_STEP2(24, 0)
+        SIK_STEP2(24, 8)
+        SIK_STEP2(28, 8)
+        SIK_STEP2(32, 8)
+#else
         SIK_STEP(1, 0)
         SIK_STEP(2, 0)
         SIK_STEP(3, 0)
@@ -1143,9 +1315,11 @@ static hipError_t launch_step_t(const Dims& d, int T, int nchunk, size_t dyn, co
         SIK_STEP_F(12, 4)
         SIK_STEP_F(14, 4)
         SIK_STEP_F(16, 4)
+#endif
         default: return hipErrorInvalidValue;
     }
 #undef SIK_STEP
+#undef SIK_STEP2
 #undef SIK_STEP_Q2
 #undef SIK_STEP_F
 #undef SIK_STEP_FX

@@ -1,0 +1,77 @@
+"""The one-launch step with two heads to a workgroup (chunks of 8192 tokens and more on 16-bit rows): the tokens it
+selects, and the attention over them, against the two-launch step on the same cache, which shares none of its kernels."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_14224_amd as sik
+
+pytestmark = pytest.mark.gpu
+TDT = {"bf16": torch.bfloat16, "fp16": torch.float16}
+
+
+def build(B, Hkv, Hq, capacity, lens, k, dtype, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    lay = sik.make_layout(B, Hkv, Hq, 128, capacity, TDT[dtype], torch.float32)
+    s = dict(lay=lay, ws=sik.alloc_workspace(lay, k), lens=torch.tensor(lens, dtype=torch.int32, device="cuda"))
+    s["K"], s["V"] = (torch.randn(B, Hkv, capacity, 128, generator=gen, device="cuda", dtype=torch.float32).to(TDT[dtype])
+                      for _ in range(2))
+    s["mu"] = torch.empty(B, Hkv, 128, device="cuda")
+    s["cb"] = torch.empty(B, Hkv, 32, 16, 4, device="cuda")
+    s["codes"] = torch.zeros(B, Hkv, capacity, 16, dtype=torch.uint8, device="cuda")
+    counts = torch.empty(B, Hkv, 32, 16, dtype=torch.int32, device="cuda")
+    sik.sik_quantize_keys(lay, s["K"], s["lens"], 0, 0, sik.SIK_Q_FIT, s["mu"], s["cb"], counts, s["codes"], s["ws"])
+    s["q"] = torch.randn(B, Hq, 128, generator=gen, device="cuda").to(TDT[dtype])
+    s["new"] = [torch.randn(B, Hkv, 128, generator=gen, device="cuda").to(TDT[dtype]) for _ in range(2)]
+    return s
+
+
+def step(s, k, launches, append, q, per_mille=0):
+    lens, codes = s["lens"].clone(), s["codes"].clone()
+    K, V = (s["K"].clone(), s["V"].clone()) if append else (s["K"], s["V"])
+    B, Hq = q.shape[:2]
+    out = torch.full((B, Hq, 128), np.nan, device="cuda")
+    idx = torch.full((B, Hq, k), -7, dtype=torch.int32, device="cuda")
+    sik.sik_decode_step_ex(s["lay"], q=q, k_new=s["new"][0] if append else None, v_new=s["new"][1] if append else None, K=K,
+                           V=V, seq_len=lens, mu=s["mu"], codebook=s["cb"], codes=codes, k=k, k_per_mille=per_mille,
+                           out=out, idx_out=idx, workspace=s["ws"], launches=launches)
+    torch.cuda.synchronize()
+    assert sik.sik_workspace_status(s["ws"]) == 0
+    return out, torch.sort(idx, dim=-1).values, lens, codes, K, V
+
+
+# tokens of a chunk: 8192, 12288, 16384, 18432, 20480; heads of a group: whole and half pairs; one and several chunks
+CASES = [
+    (33, 8, 24, 8192, 256, "bf16", False),    # one chunk of 8192, more workgroups than two per compute unit, 2 + 1 heads
+    (32, 8, 16, 8200, 100, "fp16", True),     # one chunk of 12288 mostly empty, one pair per KV head
+    (16, 8, 40, 12289, 617, "bf16", True),    # one chunk of 16384, 2 + 2 + 1 heads
+    (16, 8, 56, 18000, 700, "fp16", False),   # 2 + 2 + 2 + 1 heads
+    (16, 8, 32, 36864, 1500, "bf16", True),   # two chunks of 18432, the second one full
+    (16, 8, 32, 36866, 4, "fp16", True),      # two chunks of 20480
+]
+
+
+@pytest.mark.parametrize("B,Hkv,Hq,L,k,dtype,append", CASES)
+def test_head_pairs_pick_what_two_launches_pick(B, Hkv, Hq, L, k, dtype, append):
+    lens = [max(0, L - append - (b * 977 if b % 3 else 0)) for b in range(B)]
+    lens[1:5] = [0, 1, k, 8191]
+    s = build(B, Hkv, Hq, L, lens, k, dtype, seed=L)
+    tokens = sik.sik_plan_info(s["lay"])[7] * 1024
+    assert tokens >= 8192
+    for q in (s["q"], torch.zeros_like(s["q"])):  # zero: all scores equal, the threshold bin holds every token
+        want = step(s, k, 2, append, q)
+        got = step(s, k, 1, append, q)
+        for a, b in zip(got[1:], want[1:]):
+            assert torch.equal(a, b)
+        # binary32 sums over the same rows in another order (chunk and slice sizes differ)
+        scale = want[0].abs().amax(dim=-1, keepdim=True)
+        assert bool(((got[0] - want[0]).abs() <= 2e-5 * scale).all())
+        again = step(s, k, 1, append, q)
+        assert torch.equal(again[0], got[0])  # the same bits whatever the order of arrival
+
+
+def test_head_pairs_budget_follows_the_context():
+    s = build(16, 8, 32, 16384, [16384 - 700 * b for b in range(16)], 1229, "bf16", seed=3)
+    want, got = (step(s, 1229, launches, False, s["q"], per_mille=75) for launches in (2, 1))
+    assert torch.equal(got[1], want[1])
+    assert bool(((got[0] - want[0]).abs() <= 2e-5 * want[0].abs().amax(dim=-1, keepdim=True)).all())

@@ -64,3 +64,12 @@ def test_registers_leave_room_for_four_compressing_workgroups():
     assert all(k[".max_flat_workgroup_size"] == 384 and k[".group_segment_fixed_size"] <= 160 * 1024 // 4
                for k in some.values())
     assert all(k[".vgpr_count"] <= 80 for k in some.values()), {n: k[".vgpr_count"] for n, k in some.items()}
+
+
+def test_two_head_pair_workgroups_share_a_compute_unit():
+    # workgroups of a pair launch wait for each other, two to a compute unit: 2 x 8 wavefronts on 4 SIMDs of 512 registers,
+    # and 160 KB of LDS for two times the static part and the 64 KB that the plan may ask for
+    some = {n: k for n, k in _kernels().items() if "step_kernel" in n and k[".max_flat_workgroup_size"] == 512}
+    assert len(some) == 20
+    assert all(k[".vgpr_count"] <= 128 and k[".vgpr_spill_count"] == 0 for k in some.values())
+    assert all(k[".group_segment_fixed_size"] + 64 * 1024 <= 80 * 1024 for k in some.values())
