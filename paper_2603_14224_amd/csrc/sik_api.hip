@@ -142,7 +142,7 @@ int sik_plan_info(const sik_layout* layout, int32_t* info) {
     // one-launch decode step: tokens per thread (chunk = 1024 x that) on the current device, 0 = not taken
     size_t dyn;
     int listcap, snc;
-    const int tt = step_plan(d, 1, false, device_compute_units(), false, false, &snc, &dyn, &listcap);
+    const int tt = step_plan(d, 1, false, device_compute_units(), false, false, false, false, &snc, &dyn, &listcap);
     info[7] = step_chunk_k(tt);
     return SIK_OK;
 }
@@ -375,18 +375,29 @@ static int decode_step_impl(const sik_layout* layout, const void* q, const void*
     // stay in registers, chunks of a head exchange only histograms, partials and threshold-bin candidates.
     size_t step_dyn = 0;
     int step_nchunk = 0, step_listcap = 0;
-    // (by default only for large launches: with one sequence the histogram exchange between the many chunks of a
-    // head and the heavier barriers of 1024-thread workgroups cost more than the launch boundary they save)
+    // By default where a single chunk per head block pays (step_single_pays), and for large launches: with one sequence
+    // the histogram exchange between the many chunks of a head and the heavier barriers of 1024-thread workgroups cost
+    // more than the launch boundary they save.  (Two or three chunks per head block would already pay on 16-bit rows
+    // from about a million keys, 10 x 8 x 16K with 4:1 52 -> 47 us, but such workgroups wait for each other: steps on two
+    // streams, each of which now runs, could keep each other's from starting.)
     const bool large = static_cast<int64_t>(d.units()) * ((d.R + 3) / 4) * d.Lmax > (2 << 20);
-    const bool one_launch = !opt.group_shared && opt.launches != 2 && (large || opt.launches != 0);
+    const bool one_launch = !opt.group_shared && opt.launches != 2;
     const bool first_pass_16 = opt.launches == 3 && !kvq && opt.n == 0;
     int step_T = 0;
-    if (one_launch && first_pass_16)
-        step_T = step_plan(d, k, k_new != nullptr, cus, true, false, &step_nchunk, &step_dyn,
-                           &step_listcap);
-    if (one_launch && step_T == 0)
-        step_T = step_plan(d, k, k_new != nullptr, cus, false, kvq != nullptr || opt.n > 0,
-                           &step_nchunk, &step_dyn, &step_listcap);
+    auto plan = [&](bool fx, bool single) {
+        return step_plan(d, k, k_new != nullptr, cus, fx, kvq != nullptr, opt.n > 0, single, &step_nchunk, &step_dyn,
+                         &step_listcap);
+    };
+    if (one_launch && first_pass_16) step_T = plan(true, false);
+    if (one_launch && opt.launches == 0 && opt.n == 0) {
+        step_T = plan(false, true);
+        if (step_T > 0 && !step_single_pays(d, step_chunk_k(step_T), kvq != nullptr, cus)) step_T = 0;
+    }
+    // (records, several rounds of workgroups, the last one a quarter empty or more and a block's table entries too:
+    // 24 x 8 x 16K with 5:1 95 us as two launches against 124)
+    const int blocks = d.units() * ((d.R + 3) / 4), rounds = (blocks + cus - 1) / (cus > 0 ? cus : 1);
+    const bool ill = kvq && blocks > cus && (d.R % 4 == 1 || d.R % 4 == 2) && 8 * blocks < 7 * rounds * cus;
+    if (one_launch && step_T == 0 && ((large && !ill) || opt.launches != 0)) step_T = plan(false, false);
     if (step_T > 0) {
         const Append ap{static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new),
                         static_cast<uint16_t*>(K), static_cast<uint16_t*>(V), mu, codes, alpha, kvq};

@@ -151,8 +151,10 @@ bool fused_plan(const Dims& d, int* nchunk, int* chunk);
 // one-launch decode step (sik_step.hip)
 size_t step_sync_words(const Dims& d);
 int step_max_chunks(const Dims& d);
-int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool special, int* nchunk, size_t* dyn_lds,
-              int* listcap);  // special: the 2-bit cache, or a forced set
+// single: plans with one chunk per head block only
+int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool kvq, bool forced, bool single, int* nchunk,
+              size_t* dyn_lds, int* listcap);
+bool step_single_pays(const Dims& d, int kilo, bool kvq, int cus);
 int step_chunk_k(int code);
 int device_compute_units();
 hipError_t launch_sync_init(const Dims& d, const Workspace& w, hipStream_t s);

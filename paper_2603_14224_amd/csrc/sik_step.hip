@@ -15,8 +15,9 @@ constexpr int kStepT[][2] = {{1, 0}, {2, 0}, {3, 0}, {4, 0}, {6, 0}, {8, 0}, {12
 constexpr int kStepFx[] = {4, 8, 12, 16, 20};
 // the same for the variant with two heads to a workgroup of 512 threads; chunk = 512 x sum
 constexpr int kStepPair[][2] = {{16, 0}, {24, 0}, {24, 8}, {28, 8}, {32, 8}};
-// the pairs instantiated for the 2-bit cache as well
-constexpr int kStepQ2[][2] = {{1, 0}, {4, 0}, {12, 0}, {12, 4}, {14, 4}, {16, 4}};
+// the pairs instantiated for the 2-bit cache, and with a forced set for either cache
+constexpr int kStepQ2[][2] = {{1, 0}, {2, 0}, {4, 0}, {8, 0}, {12, 0}, {12, 4}, {14, 4}, {16, 4}};
+constexpr int kStepForced[][2] = {{1, 0}, {4, 0}, {12, 0}, {12, 4}, {14, 4}, {16, 4}};
 
 size_t step_sync_words(const Dims& d) {
     return kSyncHeader + static_cast<size_t>(d.rows()) * kSyncPerRow + static_cast<size_t>(d.B) * kSyncPerSeq;
@@ -53,7 +54,7 @@ static size_t step_dyn_bytes(int heads, int chunk, int TL, int k, int* listcap) 
 // 8 x 8 x 40K with 6:1 92.9 -> 86.6; 4 x 8 x 128K with 4:1 93.3 -> 90.7; 64 x 4 x 16K with 2:1 57.9 -> 53.7; none slower.
 // On 2-bit records the gather is bound by vector instructions too and there is little to overlap: 32 x 8 x 16K 60.7 us with
 // four heads, 64.2 with two.  Budgets whose lists do not fit the smaller LDS share (about 4000) keep four heads.
-int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool special, int* nchunk_out, size_t* dyn_out,
+int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool kvq, bool forced, bool single, int* nchunk_out, size_t* dyn_out,
               int* listcap_out) {
     if (d.R < 2 || d.R > 255 || cus < 1) return 0;
     auto fits = [&](int heads, int tokens, int tl) {
@@ -62,7 +63,7 @@ int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool specia
         const int nchunk = (d.Lmax + chunk - 1) / chunk;
         if (nchunk > kMaxChunks || nchunk > step_max_chunks(d)) return false;
         const bool resident = static_cast<int64_t>(hbs) * nchunk <= static_cast<int64_t>(cus) * (heads == kHB ? 1 : 2);
-        if (!resident && nchunk != 1) return false;
+        if (nchunk != 1 && (single || !resident)) return false;
         int listcap;
         const size_t dyn = step_dyn_bytes(heads, chunk, tl, k, &listcap);
         if (dyn > step_lds_budget(heads)) return false;
@@ -72,12 +73,17 @@ int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool specia
         return true;
     };
     if (fx) {
-        if (special) return 0;
+        if (kvq || forced) return 0;
         for (const int t : kStepFx)
             if (fits(kHB, t, 0)) return kStepFxCode + t * 100;
         return 0;
     }
-    if (special) {  // (the pairs instantiated for the 2-bit cache and for forced sets)
+    if (forced) {
+        for (const auto& tt : kStepForced)
+            if (fits(kHB, tt[0] + tt[1], tt[1])) return tt[0] * 100 + tt[1];
+        return 0;
+    }
+    if (kvq) {
         for (const auto& tt : kStepQ2)
             if (fits(kHB, tt[0] + tt[1], tt[1])) return tt[0] * 100 + tt[1];
         return 0;
@@ -96,6 +102,32 @@ int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool specia
 int step_chunk_k(int code) {
     const int tokens = code % 100000 / 100 + code % 100;
     return code >= kStepPairCode ? tokens / 2 : tokens;
+}
+
+// Whether the one-launch step with a single chunk per head block, of kilo x 1024 tokens, beats the two launches.  Nothing
+// in it waits for another workgroup; against the two launches it saves the boundary, the scores' way through memory
+// and the last workgroup's exchange, and it loses where its workgroups (one per four heads, or two per four in pairs) are
+// too few for the chip.  Measured on 256 compute units with 4 % of the context selected, two launches -> one launch, us,
+// by head blocks (units x ceil(R / 4)) and context:
+//   rows      1000: 8 blocks 15.9 -> 12.9, 256 19.3 -> 13.6      2000: 8 blocks 16.0 -> 15.7, 128 19.2 -> 16.0
+//             4096: 64 blocks 20.2 -> 21.1, 80 22.9 -> 21.2, 128 25.4 -> 22.8, 192 34.2 -> 25.6
+//             6000: 80 blocks 22.9 -> 25.9, 96 32.3 -> 26.8      8192: 32 blocks 20.7 -> 23.7, 64 26.2 -> 24.5, 128 38 -> 31
+//             12288: 64 blocks 32.5 -> 33.2, 80 36.9 -> 31.6, 192 81 -> 54    16384: 64 blocks 39 -> 45, 80 41.5 -> 38.7
+//             20000: 80 blocks 50.6 -> 52.3, 96 72 -> 58
+//             more than 256 blocks: 384 of 5:1 4096 46 -> 49, 8192 65 -> 59; 512 of 8:1 2048 48 -> 38, 4096 69 -> 58
+//   records   1000: 8 blocks 17.6 -> 14.9      2000: 8 blocks 17.6 -> 17.7, 64 20.8 -> 17.7
+//             4096: 64 blocks 22.7 -> 24.6, 128 26.0 -> 24.6, 192 35.7 -> 24.7
+//             8192: 128 blocks 35.4 -> 37.3, 192 48.2 -> 37.4    12288: 128 blocks 47.0 -> 50.3, 160 68.9 -> 51.8
+bool step_single_pays(const Dims& d, int kilo, bool kvq, int cus) {
+    const int blocks = d.units() * ((d.R + kHB - 1) / kHB);
+    const bool full = d.R % kHB == 0 || d.R % kHB == 3;  // (nearly) all of a block's table entries in use
+    if (blocks > cus) return kvq ? kilo == 1 || (full && kilo <= 4) : full || kilo >= 8;
+    int least;  // in sixteenths of the compute units
+    if (kvq)
+        least = kilo == 1 ? 0 : (kilo == 2 ? 2 : (kilo <= 4 ? 8 : 10));
+    else
+        least = kilo <= 2 ? 0 : (kilo == 8 ? 4 : (kilo == 6 || kilo > 16 ? 6 : 5));
+    return 16 * blocks >= least * cus;
 }
 
 int device_compute_units() {

@@ -1304,7 +1304,9 @@ static hipError_t launch_step_t(const Dims& d, int T, int nchunk, size_t dyn, co
         SIK_STEP_FX(16)
         SIK_STEP_FX(20)
         SIK_STEP_Q2(1, 0)
+        SIK_STEP_Q2(2, 0)
         SIK_STEP_Q2(4, 0)
+        SIK_STEP_Q2(8, 0)
         SIK_STEP_Q2(12, 0)
         SIK_STEP_Q2(12, 4)
         SIK_STEP_Q2(14, 4)

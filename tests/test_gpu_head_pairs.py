@@ -1,5 +1,6 @@
-"""The one-launch step with two heads to a workgroup (chunks of 8192 tokens and more on 16-bit rows): the tokens it
-selects, and the attention over them, against the two-launch step on the same cache, which shares none of its kernels."""
+"""The one-launch step with two heads to a workgroup (chunks of 8192 tokens and more on 16-bit rows), and the launch
+structure that the library takes by itself: the tokens selected, and the attention over them, against the two-launch step
+on the same cache, which shares none of the kernels."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +11,7 @@ pytestmark = pytest.mark.gpu
 TDT = {"bf16": torch.bfloat16, "fp16": torch.float16}
 
 
-def build(B, Hkv, Hq, capacity, lens, k, dtype, seed):
+def build(B, Hkv, Hq, capacity, lens, k, dtype, seed, q2=False):
     gen = torch.Generator(device="cuda").manual_seed(seed)
     lay = sik.make_layout(B, Hkv, Hq, 128, capacity, TDT[dtype], torch.float32)
     s = dict(lay=lay, ws=sik.alloc_workspace(lay, k), lens=torch.tensor(lens, dtype=torch.int32, device="cuda"))
@@ -20,7 +21,12 @@ def build(B, Hkv, Hq, capacity, lens, k, dtype, seed):
     s["cb"] = torch.empty(B, Hkv, 32, 16, 4, device="cuda")
     s["codes"] = torch.zeros(B, Hkv, capacity, 16, dtype=torch.uint8, device="cuda")
     counts = torch.empty(B, Hkv, 32, 16, dtype=torch.int32, device="cuda")
-    sik.sik_quantize_keys(lay, s["K"], s["lens"], 0, 0, sik.SIK_Q_FIT, s["mu"], s["cb"], counts, s["codes"], s["ws"])
+    if q2:
+        s["kvq"], s["alpha"] = sik.alloc_kvq(lay), torch.empty(B, Hkv, 128, device="cuda")
+        sik.sik_prefill_compress(lay, s["K"], s["V"], s["lens"], s["mu"], s["cb"], counts, s["codes"], s["alpha"], s["kvq"],
+                                 s["ws"])
+    else:
+        sik.sik_quantize_keys(lay, s["K"], s["lens"], 0, 0, sik.SIK_Q_FIT, s["mu"], s["cb"], counts, s["codes"], s["ws"])
     s["q"] = torch.randn(B, Hq, 128, generator=gen, device="cuda").to(TDT[dtype])
     s["new"] = [torch.randn(B, Hkv, 128, generator=gen, device="cuda").to(TDT[dtype]) for _ in range(2)]
     return s
@@ -28,16 +34,19 @@ def build(B, Hkv, Hq, capacity, lens, k, dtype, seed):
 
 def step(s, k, launches, append, q, per_mille=0):
     lens, codes = s["lens"].clone(), s["codes"].clone()
-    K, V = (s["K"].clone(), s["V"].clone()) if append else (s["K"], s["V"])
+    if "kvq" in s:
+        kvq, K, V = s["kvq"].clone(), None, None
+    else:
+        kvq, (K, V) = None, ((s["K"].clone(), s["V"].clone()) if append else (s["K"], s["V"]))
     B, Hq = q.shape[:2]
     out = torch.full((B, Hq, 128), np.nan, device="cuda")
     idx = torch.full((B, Hq, k), -7, dtype=torch.int32, device="cuda")
     sik.sik_decode_step_ex(s["lay"], q=q, k_new=s["new"][0] if append else None, v_new=s["new"][1] if append else None, K=K,
-                           V=V, seq_len=lens, mu=s["mu"], codebook=s["cb"], codes=codes, k=k, k_per_mille=per_mille,
+                           V=V, kvq=kvq, alpha=s.get("alpha"), seq_len=lens, mu=s["mu"], codebook=s["cb"], codes=codes, k=k, k_per_mille=per_mille,
                            out=out, idx_out=idx, workspace=s["ws"], launches=launches)
     torch.cuda.synchronize()
     assert sik.sik_workspace_status(s["ws"]) == 0
-    return out, torch.sort(idx, dim=-1).values, lens, codes, K, V
+    return out, torch.sort(idx, dim=-1).values, lens, codes, *((K, V) if kvq is None else (kvq,))
 
 
 # tokens of a chunk: 8192, 12288, 16384, 18432, 20480; heads of a group: whole and half pairs; one and several chunks
@@ -74,4 +83,19 @@ def test_head_pairs_budget_follows_the_context():
     s = build(16, 8, 32, 16384, [16384 - 700 * b for b in range(16)], 1229, "bf16", seed=3)
     want, got = (step(s, 1229, launches, False, s["q"], per_mille=75) for launches in (2, 1))
     assert torch.equal(got[1], want[1])
+    assert bool(((got[0] - want[0]).abs() <= 2e-5 * want[0].abs().amax(dim=-1, keepdim=True)).all())
+
+
+# around the lines between the routes: contexts at and beyond the chunk sizes, few and many head blocks, several rounds
+@pytest.mark.parametrize("q2", [False, True], ids=["rows", "records"])
+@pytest.mark.parametrize("B,Hkv,Hq,L,k", [(1, 1, 4, 1024, 60), (1, 1, 4, 1025, 60), (3, 2, 6, 2048, 100), (3, 2, 6, 2049, 100),
+                                          (10, 8, 32, 4096, 2000), (20, 8, 32, 4097, 170), (8, 8, 32, 8192, 333),
+                                          (5, 8, 40, 12288, 500), (20, 4, 28, 20480, 700), (48, 8, 16, 1000, 33),
+                                          (34, 8, 64, 1030, 50)])
+def test_route_taken_by_itself(B, Hkv, Hq, L, k, q2):
+    lens = [max(0, L - 1 - (b * 131 if b % 2 else 0)) for b in range(B)]
+    s = build(B, Hkv, Hq, L, lens, k, "bf16", seed=L + B, q2=q2)
+    want, got = step(s, k, 2, True, s["q"]), step(s, k, 0, True, s["q"])
+    for a, b in zip(got[1:], want[1:]):
+        assert torch.equal(a, b)
     assert bool(((got[0] - want[0]).abs() <= 2e-5 * want[0].abs().amax(dim=-1, keepdim=True)).all())
