@@ -232,10 +232,17 @@ constexpr int kEncEntries = 16 * 5;              // per group: 16 codes x (4 sum
 constexpr int kEncTokPerIter = kEncThreads / 32;  // tokens the two encoding wavefronts take per step
 constexpr int kEncUnroll = 16;
 
+// The 8 bytes of sign group g of row i (a 32-bit offset: the rows of a KV head are at most 1.06 GB).
+__device__ __forceinline__ const uint2* key_slice(const uint2* rows, int i, int g) {
+    return reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(rows) +
+                                          (static_cast<uint32_t>(i) * (kD * 2u) + static_cast<uint32_t>(g) * 8u));
+}
+
 // The encoder's per-lane state and token steps, shared by encode_kernel and compress_kernel.
 template <int DT, bool CLUSTER>
 struct SignEncoder {
     float4 m;        // channel means of this lane's sign group
+    bool finite;     // CLUSTER: every mean of the wavefront's groups is (the same in every lane)
     float4* cols;    // this lane's accumulator columns (stride kWave per code)
     uint32_t* colc;
     uint8_t* cbase;  // code plane of the (sequence, KV head)
@@ -243,6 +250,11 @@ struct SignEncoder {
 
     __device__ __forceinline__ void clear() {
         if constexpr (CLUSTER) {
+            // a mean of +0 becomes -0: no difference changes, but that of a key of -0 (not below its mean) is then +0
+            m = make_float4(m.x == 0.f ? -0.f : m.x, m.y == 0.f ? -0.f : m.y, m.z == 0.f ? -0.f : m.z,
+                            m.w == 0.f ? -0.f : m.w);
+            const float top = fmaxf(fmaxf(fabsf(m.x), fabsf(m.y)), fmaxf(fabsf(m.z), fabsf(m.w)));
+            finite = __ballot(!(top < INFINITY) || m.x != m.x || m.y != m.y || m.z != m.z || m.w != m.w) == 0ull;
 #pragma unroll
             for (int c = 0; c < 16; ++c) {
                 cols[c * kWave] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -275,35 +287,55 @@ struct SignEncoder {
         const int other = neighbour(code);
         if ((g & 1) == 0) cbase[static_cast<size_t>(i) * kCodeBytes + (g >> 1)] = static_cast<uint8_t>((code << 4) | other);
         if constexpr (CLUSTER) {
-            cols[code * kWave] = plus(cols[code * kWave], d);
-            count(code);
+            const int inv = 15 - code;
+            cols[inv * kWave] = plus(cols[inv * kWave], d);
+            count(inv);
         }
     }
     // Tokens i and i + kEncTokPerIter, both in the range.  The lanes of a pair exchange the nibble that the other one
     // needs: the even lane stores the first token's byte, the odd lane the second's.  Both accumulators are read
     // before either is written; where the Codes agree the second token adds to the first one's sum, so that every
-    // sum is still added up in token order, and a step of the LDS chain covers two tokens.  (Bound by that chain and by
-    // the instructions between its steps: one token at a time, each under a condition of its own and with its count
-    // read and written back, keys of 1 x 8 x 32K took 51.3 us for the whole fit, now 46.8; 4 x 8 x 64K into records,
-    // where the record builders share the vector units, 421 and 418.)
-    __device__ __forceinline__ void two_tokens(int i, const uint2 v0, const uint2 v1) {
+    // sum is still added up in token order, and a step of the LDS chain covers two tokens.
+    //
+    // With CLUSTER the accumulator columns go by 15 - Code, the sign bits of the differences: for finite means (keys are
+    // finite then) K >= mu fails exactly where the rounded difference is negative (a difference of unequal values is not
+    // rounded to zero), and four sign bits are four instructions, four comparisons ten.
+    struct Two {
         float4 d0, d1;
-        const int c0 = sign(v0, d0), c1 = sign(v1, d1);
+        int c0, c1;
+    };
+    __device__ __forceinline__ int inverted(const uint2 v, float4& d) const {
+        if constexpr (!CLUSTER) return 15 - sign(v, d);
+        d = make_float4(widen16<DT>(v.x & 0xffffu) - m.x, widen16<DT>(v.x >> 16) - m.y, widen16<DT>(v.y & 0xffffu) - m.z,
+                        widen16<DT>(v.y >> 16) - m.w);
+        uint32_t c = __float_as_uint(d.x) >> 31;
+        c = __builtin_amdgcn_alignbit(c, __float_as_uint(d.y), 31);  // 2 c + the sign bit
+        c = __builtin_amdgcn_alignbit(c, __float_as_uint(d.z), 31);
+        c = __builtin_amdgcn_alignbit(c, __float_as_uint(d.w), 31);
+        return static_cast<int>(c);
+    }
+    // codes and differences of the two tokens; the byte goes out
+    __device__ __forceinline__ Two prepare(int i, const uint2 v0, const uint2 v1) const {
+        Two t;
+        t.c0 = inverted(v0, t.d0);
+        t.c1 = inverted(v1, t.d1);
         const bool even = (g & 1) == 0;
-        const int other = neighbour(even ? c1 : c0);
-        const int byte = ((even ? c0 : other) << 4) | (even ? other : c1);
-        cbase[static_cast<size_t>(even ? i : i + kEncTokPerIter) * kCodeBytes + (g >> 1)] = static_cast<uint8_t>(byte);
-        if constexpr (CLUSTER) {
-            const float4 a0 = cols[c0 * kWave], a1 = cols[c1 * kWave];
-            const bool same = c0 == c1;
-            const float4 s0 = plus(a0, d0);
-            const float4 s1 = plus(make_float4(same ? s0.x : a1.x, same ? s0.y : a1.y, same ? s0.z : a1.z,
-                                               same ? s0.w : a1.w), d1);
-            cols[c0 * kWave] = s0;
-            cols[c1 * kWave] = s1;
-            count(c0);
-            count(c1);
-        }
+        const int mine = even ? t.c0 : t.c1, other = neighbour(even ? t.c1 : t.c0);
+        const int byte = even ? (mine << 4) | other : (other << 4) | mine;
+        // (32-bit offset: a code plane holds at most 66 MB)
+        cbase[static_cast<uint32_t>(even ? i : i + kEncTokPerIter) * kCodeBytes + static_cast<uint32_t>(g >> 1)] =
+            static_cast<uint8_t>(~byte);
+        return t;
+    }
+    __device__ __forceinline__ void add(const Two& t, const float4 a0, const float4 a1) {
+        const bool same = t.c0 == t.c1;
+        const float4 s0 = plus(a0, t.d0);
+        const float4 s1 = plus(make_float4(same ? s0.x : a1.x, same ? s0.y : a1.y, same ? s0.z : a1.z,
+                                           same ? s0.w : a1.w), t.d1);
+        cols[t.c0 * kWave] = s0;
+        cols[t.c1 * kWave] = s1;
+        count(t.c0);
+        count(t.c1);
     }
     // N tokens of this lane, i, i + kEncTokPerIter, ...; `whole`, the same in every lane, where all lanes of the
     // workgroup have all of theirs before `end`.  The tokens of a block that is not whole go one at a time: 60 of the
@@ -311,9 +343,27 @@ struct SignEncoder {
     template <int N>
     __device__ __forceinline__ void tokens(int i, const uint2 (&v)[N], int end, bool whole) {
         static_assert(N % 2 == 0, "tokens are taken in twos");
-        if (whole) {
+        if (whole && (!CLUSTER || finite)) {
+            // Codes and differences of the next two tokens are computed while the accumulators of these two are on their
+            // way from LDS.  (Left to the compiler, a wavefront alone on its SIMD waited 37 % of its cycles, most of
+            // them there, and issued 85 vector instructions per two tokens, now 57: keys of 1 x 8 x 32K took 46.8 us for the
+            // whole fit, 43.4 so, 38.3 with the partials published without bank conflicts; 1 x 8 x 2000 24.2 -> 18.3,
+            // 4 x 8 x 64K 235 -> 220, into records 400 -> 391.)
+            Two t = prepare(i, v[0], v[1]);
 #pragma unroll
-            for (int u = 0; u < N; u += 2) two_tokens(i + u * kEncTokPerIter, v[u], v[u + 1]);
+            for (int u = 0; u < N; u += 2) {
+                if constexpr (CLUSTER) {
+                    const float4 a0 = cols[t.c0 * kWave], a1 = cols[t.c1 * kWave];
+                    __builtin_amdgcn_sched_barrier(0);
+                    Two next = t;
+                    if (u + 2 < N) next = prepare(i + (u + 2) * kEncTokPerIter, v[u + 2 < N ? u + 2 : u], v[u + 3 < N ? u + 3 : u]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    add(t, a0, a1);
+                    t = next;
+                } else if (u + 2 < N) {
+                    t = prepare(i + (u + 2) * kEncTokPerIter, v[u + 2 < N ? u + 2 : u], v[u + 3 < N ? u + 3 : u]);
+                }
+            }
         } else {
 #pragma unroll
             for (int u = 0; u < N; ++u)
@@ -323,20 +373,26 @@ struct SignEncoder {
 };
 
 // Workgroup partial of the cluster sums: part[g][code][4 sums, count] from the accumulator columns of the
-// encoding wavefronts (waves 0 and 1 of the workgroup); called by `nthreads` threads after a barrier.
+// encoding wavefronts (waves 0 and 1 of the workgroup); called by `nthreads` threads after a barrier.  A thread takes all
+// five numbers of a (code, group), neighbours neighbouring groups, so that the 128-bit reads meet every bank once (one
+// number per thread, neighbours neighbouring codes: 13 to a bank, 1.4 us per workgroup).
 __device__ __forceinline__ void publish_cluster_partial(const float4* tabs, const uint32_t* tabc, float* pw, int tid,
                                                         int nthreads) {
-    for (int e = tid; e < kG * kEncEntries; e += nthreads) {
-        const int gg = e / kEncEntries, ent = e % kEncEntries, code = ent / 5, comp = ent % 5;
-        float sum = 0.0f;
+    for (int e = tid; e < kG * 16; e += nthreads) {
+        const int gg = e % kG, code = e / kG;
+        float sum[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int w = 0; w < kEncThreads / kWave; ++w) {
-            const int at = (w * 16 + code) * kWave + gg;
-            sum += comp < 4 ? reinterpret_cast<const float*>(&tabs[at])[comp] +
-                                  reinterpret_cast<const float*>(&tabs[at + 32])[comp]
-                            : static_cast<float>(tabc[at] + tabc[at + 32]);
+            const int at = (w * 16 + 15 - code) * kWave + gg;  // (the columns go by 15 - Code)
+            const float4 a = tabs[at], b = tabs[at + 32];
+            sum[0] += a.x + b.x;
+            sum[1] += a.y + b.y;
+            sum[2] += a.z + b.z;
+            sum[3] += a.w + b.w;
+            sum[4] += static_cast<float>(tabc[at] + tabc[at + 32]);
         }
-        pw[e] = sum;
+#pragma unroll
+        for (int c = 0; c < 5; ++c) pw[(gg * 16 + code) * 5 + c] = sum[c];
     }
 }
 
@@ -382,7 +438,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const uint16_t* __r
 #pragma unroll
         for (int u = 0; u < kEncUnroll; ++u) {
             const int i = min(i0 + u * kEncTokPerIter, last);
-            nx[u] = ld_stream(&base[static_cast<size_t>(i) * 32 + g]);
+            nx[u] = ld_stream(key_slice(base, i, g));
         }
     };
     if (start < end) request(start + sub);
@@ -451,7 +507,7 @@ __global__ __launch_bounds__(kCmpThreads, 5) void compress_kernel(
         auto request = [&](int i0) {
 #pragma unroll
             for (int u = 0; u < kCmpEncSteps; ++u)
-                nx[u] = base[static_cast<size_t>(min(i0 + u * kEncTokPerIter, last)) * 32 + g];
+                nx[u] = *key_slice(base, min(i0 + u * kEncTokPerIter, last), g);
         };
         if (start < end) request(start + sub);
         for (int blk = start; blk < end; blk += kCmpBlock) {  // the same trip count on both sides of the workgroup
