@@ -337,13 +337,13 @@ struct SignEncoder {
         count(t.c0);
         count(t.c1);
     }
-    // N tokens of this lane, i, i + kEncTokPerIter, ...; `whole`, the same in every lane, where all lanes of the
-    // workgroup have all of theirs before `end`.  The tokens of a block that is not whole go one at a time: 60 of the
-    // 252 in a workgroup's range at 8 x 2000 to 12345 keys, where the pairs give 5 to 6 % of the whole fit instead of 9.
+    // N tokens of this lane, i, i + kEncTokPerIter, ..., of which those before `end` exist; `left`, the same in every lane:
+    // tokens of the workgroup's range from this block's first one on.
     template <int N>
-    __device__ __forceinline__ void tokens(int i, const uint2 (&v)[N], int end, bool whole) {
+    __device__ __forceinline__ void tokens(int i, const uint2 (&v)[N], int end, int left) {
         static_assert(N % 2 == 0, "tokens are taken in twos");
-        if (whole && (!CLUSTER || finite)) {
+        const bool twos = !CLUSTER || finite;
+        if (twos && left >= N * kEncTokPerIter) {
             // Codes and differences of the next two tokens are computed while the accumulators of these two are on their
             // way from LDS.  (Left to the compiler, a wavefront alone on its SIMD waited 37 % of its cycles, most of
             // them there, and issued 85 vector instructions per two tokens, now 57: keys of 1 x 8 x 32K took 46.8 us for the
@@ -365,9 +365,18 @@ struct SignEncoder {
                 }
             }
         } else {
+            // what is left of a range: in twos as far as every lane has both (1 x 8 x 2000 keys 18.0 -> 17.6 us, 8 x 8 x 12345
+            // ragged 68.5 -> 67.9, against one at a time)
 #pragma unroll
-            for (int u = 0; u < N; ++u)
-                if (i + u * kEncTokPerIter < end) token(i + u * kEncTokPerIter, v[u]);
+            for (int u = 0; u < N; u += 2) {
+                if (twos && left >= (u + 2) * kEncTokPerIter) {
+                    const Two t = prepare(i + u * kEncTokPerIter, v[u], v[u + 1]);
+                    if constexpr (CLUSTER) add(t, cols[t.c0 * kWave], cols[t.c1 * kWave]);
+                } else {
+                    if (i + u * kEncTokPerIter < end) token(i + u * kEncTokPerIter, v[u]);
+                    if (i + (u + 1) * kEncTokPerIter < end) token(i + (u + 1) * kEncTokPerIter, v[u + 1]);
+                }
+            }
         }
     }
 };
@@ -447,7 +456,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const uint16_t* __r
 #pragma unroll
         for (int u = 0; u < kEncUnroll; ++u) v[u] = nx[u];
         request(blk + kEncTokPerIter * kEncUnroll + sub);
-        enc.tokens(blk + sub, v, end, end - blk >= kEncTokPerIter * kEncUnroll);
+        enc.tokens(blk + sub, v, end, end - blk);
     }
     if constexpr (CLUSTER) {
         __syncthreads();
@@ -515,7 +524,7 @@ __global__ __launch_bounds__(kCmpThreads, 5) void compress_kernel(
 #pragma unroll
             for (int u = 0; u < kCmpEncSteps; ++u) v[u] = nx[u];
             request(blk + kCmpBlock + sub);
-            enc.tokens(blk + sub, v, end, end - blk >= kCmpBlock);
+            enc.tokens(blk + sub, v, end, end - blk);
             __syncthreads();
         }
     } else {
