@@ -90,10 +90,10 @@ int sik_version(void);
  * info (host pointer, SIK_PLAN_INFO_LEN int32): [0] token chunks per head of the scoring launch, [1] tokens per such
  * chunk, [2] blocks of up to 4 query heads per KV head, [3] chunks per row of the stand-alone histogram pass of
  * sik_topk, [4] tokens per such chunk, [5] chunks per query head of the fused selection + attention launch (0: max_len
- * is beyond that path), [6] tokens per such chunk, [7] tokens per thread of the one-launch decode step on the
- * current device (its chunks hold 1024 times that; 0: no one-launch plan fits this layout, the step always runs as
- * separate launches; sik_decode_step takes the one-launch step only for large launches, sik_decode_args.launches
- * chooses).  Every chunk holds at most 64512 tokens and there are at most 64 per head; a layout that cannot be cut
+ * is beyond that path), [6] tokens per such chunk, [7] tokens of a chunk of the one-launch decode step on
+ * the current device, in units of 1024 (0: no one-launch plan fits this layout, the step always runs as separate
+ * launches; sik_decode_step takes the one-launch step for large launches and wherever one chunk per head, which may
+ * then be longer, covers the context and fills enough of the device; sik_decode_args.launches chooses).  Every chunk holds at most 64512 tokens and there are at most 64 per head; a layout that cannot be cut
  * that way is SIK_ERR_SHAPE here and in every other call. */
 #define SIK_PLAN_INFO_LEN 8
 int sik_plan_info(const sik_layout *layout, int32_t *info);
@@ -181,8 +181,9 @@ int sik_decode_step(const sik_layout *layout, const void *q, const void *k_new, 
  * workloads of one sequence, 32K and 128K tokens, fit; large batches do not).  The call allocates nothing and
  * frees nothing.  Every call on one GPU shares that GPU's buffer, whatever the stream or thread: calls that
  * overlap in time on one GPU race; calls on one stream are ordered and safe.  The buffer keeps the previous
- * call's contents; the step clears what it needs cleared itself, and always runs as separate scoring and selection
- * + attention launches (no workgroup waits for another, so the buffer needs no initialisation).  The first call on
+ * call's contents; the step clears what it needs cleared itself, and runs as sik_decode_step does where no workgroup
+ * of it waits for another, else as separate scoring and selection + attention launches (so the buffer needs no
+ * initialisation).  The first call on
  * a GPU looks the buffer's address up (hipGetSymbolAddress) and must therefore be made outside stream capture. */
 #define SIK_STATIC_SCRATCH_BYTES (32u << 20)
 int sik_decode_step_static(const sik_layout *layout, const void *q, const void *k_new, const void *v_new, void *K,

@@ -12,7 +12,9 @@ thread_local LaunchEvents g_launch_events;
 
 // Scratch memory of sik_decode_step_static: one copy per GPU, part of the loaded code object.  On the host this
 // name is only a handle for hipGetSymbolAddress; the device address it yields (per device) is what kernels get.
-static __device__ __align__(256) unsigned char scratch[SIK_STATIC_SCRATCH_BYTES];
+// (The reserved synchronisation words come on top of the stated size.)
+constexpr size_t kStaticBytes = SIK_STATIC_SCRATCH_BYTES + kSyncReserve * 4;
+static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 constexpr int kMaxDevices = 64;
 static std::atomic<void*> g_scratch_ptr[kMaxDevices];
 
@@ -389,7 +391,7 @@ static int decode_step_impl(const sik_layout* layout, const void* q, const void*
                          &step_listcap);
     };
     if (one_launch && first_pass_16) step_T = plan(true, false);
-    if (one_launch && opt.launches == 0 && opt.n == 0) {
+    if (one_launch && opt.launches <= 0 && opt.n == 0) {
         step_T = plan(false, true);
         if (step_T > 0 && !step_single_pays(d, step_chunk_k(step_T), kvq != nullptr, cus)) step_T = 0;
     }
@@ -397,7 +399,7 @@ static int decode_step_impl(const sik_layout* layout, const void* q, const void*
     // 24 x 8 x 16K with 5:1 95 us as two launches against 124)
     const int blocks = d.units() * ((d.R + 3) / 4), rounds = (blocks + cus - 1) / (cus > 0 ? cus : 1);
     const bool ill = kvq && blocks > cus && (d.R % 4 == 1 || d.R % 4 == 2) && 8 * blocks < 7 * rounds * cus;
-    if (one_launch && step_T == 0 && ((large && !ill) || opt.launches != 0)) step_T = plan(false, false);
+    if (one_launch && step_T == 0 && ((large && !ill && opt.launches == 0) || opt.launches > 0)) step_T = plan(false, false);
     if (step_T > 0) {
         const Append ap{static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new),
                         static_cast<uint16_t*>(K), static_cast<uint16_t*>(V), mu, codes, alpha, kvq};
@@ -492,15 +494,17 @@ int sik_decode_step_static(const sik_layout* layout, const void* q, const void* 
     const int rc = check_layout(layout, &d);
     if (rc) return rc;
     if (k < 1 || k > d.Lmax) return SIK_ERR_K_RANGE;
-    if (carve(d, k, nullptr).total_bytes > SIK_STATIC_SCRATCH_BYTES) return SIK_ERR_STATIC_LIMIT;
+    if (carve(d, k, nullptr).total_bytes > kStaticBytes) return SIK_ERR_STATIC_LIMIT;
     void* ws = static_scratch();
     if (ws == nullptr) return SIK_ERR_LAUNCH;
-    // always the two launches: nothing in them waits on another workgroup, so the shared buffer never needs the
-    // one-time initialisation (and re-initialisation after a give-up) that the one-launch step asks of a workspace
+    // One launch with a single chunk per head block where sik_decode_step takes that (the same bits), else two: nothing in
+    // either waits on another workgroup, so the shared buffer never needs an initialisation after a give-up; its
+    // synchronisation words are zero when the library is loaded, lie in the reserved part that nothing else is written
+    // to, and every step leaves them at zero.
     StepOptions opt{};
-    opt.launches = 2;
+    opt.launches = kSingleOrTwo;
     return decode_step_impl(layout, q, k_new, v_new, K, V, nullptr, nullptr, seq_len, mu, codebook, codes, k,
-                            softmax_scale, out, idx_out, ws, SIK_STATIC_SCRATCH_BYTES, stream, nullptr, opt);
+                            softmax_scale, out, idx_out, ws, kStaticBytes, stream, nullptr, opt);
 }
 
 int sik_decode_step_profiled(const sik_layout* layout, const void* q, const void* k_new, const void* v_new,

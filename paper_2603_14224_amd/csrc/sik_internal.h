@@ -132,6 +132,7 @@ hipError_t launch_attn(const Dims& d, const Workspace& w, const void* q, const v
 // StepOptions set: n_forced entries per (b, KV head), always attended and outside the top-k (launch_score gave them
 // -infinity); with fK, fV (2-bit cache only) they are attended from those 16-bit rows [B, Hkv, n_forced, D],
 // centred by mu, instead of from their records.
+constexpr int kSingleOrTwo = -1;
 struct StepOptions {  // what sik_decode_step_ex adds to the plain decode step
     const int32_t* idx;
     int n;
@@ -141,7 +142,7 @@ struct StepOptions {  // what sik_decode_step_ex adds to the plain decode step
     int k_per_mille;    // > 0: per-sequence budget min(k, ceil(L * k_per_mille / 1000))
     bool group_shared;  // one index set per KV head from the summed scores of its query heads (unfused path)
     int launches;       // 0: the library chooses; 1 / 3: the one-launch step whenever its plan allows (3: with the
-                        // 16-bit first pass); 2: never
+                        // 16-bit first pass); 2: never; kSingleOrTwo: never with chunks that wait for each other
     int spin_limit;     // polls a bounded wait of the one-launch step may take (0: the default)
 };
 hipError_t launch_fused(const Dims& d, const Workspace& w, const void* q, const void* K, const void* V,
@@ -149,6 +150,7 @@ hipError_t launch_fused(const Dims& d, const Workspace& w, const void* q, const 
                         int k, float scale, int32_t* idx_out, void* out, hipStream_t s);
 bool fused_plan(const Dims& d, int* nchunk, int* chunk);
 // one-launch decode step (sik_step.hip)
+constexpr size_t kSyncReserve = 65536;  // 256 KB: layouts of up to about 16000 query-head rows
 size_t step_sync_words(const Dims& d);
 int step_max_chunks(const Dims& d);
 // single: plans with one chunk per head block only

@@ -19,8 +19,12 @@ constexpr int kStepPair[][2] = {{16, 0}, {24, 0}, {24, 8}, {28, 8}, {32, 8}};
 constexpr int kStepQ2[][2] = {{1, 0}, {2, 0}, {4, 0}, {8, 0}, {12, 0}, {12, 4}, {14, 4}, {16, 4}};
 constexpr int kStepForced[][2] = {{1, 0}, {4, 0}, {12, 0}, {12, 4}, {14, 4}, {16, 4}};
 
+// At least kSyncReserve words whatever the layout: the words beyond a layout's own stay zero as well, so that a workspace
+// that serves several layouts in turn has zeros where the largest of them looks (without this, what a small layout's
+// scoring launch leaves behind its few counters would be taken for arrivals by a larger layout's one-launch step).
 size_t step_sync_words(const Dims& d) {
-    return kSyncHeader + static_cast<size_t>(d.rows()) * kSyncPerRow + static_cast<size_t>(d.B) * kSyncPerSeq;
+    const size_t need = kSyncHeader + static_cast<size_t>(d.rows()) * kSyncPerRow + static_cast<size_t>(d.B) * kSyncPerSeq;
+    return need < kSyncReserve ? kSyncReserve : need;
 }
 
 // Upper bound of the chunks per head block any one-launch plan of this layout uses (sizes the histogram area).

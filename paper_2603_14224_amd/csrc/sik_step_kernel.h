@@ -457,6 +457,14 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
     } else {
 #pragma unroll
     for (int it = 0; it < TT; ++it) {
+        if (start + it * NT >= end) {  // uniform: no token in this slot, nor in those after it
+#pragma unroll
+            for (int s = 0; s < HB; ++s)
+                if (it < T) sc[it < T ? it : 0][s] = __builtin_nanf("");
+            if (it >= T) lsc[(it - T) * NT + tid] = make_entry({__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")});
+            if constexpr (FX) fx[it][0] = fx[it][1] = 0u;
+            continue;
+        }
         const int tok = start + it * NT + tid;
         uint4 code = cur[it & 1];
         if (it + 2 < TT) {

@@ -99,3 +99,18 @@ def test_route_taken_by_itself(B, Hkv, Hq, L, k, q2):
     for a, b in zip(got[1:], want[1:]):
         assert torch.equal(a, b)
     assert bool(((got[0] - want[0]).abs() <= 2e-5 * want[0].abs().amax(dim=-1, keepdim=True)).all())
+
+
+def test_one_workspace_for_layouts_of_different_size():
+    # initialised for the small layout only: what its launches leave behind its own counters must not meet the larger
+    # layout's, whose appends are counted there
+    small = build(1, 1, 4, 3000, [2990], 64, "bf16", seed=1)
+    large = build(20, 8, 32, 4000, [3990 - b for b in range(20)], 64, "bf16", seed=2)
+    shared = torch.randint(1, 255, (large["ws"].numel(),), dtype=torch.uint8, device="cuda")
+    sik.sik_workspace_init(small["lay"], 64, shared)
+    want = [step(s, 64, 2, True, s["q"]) for s in (small, large)]
+    small["ws"] = large["ws"] = shared
+    for _ in range(2):
+        for s, w in zip((small, large), want):
+            got = step(s, 64, 0, True, s["q"])
+            assert all(torch.equal(a, b) for a, b in zip(got[1:], w[1:]))
