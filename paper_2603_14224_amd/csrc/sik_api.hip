@@ -391,9 +391,9 @@ static int decode_step_impl(const sik_layout* layout, const void* q, const void*
                          &step_listcap);
     };
     if (one_launch && first_pass_16) step_T = plan(true, false);
-    if (one_launch && opt.launches <= 0 && opt.n == 0) {
+    if (one_launch && opt.launches <= 0) {
         step_T = plan(false, true);
-        if (step_T > 0 && !step_single_pays(d, step_chunk_k(step_T), kvq != nullptr, cus)) step_T = 0;
+        if (step_T > 0 && !step_single_pays(d, step_chunk_k(step_T), kvq != nullptr, opt.n > 0, cus)) step_T = 0;
     }
     // (records, several rounds of workgroups, the last one a quarter empty or more and a block's table entries too:
     // 24 x 8 x 16K with 5:1 95 us as two launches against 124)

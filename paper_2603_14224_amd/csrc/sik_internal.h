@@ -156,7 +156,7 @@ int step_max_chunks(const Dims& d);
 // single: plans with one chunk per head block only
 int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool kvq, bool forced, bool single, int* nchunk,
               size_t* dyn_lds, int* listcap);
-bool step_single_pays(const Dims& d, int kilo, bool kvq, int cus);
+bool step_single_pays(const Dims& d, int kilo, bool kvq, bool forced, int cus);
 int step_chunk_k(int code);
 int device_compute_units();
 hipError_t launch_sync_init(const Dims& d, const Workspace& w, hipStream_t s);

@@ -122,12 +122,21 @@ int step_chunk_k(int code) {
 //   records   1000: 8 blocks 17.6 -> 14.9      2000: 8 blocks 17.6 -> 17.7, 64 20.8 -> 17.7
 //             4096: 64 blocks 22.7 -> 24.6, 128 26.0 -> 24.6, 192 35.7 -> 24.7
 //             8192: 128 blocks 35.4 -> 37.3, 192 48.2 -> 37.4    12288: 128 blocks 47.0 -> 50.3, 160 68.9 -> 51.8
-bool step_single_pays(const Dims& d, int kilo, bool kvq, int cus) {
+//   64 forced tokens (chunks of 1, 4, 12, 16 and more x 1024, one workgroup per four heads)
+//   rows      1000: 8 blocks 18.4 -> 15.7      2000: 32 blocks 19.4 -> 19.1, 64 21.7 -> 19.1
+//             4096: 64 blocks 24.7 -> 24.6, 96 28.5 -> 25.2, 192 41 -> 31    8192: 128 blocks 41 -> 44, 160 55 -> 45
+//             16384: 160 blocks 85 -> 76; more than 256 blocks (384 of 5:1): slower at every context
+//   records   1000: 8 blocks 21.0 -> 19.3      2000: 32 blocks 21.6 -> 22.8, 64 24.5 -> 22.5
+//             4096: 64 blocks 26.6 -> 29.4, 96 30.6 -> 29.7, 192 40 -> 30    8192: 128 blocks 39.8 -> 43.5, 160 54 -> 44
+bool step_single_pays(const Dims& d, int kilo, bool kvq, bool forced, int cus) {
     const int blocks = d.units() * ((d.R + kHB - 1) / kHB);
     const bool full = d.R % kHB == 0 || d.R % kHB == 3;  // (nearly) all of a block's table entries in use
+    if (blocks > cus && forced) return false;
     if (blocks > cus) return kvq ? kilo == 1 || (full && kilo <= 4) : full || kilo >= 8;
     int least;  // in sixteenths of the compute units
-    if (kvq)
+    if (forced)
+        least = kilo == 1 ? 0 : (kilo > 4 ? 10 : (d.Lmax <= 2048 ? 4 : 6));
+    else if (kvq)
         least = kilo == 1 ? 0 : (kilo == 2 ? 2 : (kilo <= 4 ? 8 : 10));
     else
         least = kilo <= 2 ? 0 : (kilo == 8 ? 4 : (kilo == 6 || kilo > 16 ? 6 : 5));

@@ -32,7 +32,7 @@ def build(B, Hkv, Hq, capacity, lens, k, dtype, seed, q2=False):
     return s
 
 
-def step(s, k, launches, append, q, per_mille=0):
+def step(s, k, launches, append, q, per_mille=0, forced=None):
     lens, codes = s["lens"].clone(), s["codes"].clone()
     if "kvq" in s:
         kvq, K, V = s["kvq"].clone(), None, None
@@ -42,7 +42,7 @@ def step(s, k, launches, append, q, per_mille=0):
     out = torch.full((B, Hq, 128), np.nan, device="cuda")
     idx = torch.full((B, Hq, k), -7, dtype=torch.int32, device="cuda")
     sik.sik_decode_step_ex(s["lay"], q=q, k_new=s["new"][0] if append else None, v_new=s["new"][1] if append else None, K=K,
-                           V=V, kvq=kvq, alpha=s.get("alpha"), seq_len=lens, mu=s["mu"], codebook=s["cb"], codes=codes, k=k, k_per_mille=per_mille,
+                           V=V, kvq=kvq, alpha=s.get("alpha"), forced_idx=forced, seq_len=lens, mu=s["mu"], codebook=s["cb"], codes=codes, k=k, k_per_mille=per_mille,
                            out=out, idx_out=idx, workspace=s["ws"], launches=launches)
     torch.cuda.synchronize()
     assert sik.sik_workspace_status(s["ws"]) == 0
@@ -87,15 +87,20 @@ def test_head_pairs_budget_follows_the_context():
 
 
 # around the lines between the routes: contexts at and beyond the chunk sizes, few and many head blocks, several rounds
+@pytest.mark.parametrize("forced", [0, 32], ids=["plain", "forced"])
 @pytest.mark.parametrize("q2", [False, True], ids=["rows", "records"])
 @pytest.mark.parametrize("B,Hkv,Hq,L,k", [(1, 1, 4, 1024, 60), (1, 1, 4, 1025, 60), (3, 2, 6, 2048, 100), (3, 2, 6, 2049, 100),
                                           (10, 8, 32, 4096, 2000), (20, 8, 32, 4097, 170), (8, 8, 32, 8192, 333),
                                           (5, 8, 40, 12288, 500), (20, 4, 28, 20480, 700), (48, 8, 16, 1000, 33),
                                           (34, 8, 64, 1030, 50)])
-def test_route_taken_by_itself(B, Hkv, Hq, L, k, q2):
+def test_route_taken_by_itself(B, Hkv, Hq, L, k, q2, forced):
     lens = [max(0, L - 1 - (b * 131 if b % 2 else 0)) for b in range(B)]
     s = build(B, Hkv, Hq, L, lens, k, "bf16", seed=L + B, q2=q2)
-    want, got = step(s, k, 2, True, s["q"]), step(s, k, 0, True, s["q"])
+    # forced tokens anywhere in the longest sequence, some of them beyond the end of a shorter one
+    named = torch.randint(0, L, (B, Hkv, forced), device="cuda", dtype=torch.int32).sort(-1).values if forced else None
+    if forced:
+        named[..., 1:][named[..., 1:] == named[..., :-1]] = -1  # a token is named once
+    want, got = (step(s, k, launches, True, s["q"], forced=named) for launches in (2, 0))
     for a, b in zip(got[1:], want[1:]):
         assert torch.equal(a, b)
     assert bool(((got[0] - want[0]).abs() <= 2e-5 * want[0].abs().amax(dim=-1, keepdim=True)).all())
