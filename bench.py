@@ -29,8 +29,8 @@ HBM_PEAK_GBPS = 8000.0
 MEASURED_TRAFFIC = {
     ("C2", "select_attend_kernel"): (29488988, "profiles/decode_step_two_launches_C2_C3.md"),
     ("C3", "select_attend_kernel"): (58730732, "profiles/decode_step_two_launches_C2_C3.md"),
-    ("C4", "step_kernel"): (335015269, "profiles/decode_step_one_launch_C4_C5.md"),
-    ("C5", "step_kernel"): (277505678, "profiles/decode_step_one_launch_C4_C5.md"),
+    ("C4", "step_kernel"): (354539110, "profiles/decode_step_one_launch_C4_C5.md"),
+    ("C5", "step_kernel"): (241099674, "profiles/decode_step_one_launch_C4_C5.md"),
 }
 # execution times returned by sik_decode_step_profiled, in launch order: small launches run scoring, then fused
 # selection + attention; large ones run as one launch, reported in the last slot and named step_kernel here
