@@ -49,55 +49,49 @@ __device__ __forceinline__ uint4 load_row_slice(const uint4* p) {
 }
 
 // Attend over token indices supplied by fetch(j): this wavefront takes entries first + it * step +
-// (0 .. 4 U - 1), it = 0, 1, ... while below n (a workgroup of four wavefronts sharing one list uses first = 4 U * wave,
-// step = 16 U; a wavefront with a private list first = 0, step = 4 U), the rows of a step all in flight together.  Negative or out-of-range
+// (0..15), it = 0, 1, ... while below n (a workgroup sharing one list uses first = 16 * wave,
+// step = 64; a wavefront with a private list first = 0, step = 16).  Negative or out-of-range
 // entries are skipped.  qraw holds this lane's 8 query components in their 16-bit storage form; the
 // logit is (q . k) * scale_log2e + zbias with scale_log2e = softmax_scale * log2(e); zbias (one constant per
 // query) lets rows of an uncentred key share a softmax with logits taken against the centred key.
-template <int DT, bool STREAM = false, int U = 4, class Fetch>
+template <int DT, bool STREAM = false, class Fetch>
 __device__ __forceinline__ void attend_list(Fetch fetch, int n, int first, int step,
                                             const uint4* __restrict__ Kp, const uint4* __restrict__ Vp,
                                             const uint4 qraw, float scale_log2e, int Lmax, SoftmaxState& st,
                                             float zbias = 0.0f) {
-    static_assert(U % 4 == 0, "a lane fetches every sixteenth entry of a step");
     const int lane = threadIdx.x & 63;
     const int slot = lane >> 4, p = lane & 15;
     for (int base = first; base < n; base += step) {
-        int mine[U / 4];
+        const int jj = base + p;
+        const int mine = jj < n ? fetch(jj) : -1;
+        int id[4];
+        uint4 kv[4], vv[4];
 #pragma unroll
-        for (int y = 0; y < U / 4; ++y) {
-            const int jj = base + 16 * y + p;
-            mine[y] = jj < n ? fetch(jj) : -1;
-        }
-        int id[U];
-        uint4 kv[U], vv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            id[u] = __shfl(mine[u / 4], (lane & 48) + 4 * (u % 4) + slot, 64);
+        for (int u = 0; u < 4; ++u) {
+            id[u] = __shfl(mine, (lane & 48) + 4 * u + slot, 64);
             const bool ok = id[u] >= 0 && id[u] < Lmax;
             const size_t r = ok ? static_cast<size_t>(id[u]) : 0;
             id[u] = ok ? id[u] : -1;
             kv[u] = load_row_slice<STREAM>(&Kp[r * 16 + p]);
             vv[u] = load_row_slice<STREAM>(&Vp[r * 16 + p]);
         }
-        float z[U];
-        float mnew = st.m;
+        float z[4];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < 4; ++u) {
             float dot = dot2_acc<DT>(qraw.x, kv[u].x, 0.0f);
             dot = dot2_acc<DT>(qraw.y, kv[u].y, dot);
             dot = dot2_acc<DT>(qraw.z, kv[u].z, dot);
             dot = dot2_acc<DT>(qraw.w, kv[u].w, dot);
             dot = fmaf(row16_sum(dot), scale_log2e, zbias);
             z[u] = id[u] >= 0 ? dot : kNegBig;
-            mnew = fmaxf(mnew, z[u]);
         }
+        const float mnew = fmaxf(fmaxf(st.m, fmaxf(z[0], z[1])), fmaxf(z[2], z[3]));
         const float corr = fast_exp2(st.m - mnew);
         st.l *= corr;
 #pragma unroll
         for (int e = 0; e < 8; ++e) st.acc[e] *= corr;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < 4; ++u) {
             const float pu = id[u] >= 0 ? fast_exp2(z[u] - mnew) : 0.0f;
             float vf[8];
             widen8<DT>(vv[u], vf);
