@@ -97,6 +97,12 @@ __device__ __forceinline__ uint32_t group_suffix_sum(uint32_t v, uint32_t* lds4)
     return v;
 }
 
+// What stands among a head's scores in memory for a token that does not compete: a NaN of a pattern that no sum has (and
+// the lowest sort key there is).
+constexpr uint32_t kNoScoreBits = 0xffffffffu;
+__device__ __forceinline__ float no_score() { return __uint_as_float(kNoScoreBits); }
+__device__ __forceinline__ bool is_no_score(float v) { return __float_as_uint(v) == kNoScoreBits; }
+
 __device__ __forceinline__ float uniform(float x) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
@@ -699,7 +705,7 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
             gmask[s][0] &= __brev(livemask) >> (32 - TT);
         }
         // a band too crowded to rank: the exact scores of its members go to memory for the radix selection of the
-        // last phase, minus infinity for everything else
+        // last phase, no_score() for everything else
         if (any_crowded) {
             for (int it = 0; it < TT; ++it) {
                 const int tok = start + it * NT + tid;
@@ -709,7 +715,7 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
                     for (int s = 0; s < HB; ++s) {
                         if (crowded[s]) {
                             const bool member = ((gmask[s][0] & ~smask[s][0]) >> (TT - 1 - it)) & 1u;
-                            st_agent(&a.scores[(row0 + s) * a.sstride + tok], member ? exact_score(lut, code, s) : -INFINITY);
+                            st_agent(&a.scores[(row0 + s) * a.sstride + tok], member ? exact_score(lut, code, s) : no_score());
                         }
                     }
                 }
@@ -770,14 +776,17 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
             }
         }
         // a threshold bin too crowded to rank (e.g. all scores equal) sends the head's scores to memory for the radix
-        // selection of the last phase (a forced token's NaN goes out as minus infinity: it does not compete)
+        // selection of the last phase, whatever they are: the scores of a query that is not finite are not numbers, lie in
+        // bin 0 together and compete as they do in the two-launch step.  Forced tokens go out as no_score().
         if (any_crowded) {
             each_slot([&](auto slot, auto, const float (&v)[HB]) __attribute__((always_inline)) {
                 const int tok = start + slot * NT + tid;
+                const bool out =
+                    FORCED && n_forced > 0 && ((fbits[FORCED ? slot * (NT / 32) + (tid >> 5) : 0] >> (tid & 31)) & 1u);
 #pragma unroll
                 for (int s = 0; s < HB; ++s)
                     if (crowded[s] && tok < end)
-                        st_agent(&a.scores[(row0 + s) * a.sstride + tok], v[s] == v[s] ? v[s] : -INFINITY);
+                        st_agent(&a.scores[(row0 + s) * a.sstride + tok], out ? no_score() : v[s]);
             });
         }
     }
@@ -1161,13 +1170,13 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
             __syncthreads();
             if constexpr (FX)
                 radix_select_members<NT, true>(a.scores + (row0 + s) * a.sstride, L,
-                                                         [](float v) { return v > -INFINITY; }, need_s, dst, lhist,
+                                                         [](float v) { return !is_no_score(v); }, need_s, dst, lhist,
                                                          &lds4[0][0]);
             else
                 radix_select_members<NT, true>(
                     a.scores + (row0 + s) * a.sstride, L,
                     [lo = blo[s], sc_ = bscale[s], bst = sthr[s][0]](float v) {
-                        return v > -INFINITY && score_bin(v, lo, sc_) == bst;
+                        return !(FORCED && is_no_score(v)) && score_bin(v, lo, sc_) == bst;
                     },
                     need_s, dst, lhist, &lds4[0][0]);
             __threadfence_block();

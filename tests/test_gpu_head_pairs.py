@@ -119,3 +119,26 @@ def test_one_workspace_for_layouts_of_different_size():
         for s, w in zip((small, large), want):
             got = step(s, 64, 0, True, s["q"])
             assert all(torch.equal(a, b) for a, b in zip(got[1:], w[1:]))
+
+
+# every one-launch variant: one chunk of 2048, a pair's chunk of 16384, two chunks, records, the 16-bit first pass
+@pytest.mark.parametrize("forced", [0, 16], ids=["plain", "forced"])
+@pytest.mark.parametrize("B,Hkv,Hq,L,q2,launches", [(3, 2, 8, 2000, False, 1), (12, 8, 40, 15000, False, 1),
+                                                    (2, 8, 32, 30000, False, 1), (3, 2, 6, 3000, True, 1),
+                                                    (3, 2, 8, 4000, False, 3)])
+def test_query_that_is_not_finite(B, Hkv, Hq, L, q2, launches, forced):
+    # scores that are infinite or not numbers all lie in one bin, with more members than are ranked: the tokens taken are
+    # those of the two-launch step, and no slot of the index rows is left as it was
+    s = build(B, Hkv, Hq, L, [L] * B, L - 1, "bf16", seed=L, q2=q2)
+    named = (3 * torch.arange(forced, device="cuda", dtype=torch.int32)).repeat(B, Hkv, 1).contiguous() if forced else None
+    for h, x in enumerate((float("nan"), float("inf"), float("-inf"))):
+        s["q"][:, h, 7] = x
+    # (the two launches give a forced token the score -inf: at most its match among the scores, and above the negative NaNs
+    # of scores that overflow, so those two are compared without forced tokens only)
+    if not forced:
+        s["q"][:, 3] = 3e38
+    for k in (300,) if forced else (300, min(L - 1, 2500)):
+        want, got = (step(s, k, n, False, s["q"], forced=named) for n in (2, launches))
+        assert torch.equal(got[1], want[1]) and int(got[1].min()) >= -1
+        bad = 3 if forced else 4
+        assert torch.equal(got[0][:, :bad], want[0][:, :bad])  # no number comes out of these rows: zero either way
