@@ -403,9 +403,14 @@ static int decode_step_impl(const sik_layout* layout, const void* q, const void*
     if (step_T > 0) {
         const Append ap{static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new),
                         static_cast<uint16_t*>(K), static_cast<uint16_t*>(V), mu, codes, alpha, kvq};
+        if (k_new && step_sync_need(d) > kSyncReserve) {
+            timed(0);
+            e = done(0, launch_leave_clear(d, w, s));
+        }
         timed(3);
-        e = done(3, launch_step(d, w, step_T, step_nchunk, step_dyn, step_listcap, q, k_new ? ap : Append{}, codebook,
-                                codes, seq_len, K, V, kvq, alpha, k, opt, softmax_scale, idx_out, out, s));
+        if (e == hipSuccess)
+            e = done(3, launch_step(d, w, step_T, step_nchunk, step_dyn, step_listcap, q, k_new ? ap : Append{}, codebook,
+                                    codes, seq_len, K, V, kvq, alpha, k, opt, softmax_scale, idx_out, out, s));
     } else if (shared_unfused || !fused) {
         // prep (append + counters; skipped when nothing is appended: the scoring launch then clears the per-head
         // counters itself), scoring (on the summed query when the selection is shared), stand-alone selector (per

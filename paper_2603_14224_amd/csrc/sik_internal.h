@@ -150,8 +150,9 @@ hipError_t launch_fused(const Dims& d, const Workspace& w, const void* q, const 
                         int k, float scale, int32_t* idx_out, void* out, hipStream_t s);
 bool fused_plan(const Dims& d, int* nchunk, int* chunk);
 // one-launch decode step (sik_step.hip)
-constexpr size_t kSyncReserve = 65536;  // 256 KB: layouts of up to about 16000 query-head rows
-size_t step_sync_words(const Dims& d);
+constexpr size_t kSyncReserve = 65536;  // 256 KB: layouts of up to about 16000 query-head rows (beyond: launch_leave_clear)
+size_t step_sync_need(const Dims& d);   // words this layout's step uses
+size_t step_sync_words(const Dims& d);  // words kept in front of a workspace
 int step_max_chunks(const Dims& d);
 // single: plans with one chunk per head block only
 int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool kvq, bool forced, bool single, int* nchunk,
@@ -160,6 +161,8 @@ bool step_single_pays(const Dims& d, int kilo, bool kvq, bool forced, int cus);
 int step_chunk_k(int code);
 int device_compute_units();
 hipError_t launch_sync_init(const Dims& d, const Workspace& w, hipStream_t s);
+// zeroes the counters by which the last workgroup of a sequence to leave the step publishes the new length
+hipError_t launch_leave_clear(const Dims& d, const Workspace& w, hipStream_t s);
 hipError_t launch_step(const Dims& d, const Workspace& w, int T, int nchunk, size_t dyn_lds, int listcap, const void* q,
                        const Append& ap, const float* codebook, const uint8_t* codes, int32_t* seq_len,
                        const void* K, const void* V, const void* kvq, const float* alpha, int k, const StepOptions& fo,

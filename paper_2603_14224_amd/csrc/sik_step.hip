@@ -19,11 +19,17 @@ constexpr int kStepPair[][2] = {{16, 0}, {24, 0}, {24, 8}, {28, 8}, {32, 8}};
 constexpr int kStepQ2[][2] = {{1, 0}, {2, 0}, {4, 0}, {8, 0}, {12, 0}, {12, 4}, {14, 4}, {16, 4}};
 constexpr int kStepForced[][2] = {{1, 0}, {4, 0}, {12, 0}, {12, 4}, {14, 4}, {16, 4}};
 
+size_t step_sync_need(const Dims& d) {
+    return kSyncHeader + static_cast<size_t>(d.rows()) * kSyncPerRow + static_cast<size_t>(d.B) * kSyncPerSeq;
+}
+
 // At least kSyncReserve words whatever the layout: the words beyond a layout's own stay zero as well, so that a workspace
 // that serves several layouts in turn has zeros where the largest of them looks (without this, what a small layout's
 // scoring launch leaves behind its few counters would be taken for arrivals by a larger layout's one-launch step).
+// The counters of a layout that needs more lie where a smaller one keeps its histograms.  Such a layout has thousands of
+// head blocks, hence one chunk each, and uses the sequences' counters only, to publish appended rows: launch_leave_clear.
 size_t step_sync_words(const Dims& d) {
-    const size_t need = kSyncHeader + static_cast<size_t>(d.rows()) * kSyncPerRow + static_cast<size_t>(d.B) * kSyncPerSeq;
+    const size_t need = step_sync_need(d);
     return need < kSyncReserve ? kSyncReserve : need;
 }
 
@@ -165,6 +171,12 @@ hipError_t launch_sync_init(const Dims& d, const Workspace& w, hipStream_t s) {
     const size_t n = step_sync_words(d);
     return launch_kernel(fill_zero_kernel, static_cast<int>((n + 255) / 256 > 64 ? 64 : (n + 255) / 256), 256, s,
                          w.sync, n);
+}
+
+hipError_t launch_leave_clear(const Dims& d, const Workspace& w, hipStream_t s) {
+    const size_t n = static_cast<size_t>(d.B) * kSyncPerSeq;
+    return launch_kernel(fill_zero_kernel, static_cast<int>((n + 255) / 256 > 64 ? 64 : (n + 255) / 256), 256, s,
+                         w.sync + kSyncHeader + static_cast<size_t>(d.rows()) * kSyncPerRow, n);
 }
 
 hipError_t launch_step(const Dims& d, const Workspace& w, int T, int nchunk, size_t dyn, int listcap, const void* q,

@@ -121,6 +121,20 @@ def test_one_workspace_for_layouts_of_different_size():
             assert all(torch.equal(a, b) for a, b in zip(got[1:], w[1:]))
 
 
+def test_one_workspace_beyond_the_reserved_counters():
+    # 16640 query-head rows need more counters than every workspace keeps: the last of them lie where the small layout
+    # keeps its histograms
+    small = build(1, 8, 32, 4096, [4090], 8, "bf16", seed=1)
+    large = build(520, 8, 32, 64, [63 - b % 60 for b in range(520)], 8, "bf16", seed=2)
+    want = [step(s, 8, 2, True, s["q"]) for s in (small, large)]
+    sik.sik_workspace_init(large["lay"], 8, large["ws"])
+    small["ws"] = large["ws"]
+    for _ in range(2):
+        for s, w in zip((small, large), want):
+            got = step(s, 8, 0, True, s["q"])
+            assert all(torch.equal(a, b) for a, b in zip(got[1:], w[1:]))
+
+
 # every one-launch variant: one chunk of 2048, a pair's chunk of 16384, two chunks, records, the 16-bit first pass
 @pytest.mark.parametrize("forced", [0, 16], ids=["plain", "forced"])
 @pytest.mark.parametrize("B,Hkv,Hq,L,q2,launches", [(3, 2, 8, 2000, False, 1), (12, 8, 40, 15000, False, 1),
