@@ -180,10 +180,11 @@ int sik_decode_step(const sik_layout *layout, const void *q, const void *k_new, 
  * whose sik_workspace_bytes exceeds that returns SIK_ERR_STATIC_LIMIT and launches nothing (the benchmark
  * workloads of one sequence, 32K and 128K tokens, fit; large batches do not).  The call allocates nothing and
  * frees nothing.  Every call on one GPU shares that GPU's buffer, whatever the stream or thread: calls that
- * overlap in time on one GPU race; calls on one stream are ordered and safe.  The buffer keeps the previous
- * call's contents; the step clears what it needs cleared itself, and runs as sik_decode_step does where no workgroup
- * of it waits for another, else as separate scoring and selection + attention launches (so the buffer needs no
- * initialisation).  The first call on
+ * overlap in time on one GPU race, which spoils their own outputs and nothing later; calls on one stream are ordered
+ * and safe.  The buffer keeps the previous call's contents, the step clears what it needs cleared itself, no workgroup of
+ * it waits for another, and nothing needs initialising.  (With an appended row it always runs as separate scoring and
+ * selection + attention launches, without one as sik_decode_step does where that needs no wait: where
+ * sik_decode_step takes one launch and this call two, the rows differ by the order of fp32 sums.)  The first call on
  * a GPU looks the buffer's address up (hipGetSymbolAddress) and must therefore be made outside stream capture. */
 #define SIK_STATIC_SCRATCH_BYTES (32u << 20)
 int sik_decode_step_static(const sik_layout *layout, const void *q, const void *k_new, const void *v_new, void *K,

@@ -502,12 +502,13 @@ int sik_decode_step_static(const sik_layout* layout, const void* q, const void* 
     if (carve(d, k, nullptr).total_bytes > kStaticBytes) return SIK_ERR_STATIC_LIMIT;
     void* ws = static_scratch();
     if (ws == nullptr) return SIK_ERR_LAUNCH;
-    // One launch with a single chunk per head block where sik_decode_step takes that (the same bits), else two: nothing in
-    // either waits on another workgroup, so the shared buffer never needs an initialisation after a give-up; its
-    // synchronisation words are zero when the library is loaded, lie in the reserved part that nothing else is written
-    // to, and every step leaves them at zero.
+    // Nothing is assumed about what earlier calls left in the buffer, which nobody else can reach to initialise it.  Without
+    // an appended row: one launch with a single chunk per head block where sik_decode_step takes that (it uses none of the
+    // counters), else two.  With one: two launches, which clear their counters themselves (the one-launch step's would
+    // keep for the life of the process what calls that overlapped against the contract left there; clearing them in a
+    // launch of its own, 1 x 8 x 900 with 4:1 takes 15.3 us, as two launches 16.7, but 1 x 8 x 1900 17.4 and 16.4).
     StepOptions opt{};
-    opt.launches = kSingleOrTwo;
+    opt.launches = k_new ? 2 : kSingleOrTwo;
     return decode_step_impl(layout, q, k_new, v_new, K, V, nullptr, nullptr, seq_len, mu, codebook, codes, k,
                             softmax_scale, out, idx_out, ws, kStaticBytes, stream, nullptr, opt);
 }

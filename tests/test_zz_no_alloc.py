@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 import paper_2603_14224_amd as sik  # noqa: E402
 
 
-def both_ways(oracle, cfg, capacity, seq_len, append, step):
+def both_ways(oracle, cfg, capacity, seq_len, append, step, launches=0):
     """One decode step through each entry point from identical states; returns nothing, asserts equality."""
     res = []
     for static in (False, True):
@@ -28,6 +28,10 @@ def both_ways(oracle, cfg, capacity, seq_len, append, step):
         if static:
             sik.sik_decode_step_static(st.layout, dev(q, cfg.dtype), dkn, dvn, st.dK, st.dV, st.dsl, st.dmu, st.dcb,
                                        st.dcodes, k, 0.0, out, idx)
+        elif launches:
+            sik.sik_decode_step_ex(st.layout, q=dev(q, cfg.dtype), k_new=dkn, v_new=dvn, K=st.dK, V=st.dV, seq_len=st.dsl,
+                                   mu=st.dmu, codebook=st.dcb, codes=st.dcodes, k=k, out=out, idx_out=idx, workspace=st.ws,
+                                   launches=launches)
         else:
             sik.sik_decode_step(st.layout, dev(q, cfg.dtype), dkn, dvn, st.dK, st.dV, st.dsl, st.dmu, st.dcb,
                                 st.dcodes, k, 0.0, out, idx, st.ws)
@@ -46,6 +50,16 @@ def test_static_scratch_entry_point_matches_workspace_entry_point(oracle):
               [3000, 17, 1500], True, 1)
     # and a third, without append, selecting everything
     both_ways(oracle, cfg_small("C2", n_kv_heads=1, n_q_heads=4, context=900, top_k=1024), 1100, None, False, 2)
+
+
+def test_static_step_on_a_short_context_appends_in_two_launches(oracle):
+    # sik_decode_step takes one launch here, whose counters publish an appended row; the static entry uses no counters that
+    # outlive a call: with a row it takes two launches (the bits of two), without one the same one launch
+    cfg = cfg_small("C2", batch=3, n_kv_heads=2, n_q_heads=8, context=1000, top_k=64)
+    for step, append in enumerate((True, False, True, True)):
+        both_ways(oracle, cfg, 1024, [1000, 1, 1023], append, step, launches=2 if append else 0)
+    both_ways(oracle, cfg_small("C2", context=20000, top_k=600), 20008, None, True, 0)  # a larger one in between
+    both_ways(oracle, cfg, 1024, [1000, 1, 1023], True, 7, launches=2)
 
 
 def test_static_scratch_entry_point_rejects_what_does_not_fit():
