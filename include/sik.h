@@ -177,7 +177,8 @@ int sik_decode_step(const sik_layout *layout, const void *q, const void *k_new, 
  * capture that must not call hipMalloc, tight serving loops, harnesses that forbid allocation.  Same arguments
  * and results as sik_decode_step without the workspace pair: the scratch memory is a buffer of
  * SIK_STATIC_SCRATCH_BYTES built into the library (one copy per GPU, held until the process ends).  A layout / k
- * whose sik_workspace_bytes exceeds that returns SIK_ERR_STATIC_LIMIT and launches nothing (the benchmark
+ * whose sik_workspace_bytes exceeds that - without what is kept for counters beyond the layout's own, up to 256 KB -
+ * returns SIK_ERR_STATIC_LIMIT and launches nothing (the benchmark
  * workloads of one sequence, 32K and 128K tokens, fit; large batches do not).  The call allocates nothing and
  * frees nothing.  Every call on one GPU shares that GPU's buffer, whatever the stream or thread: calls that
  * overlap in time on one GPU race, which spoils their own outputs and nothing later; calls on one stream are ordered

@@ -12,7 +12,8 @@ thread_local LaunchEvents g_launch_events;
 
 // Scratch memory of sik_decode_step_static: one copy per GPU, part of the loaded code object.  On the host this
 // name is only a handle for hipGetSymbolAddress; the device address it yields (per device) is what kernels get.
-// (The reserved synchronisation words come on top of the stated size.)
+// (The reserved synchronisation words come on top of the stated size: every layout that fits that size with the words it
+// uses fits this one with those it does not.)
 constexpr size_t kStaticBytes = SIK_STATIC_SCRATCH_BYTES + kSyncReserve * 4;
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 constexpr int kMaxDevices = 64;
@@ -499,7 +500,9 @@ int sik_decode_step_static(const sik_layout* layout, const void* q, const void* 
     const int rc = check_layout(layout, &d);
     if (rc) return rc;
     if (k < 1 || k > d.Lmax) return SIK_ERR_K_RANGE;
-    if (carve(d, k, nullptr).total_bytes > kStaticBytes) return SIK_ERR_STATIC_LIMIT;
+    // (the counters that the layout does not use are reserved on top of the stated size)
+    const size_t unused = align256(step_sync_words(d) * 4) - align256(step_sync_need(d) * 4);
+    if (carve(d, k, nullptr).total_bytes - unused > SIK_STATIC_SCRATCH_BYTES) return SIK_ERR_STATIC_LIMIT;
     void* ws = static_scratch();
     if (ws == nullptr) return SIK_ERR_LAUNCH;
     // Nothing is assumed about what earlier calls left in the buffer, which nobody else can reach to initialise it.  Without

@@ -168,3 +168,24 @@ def test_chunk_plans_stay_inside_their_limits():
     assert sik.sik_workspace_bytes(too_long, 16) == 0
     assert sik.lib().sik_score(ctypes.byref(too_long), FAKE, FAKE, FAKE, FAKE, FAKE, None) == -2
     assert sik.lib().sik_topk(ctypes.byref(too_long), FAKE, FAKE, 16, FAKE, FAKE, 1 << 40, None) == -2
+
+
+@pytest.mark.parametrize("batch,max_len", [(1, 131136), (2, 40000)])
+def test_static_entry_limit_leaves_out_counters_that_the_layout_does_not_use(batch, max_len):
+    # every workspace keeps 65536 words for counters; of these the layout uses 8 + 4 per query-head row + 2 per sequence
+    lay = L(batch=batch, max_len=max_len)
+    own = -(-(8 + 4 * 32 * batch + 2 * batch) * 4 // 256) * 256
+
+    def needed(k):
+        return sik.sik_workspace_bytes(lay, k) - 65536 * 4 + own
+
+    lo, hi = 1, max_len  # the largest budget that fits, and the first that does not
+    assert needed(lo) <= sik.SIK_STATIC_SCRATCH_BYTES < needed(hi)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if needed(mid) <= sik.SIK_STATIC_SCRATCH_BYTES else (lo, mid)
+    for k, refused in ((lo - 1, False), (lo, False), (hi, True), (hi + 2048, True)):
+        # (q is missing: a layout that fits is refused for that, or for the absence of a GPU, before any launch)
+        rc = sik.lib().sik_decode_step_static(ctypes.byref(lay), None, None, None, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, k,
+                                              0.0, FAKE, None, None)
+        assert (rc == -9) == refused and rc != 0
