@@ -97,6 +97,8 @@ __device__ __forceinline__ uint32_t group_suffix_sum(uint32_t v, uint32_t* lds4)
     return v;
 }
 
+constexpr int kRankSole = 512;
+
 // What stands among a head's scores in memory for a token that does not compete: a NaN of a pattern that no sum has (and
 // the lowest sort key there is).
 constexpr uint32_t kNoScoreBits = 0xffffffffu;
@@ -229,6 +231,10 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
         }
     };
     const int nact = L > 0 ? (L + kChunk - 1) / kChunk : 1;
+    // Threshold-bin candidates that are ranked, by comparing each with every other.  A workgroup that finishes its heads alone
+    // does so for four heads on one compute unit, which with more than this (equal scores above all) the radix selection
+    // beats: 10 x 8 x 900 tokens of equal score 165 us, so 51, two launches 77; 500 tokens, ranked, 44 and 36.
+    const int rank_cap = nact == 1 ? kRankSole : kCandCap;
     if (c >= nact) {  // no token of this chunk is valid (chunk 0 always runs: it owns the outputs of L = 0)
         leave();
         return;
@@ -663,8 +669,8 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
         lo_f[s] = bst[s] <= 0 ? -3.4028235e38f : (bst[s] >= kBins ? INFINITY : static_cast<float>(bst[s]));
         hi_f[s] = uniform(hi_f[s]);
         lo_f[s] = uniform(lo_f[s]);
-        has_cand[s] = s < nh && bst[s] >= 0 && bst[s] < kBins && nbs[s] <= kCandCap;
-        crowded[s] = s < nh && bst[s] >= 0 && bst[s] < kBins && nbs[s] > kCandCap;
+        has_cand[s] = s < nh && bst[s] >= 0 && bst[s] < kBins && nbs[s] <= rank_cap;
+        crowded[s] = s < nh && bst[s] >= 0 && bst[s] < kBins && nbs[s] > rank_cap;
     }
     bool any_crowded = false;  // uniform
 #pragma unroll
@@ -858,7 +864,7 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
     // FX: the band's tokens get their binary32 scores, one thread per (head, token): the same sum, in the same
     // order, as the fp32 scan computes, so every path ranks by the same bits.  The code loads go out here and are
     // used after the lists have been written.
-    const bool rescore = FX && g < nh && sthr[g][0] >= 0 && sthr[g][0] < kBins && sthr[g][2] <= kCandCap;
+    const bool rescore = FX && g < nh && sthr[g][0] >= 0 && sthr[g][0] < kBins && sthr[g][2] <= rank_cap;
     const int nres = rescore ? static_cast<int>(min(s_ncand[g], static_cast<uint32_t>(kCandCap))) : 0;
     int rtok = -1;
     uint4 rcode = make_uint4(0u, 0u, 0u, 0u);
@@ -886,7 +892,7 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
         uint32_t n = nsel[0];
 #pragma unroll
         for (int s = 1; s < HB; ++s) n = tid == s ? nsel[s] : n;
-        if (sole && tid < nh && sthr[tid][0] >= 0 && sthr[tid][0] < kBins && sthr[tid][2] <= kCandCap)
+        if (sole && tid < nh && sthr[tid][0] >= 0 && sthr[tid][0] < kBins && sthr[tid][2] <= rank_cap)
             n += static_cast<uint32_t>(min(kk - min(sthr[tid][1], kk),
                                            static_cast<int>(min(s_ncand[tid], static_cast<uint32_t>(kCandCap)))));
         s_nsel[tid] = n;
@@ -925,20 +931,23 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
     SIK_TL(11);
     if (sole && g < nh) {
         const int bstar = sthr[g][0], need = kk - min(sthr[g][1], kk);
-        if (bstar >= 0 && bstar < kBins && need > 0 && sthr[g][2] <= kCandCap) {
+        if (bstar >= 0 && bstar < kBins && need > 0 && sthr[g][2] <= rank_cap) {
             const int ncand = static_cast<int>(min(s_ncand[g], static_cast<uint32_t>(kCandCap)));
             const uint64_t* const cg = cstage + g * kCandCap;
             const uint32_t sel = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 16 * (wv_u >> 2) + 15));
             for (int x0 = gt; x0 < ncand; x0 += kGroupThreads) {
                 const uint64_t me = cg[x0];
                 uint32_t rank = 0u;
-                for (int x = 0; x < ncand; x += 8) {  // (kCandCap is a multiple of 8: the reads stay inside cg)
+                int x = 0;
+                for (; x + 8 <= ncand; x += 8) {
                     uint64_t o8[8];
 #pragma unroll
                     for (int y = 0; y < 8; ++y) o8[y] = cg[x + y];
 #pragma unroll
-                    for (int y = 0; y < 8; ++y) rank += (x + y < ncand && o8[y] > me) ? 1u : 0u;
+                    for (int y = 0; y < 8; ++y) rank += o8[y] > me ? 1u : 0u;
                 }
+#pragma unroll 1
+                for (; x < ncand; ++x) rank += cg[x] > me ? 1u : 0u;
                 if (rank < static_cast<uint32_t>(need) && sel + rank < static_cast<uint32_t>(a.listcap))
                     lists[g * a.listcap + sel + rank] =
                         static_cast<uint16_t>(static_cast<int>(~static_cast<uint32_t>(me)) - start);
@@ -1026,7 +1035,7 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
     }
     __syncthreads();
     const int cgt_g = g < nh ? sthr[g][1] : 0, nb_g = g < nh ? sthr[g][2] : 0, bstar_g = g < nh ? sthr[g][0] : kBins;
-    const bool ranked_g = nb_g <= kCandCap;
+    const bool ranked_g = nb_g <= rank_cap;
     const int need_g = g < nh ? kk - min(cgt_g, kk) : 0;
     // index row of head g: the forced tokens first (written by chunk 0), then the selected ones, then the winners
     // among the candidates; orow starts behind the forced ones and has kfree slots
@@ -1162,7 +1171,7 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
     // the winners go to the head's index row in memory (there may be more of them than the LDS list holds)
     for (int s = 0; s < nh; ++s) {
         const int need_s = kk - min(sthr[s][1], kk);
-        const bool todo = (nact > 1 ? s_last[s] != 0 : true) && sthr[s][2] > kCandCap && sthr[s][0] >= 0 &&
+        const bool todo = (nact > 1 ? s_last[s] != 0 : true) && sthr[s][2] > rank_cap && sthr[s][0] >= 0 &&
                           sthr[s][0] < kBins && need_s > 0;
         if (todo) {  // uniform
             int32_t* dst = (a.idx_out ? a.idx_out : a.idx_ws) + (row0 + s) * a.k + nfv + sthr[s][1];
@@ -1190,7 +1199,11 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
         const uint4 qg = reinterpret_cast<const uint4*>(q + (row0 + g) * kD)[p];
         const int32_t* gl = (a.idx_out ? a.idx_out : a.idx_ws) + (row0 + g) * a.k + nfv + cgt_g;
         if constexpr (KVQ) {
-            const Q2Query qq = q2_prepare<DT>(qg, al8);
+            // (alpha again: kept through the selection above it would cost registers that the gather is short of)
+            const float4 b0 = reinterpret_cast<const float4*>(a.alpha + static_cast<size_t>(unit) * kD)[2 * p];
+            const float4 b1 = reinterpret_cast<const float4*>(a.alpha + static_cast<size_t>(unit) * kD)[2 * p + 1];
+            const float a8[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+            const Q2Query qq = q2_prepare<DT>(qg, a8);
             if (do_rank)
                 attend_list_q2([&](int j) { return chosen[j]; }, min(need_g, ncand), wl * 32, 128, Rp, qq,
                                a.scale_log2e, Lmax, st2);

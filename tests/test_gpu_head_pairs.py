@@ -135,6 +135,19 @@ def test_one_workspace_beyond_the_reserved_counters():
             assert all(torch.equal(a, b) for a, b in zip(got[1:], w[1:]))
 
 
+# lengths on both sides of the candidates that a workgroup of its own ranks (512) and that anything ranks (1024)
+@pytest.mark.parametrize("forced", [0, 8], ids=["plain", "forced"])
+@pytest.mark.parametrize("Hq,capacity,q2", [(8, 2048, False), (10, 2048, True), (6, 9000, False)])
+def test_equal_scores_around_the_ranking_limits(Hq, capacity, q2, forced):
+    lens = [n + d + forced for n in (512, 1024) for d in (-9, -1, 0, 1, 9)]
+    s = build(len(lens), 2, Hq, capacity, lens, 100, "bf16", seed=Hq, q2=q2)
+    named = (2 * torch.arange(forced, device="cuda", dtype=torch.int32)).repeat(len(lens), 2, 1).contiguous() if forced else None
+    q = torch.zeros_like(s["q"])
+    want, got, again = (step(s, 100, n, False, q, forced=named) for n in (2, 1, 1))
+    assert torch.equal(got[1], want[1]) and torch.equal(got[0], again[0])
+    assert bool(((got[0] - want[0]).abs() <= 2e-5 * want[0].abs().amax(dim=-1, keepdim=True)).all())
+
+
 # every one-launch variant: one chunk of 2048, a pair's chunk of 16384, two chunks, records, the 16-bit first pass
 @pytest.mark.parametrize("forced", [0, 16], ids=["plain", "forced"])
 @pytest.mark.parametrize("B,Hkv,Hq,L,q2,launches", [(3, 2, 8, 2000, False, 1), (12, 8, 40, 15000, False, 1),
