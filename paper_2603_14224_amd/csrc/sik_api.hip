@@ -396,11 +396,10 @@ static int decode_step_impl(const sik_layout* layout, const void* q, const void*
         step_T = plan(false, true);
         if (step_T > 0 && !step_single_pays(d, step_chunk_k(step_T), kvq != nullptr, opt.n > 0, cus)) step_T = 0;
     }
-    // (records, several rounds of workgroups, the last one a quarter empty or more and a block's table entries too:
-    // 24 x 8 x 16K with 5:1 95 us as two launches against 124)
-    const int blocks = d.units() * ((d.R + 3) / 4), rounds = (blocks + cus - 1) / (cus > 0 ? cus : 1);
-    const bool ill = kvq && blocks > cus && (d.R % 4 == 1 || d.R % 4 == 2) && 8 * blocks < 7 * rounds * cus;
-    if (one_launch && step_T == 0 && ((large && !ill && opt.launches == 0) || opt.launches > 0)) step_T = plan(false, false);
+    if (one_launch && step_T == 0 && (opt.launches > 0 || (large && opt.launches == 0))) {
+        step_T = plan(false, false);
+        if (opt.launches == 0 && step_nchunk == 1) step_T = 0;  // (a single chunk has been judged)
+    }
     if (step_T > 0) {
         const Append ap{static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new),
                         static_cast<uint16_t*>(K), static_cast<uint16_t*>(V), mu, codes, alpha, kvq};

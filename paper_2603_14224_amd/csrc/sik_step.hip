@@ -124,28 +124,54 @@ int step_chunk_k(int code) {
 //             6000: 80 blocks 22.9 -> 25.9, 96 32.3 -> 26.8      8192: 32 blocks 20.7 -> 23.7, 64 26.2 -> 24.5, 128 38 -> 31
 //             12288: 64 blocks 32.5 -> 33.2, 80 36.9 -> 31.6, 192 81 -> 54    16384: 64 blocks 39 -> 45, 80 41.5 -> 38.7
 //             20000: 80 blocks 50.6 -> 52.3, 96 72 -> 58
-//             more than 256 blocks: 384 of 5:1 4096 46 -> 49, 8192 65 -> 59; 512 of 8:1 2048 48 -> 38, 4096 69 -> 58
+//             8192, 2:1: 64 blocks 22.0 -> 23.7, 80 28.1 -> 23.8; 9:1: 72 blocks 29.5 -> 23.7
 //   records   1000: 8 blocks 17.6 -> 14.9      2000: 8 blocks 17.6 -> 17.7, 64 20.8 -> 17.7
 //             4096: 64 blocks 22.7 -> 24.6, 128 26.0 -> 24.6, 192 35.7 -> 24.7
 //             8192: 128 blocks 35.4 -> 37.3, 192 48.2 -> 37.4    12288: 128 blocks 47.0 -> 50.3, 160 68.9 -> 51.8
 //   64 forced tokens (chunks of 1, 4, 12, 16 and more x 1024, one workgroup per four heads)
 //   rows      1000: 8 blocks 18.4 -> 15.7      2000: 32 blocks 19.4 -> 19.1, 64 21.7 -> 19.1
 //             4096: 64 blocks 24.7 -> 24.6, 96 28.5 -> 25.2, 192 41 -> 31    8192: 128 blocks 41 -> 44, 160 55 -> 45
-//             16384: 160 blocks 85 -> 76; more than 256 blocks (384 of 5:1): slower at every context
+//             16384: 160 blocks 85 -> 76
 //   records   1000: 8 blocks 21.0 -> 19.3      2000: 32 blocks 21.6 -> 22.8, 64 24.5 -> 22.5
 //             4096: 64 blocks 26.6 -> 29.4, 96 30.6 -> 29.7, 192 40 -> 30    8192: 128 blocks 39.8 -> 43.5, 160 54 -> 44
+//             4096, 5:1: 96 blocks 26.1 -> 28.1, 128 27.5 -> 28.2; 6:1: 128 29.1 -> 28.1
+// With more blocks than compute units, and with long chunks of the variants of four heads, what counts is how much of
+// what either form computes is padding: the one launch goes in rounds, four heads to a block (three take nearly as long
+// as four, two three quarters), the two launches in chunks of a power of two, the last one padded beyond 8192 tokens.
+// `room` is the ratio of the two, head x tokens that the rounds have room for over those that the chunks have; pairs of
+// heads (rows, chunks from 8192) won everywhere.  Measured at 700 shapes of 257 to 1100 blocks and 2:1 to 13:1, by room:
+//   rows      2000: 1.40 39.7 -> 33.6, 1.57 32.3 -> 33.2, 1.9 31.1 -> 32.7    4096: 1.31 60 -> 53, 1.60 50.6 -> 52.0, 3.0 39 -> 44
+//             6000: 1.77 69 -> 63, 1.87 86 -> 93    forced: 8192: 1.77 93 -> 86, 2.7 69 -> 83    20000: 1.3 203 -> 177, 1.9 141 -> 166
+//   records   2000: 1.9 38.3 -> 33.2, 2.05 32.5 -> 33.6    4096: 1.6 57 -> 48, 2.05 45.0 -> 47.6    8192: 1.6 65.8 -> 61, 1.9 62 -> 72
+//             9500: 0.92 102 -> 82    12288, 2:1: 1.39 87 -> 76; 4:1: 1.45 93 -> 99    16384: 1.33 132 -> 127, 1.6 122 -> 128, 1.9 104 -> 126
+//   up to 256 blocks, four heads, chunks of 16384: 1.8 83.9 -> 73 (rows, forced), 66 -> 63 (records), 2.0 58.1 -> 56.4, 2.4 55.9 -> 62.9;
+//             of 18432 and 20480: 1.45 78 -> 75, 1.73 63.7 -> 69
 bool step_single_pays(const Dims& d, int kilo, bool kvq, bool forced, int cus) {
     const int blocks = d.units() * ((d.R + kHB - 1) / kHB);
     const bool full = d.R % kHB == 0 || d.R % kHB == 3;  // (nearly) all of a block's table entries in use
-    if (blocks > cus && forced) return false;
-    if (blocks > cus) return kvq ? kilo == 1 || (full && kilo <= 4) : full || kilo >= 8;
+    const bool pairs = kilo >= 8 && !kvq && !forced;
+    const int rounds = (blocks + cus - 1) / cus;
+    int chunks = 1, chunk = d.Lmax;
+    if (d.Lmax > 8192) fused_plan(d, &chunks, &chunk);
+    const double room = static_cast<double>(rounds) * cus * kHB * (d.R == 2 ? 0.75 : 1.0) / static_cast<double>(d.rows()) *
+                        d.Lmax / (static_cast<double>(chunks) * chunk);
+    if (blocks > cus) {
+        if (pairs) return true;
+        if (kvq) return room <= (kilo <= 2 ? 2.0 : (kilo <= 4 ? (forced ? 1.78 : 1.85) : (kilo <= 8 ? 1.72 : (kilo <= 12 ? 1.42 : 1.38))));
+        return room <= (kilo <= 4 ? 1.595 : 1.8);
+    }
+    if (kilo > 12 && !pairs) return 2 * blocks > cus && (d.R < kHB || room <= (kilo == 16 ? 2.05 : 1.7));
+    if (forced && kvq && kilo == 4 && d.R > kHB && !full && d.Lmax > 3072 && 3 * d.rows() < 4 * cus) return false;
+    // (one pair to a KV head, half of the compute units at most: two chunks each, where the launch is large enough for that,
+    // 16 x 8 x 19544 with 1563 selected 73 -> 64 us)
+    if (pairs && kilo > 16 && d.R == kHBPair && 2 * blocks <= cus) return false;
     int least;  // in sixteenths of the compute units
     if (forced)
         least = kilo == 1 ? 0 : (kilo > 4 ? 10 : (d.Lmax <= 2048 ? 4 : 6));
     else if (kvq)
         least = kilo == 1 ? 0 : (kilo == 2 ? 2 : (kilo <= 4 ? 8 : 10));
     else
-        least = kilo <= 2 ? 0 : (kilo == 8 ? 4 : (kilo == 6 || kilo > 16 ? 6 : 5));
+        least = kilo <= 2 ? 0 : (kilo == 8 ? (8 * d.rows() < 5 * cus ? 5 : 4) : (kilo == 6 || kilo > 16 ? 6 : 5));
     return 16 * blocks >= least * cus;
 }
 

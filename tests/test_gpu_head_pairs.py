@@ -106,6 +106,34 @@ def test_route_taken_by_itself(B, Hkv, Hq, L, k, q2, forced):
     assert bool(((got[0] - want[0]).abs() <= 2e-5 * want[0].abs().amax(dim=-1, keepdim=True)).all())
 
 
+# (batch, KV heads, query heads, capacity, records, forced tokens, one launch?), both sides of the lines of step_single_pays
+ROUTES = [(1, 1, 4, 1024, False, 0, True), (1, 1, 4, 2049, False, 0, False), (8, 8, 16, 8192, False, 0, False),
+          (10, 8, 16, 8192, False, 0, True), (9, 4, 36, 8192, False, 0, True), (33, 8, 32, 2000, False, 0, False),
+          (46, 8, 32, 2000, False, 0, True), (41, 8, 40, 4096, False, 0, False),
+          (16, 8, 16, 20000, False, 0, True), (12, 8, 16, 20000, False, 0, False), (27, 8, 40, 10922, True, 0, True),
+          (52, 8, 16, 9500, True, 0, True), (24, 8, 40, 16384, True, 0, False), (17, 8, 40, 8192, True, 0, False),
+          (18, 8, 32, 16384, True, 0, True), (9, 8, 40, 16384, True, 0, False), (6, 8, 40, 4096, True, 64, False),
+          (6, 8, 40, 3000, True, 64, True), (17, 8, 40, 16384, False, 64, False), (32, 8, 64, 8192, False, 64, True),
+          (24, 8, 40, 8192, False, 64, False)]
+
+
+@pytest.mark.parametrize("B,Hkv,Hq,capacity,q2,forced,one", ROUTES)
+def test_launches_taken_by_itself(B, Hkv, Hq, capacity, q2, forced, one):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the lines are drawn for 256 compute units")
+    lay = sik.make_layout(B, Hkv, Hq, 128, capacity, torch.bfloat16, torch.float32)
+    k = 32 + forced
+    rows = dict(K=None, V=None, kvq=sik.alloc_kvq(lay), alpha=torch.ones(B, Hkv, 128, device="cuda")) if q2 else \
+        {n: torch.zeros(B, Hkv, capacity, 128, device="cuda", dtype=torch.bfloat16) for n in "KV"}
+    us = sik.sik_decode_step_ex(
+        lay, q=torch.zeros(B, Hq, 128, device="cuda", dtype=torch.bfloat16), **rows, mu=torch.zeros(B, Hkv, 128, device="cuda"),
+        seq_len=torch.full((B,), 200, dtype=torch.int32, device="cuda"), codebook=torch.zeros(B, Hkv, 32, 16, 4, device="cuda"),
+        codes=torch.zeros(B, Hkv, capacity, 16, dtype=torch.uint8, device="cuda"), k=k,
+        forced_idx=torch.arange(forced, dtype=torch.int32, device="cuda").repeat(B, Hkv, 1) if forced else None,
+        out=torch.empty(B, Hq, 128, device="cuda"), workspace=sik.alloc_workspace(lay, k), profiled=True)
+    assert (us[1] == 0.0) == one and us[3] > 0.0
+
+
 def test_one_workspace_for_layouts_of_different_size():
     # initialised for the small layout only: what its launches leave behind its own counters must not meet the larger
     # layout's, whose appends are counted there
