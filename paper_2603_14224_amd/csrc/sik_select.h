@@ -168,10 +168,27 @@ __device__ inline void radix_select_members(const float* __restrict__ s, int L, 
                 atomicAdd(&h256[(key >> (8 * pass)) & 255u], 1u);
         }
         __syncthreads();
-        if (tid < kWave) {
-            // the digit at which the count from the top reaches `remaining`: four digits to a lane, a suffix sum over the
-            // lanes (one thread walking down the 256 counts, a dependent LDS read each, took most of the selection: equal
-            // scores, 1 x 8 x 1900 tokens in two launches 77 -> 31 us, 10 x 8 x 2000 in one 259 -> 74)
+        // The digit at which the count from the top reaches `remaining`.  Larger workgroups, which take several heads or all
+        // of the selection on themselves: four digits to a lane of the first wavefront, a suffix sum over the lanes (equal
+        // scores, 10 x 8 x 2000 in one launch 259 -> 74 us).  The 256 threads that select and attend one head: one thread
+        // walking down the counts, a dependent LDS read each; their kernel runs on every step of one sequence and is 0.2 us
+        // slower with the other form in it though it is not taken (8 layers of 1 x 8 x 32K 195.3 -> 196.8 us).
+        if constexpr (NT == kBlock) {
+            if (tid == 0) {
+                uint32_t cum = 0;
+                int dsel = 0;
+                for (int dgt = 255; dgt >= 0; --dgt) {
+                    const uint32_t cnt = h256[dgt];
+                    if (cum < remaining && remaining <= cum + cnt) {
+                        dsel = dgt;
+                        break;
+                    }
+                    cum += cnt;
+                }
+                sh[0] = static_cast<uint32_t>(dsel);
+                sh[1] = remaining - cum;
+            }
+        } else if (tid < kWave) {
             uint32_t own = 0u;
 #pragma unroll
             for (int e = 0; e < 4; ++e) own += h256[4 * tid + e];
