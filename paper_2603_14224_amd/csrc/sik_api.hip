@@ -142,11 +142,11 @@ int sik_plan_info(const sik_layout* layout, int32_t* info) {
     info[3] = nchunk, info[4] = chunk;
     const bool fused = fused_plan(d, &nchunk, &chunk);
     info[5] = fused ? nchunk : 0, info[6] = chunk;
-    // one-launch decode step: tokens per thread (chunk = 1024 x that) on the current device, 0 = not taken
+    // one-launch decode step: tokens of a chunk in units of 1024 on the current device, 0 = no plan fits
     size_t dyn;
     int listcap, snc;
-    const int tt = step_plan(d, 1, false, device_compute_units(), false, false, false, false, &snc, &dyn, &listcap);
-    info[7] = step_chunk_k(tt);
+    const int code = step_plan(d, 1, false, device_compute_units(), false, false, false, false, &snc, &dyn, &listcap);
+    info[7] = step_chunk_k(code);
     return SIK_OK;
 }
 
@@ -380,9 +380,9 @@ static int decode_step_impl(const sik_layout* layout, const void* q, const void*
     int step_nchunk = 0, step_listcap = 0;
     // By default where a single chunk per head block pays (step_single_pays), and for large launches: with one sequence
     // the histogram exchange between the many chunks of a head and the heavier barriers of 1024-thread workgroups cost
-    // more than the launch boundary they save.  (Two or three chunks per head block would already pay on 16-bit rows
-    // from about a million keys, 10 x 8 x 16K with 4:1 52 -> 47 us, but such workgroups wait for each other: steps on two
-    // streams, each of which now runs, could keep each other's from starting.)
+    // more than the launch boundary they save; several chunks wait for each other.  (Two or three would already pay on rows
+    // from about a million keys, 10 x 8 x 16K with 4:1 52 -> 47 us, but there steps on two streams, each of which now
+    // runs, could keep each other's workgroups from starting.)
     const bool large = static_cast<int64_t>(d.units()) * ((d.R + 3) / 4) * d.Lmax > (2 << 20);
     const bool one_launch = !opt.group_shared && opt.launches != 2;
     const bool first_pass_16 = opt.launches == 3 && !kvq && opt.n == 0;

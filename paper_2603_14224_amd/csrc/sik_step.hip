@@ -10,7 +10,7 @@ namespace sik {
 
 // ---- host side ---------------------------------------------------------------------------------------------------
 // instantiated (tokens per thread with scores in registers, further tokens with scores in LDS); chunk = 1024 x sum
-constexpr int kStepT[][2] = {{1, 0}, {2, 0}, {3, 0}, {4, 0}, {6, 0}, {8, 0}, {12, 0}, {12, 4}, {14, 4}, {16, 4}};
+constexpr int kStepT[][2] = {{1, 0}, {2, 0}, {3, 0}, {4, 0}, {6, 0}};
 // instantiated tokens per thread of the variant with the 16-bit first pass (two registers per token)
 constexpr int kStepFx[] = {4, 8, 12, 16, 20};
 // the same for the variant with two heads to a workgroup of 512 threads; chunk = 512 x sum
@@ -33,7 +33,8 @@ size_t step_sync_words(const Dims& d) {
     return need < kSyncReserve ? kSyncReserve : need;
 }
 
-// Upper bound of the chunks per head block any one-launch plan of this layout uses (sizes the histogram area).
+// Upper bound of the chunks per head block any one-launch plan of this layout uses (sizes the histogram area; of pairs a
+// few more would be resident in places).
 int step_max_chunks(const Dims& d) {
     const int hbs = d.units() * ((d.R + kHB - 1) / kHB);
     const int byc = 320 / hbs;  // no part of this family has more compute units
@@ -50,9 +51,10 @@ static size_t step_dyn_bytes(int heads, int chunk, int TL, int k, int* listcap) 
     return lists > tail ? lists : tail;
 }
 
-// Tokens per thread of the one-launch step for this layout, or 0 when it does not apply: the smallest T whose
-// grid fits the compute units (workgroups of a head block wait for each other, so they must all be resident);
-// a single chunk per head block needs no wait and may exceed them.
+// The variant of the one-launch step for this layout, as a code (kStepPairCode or kStepFxCode, plus T * 100 + TL: tokens
+// per thread with their scores in registers and in LDS), or 0 when none applies: the smallest chunk whose grid fits the
+// device (workgroups of a head block wait for each other, so they must all be resident: one of four heads to a compute
+// unit, two of two heads); a single chunk per head block needs no wait and may exceed it.
 //
 // Chunks of 8192 tokens and more on 16-bit rows go to the variant with two heads to a workgroup, two workgroups to a
 // compute unit: the scan is bound by LDS reads and vector instructions, the gather by HBM, and with one workgroup on
@@ -63,7 +65,10 @@ static size_t step_dyn_bytes(int heads, int chunk, int TL, int k, int* listcap) 
 // 78.5 -> 62.8; 16 x 8 x 16K with 5:1 71.2 -> 61.7, 7:1 79.8 -> 72.6, 8:1 84.9 -> 77.1; 16 x 8 x 20K with 8:1 115 -> 106;
 // 8 x 8 x 40K with 6:1 92.9 -> 86.6; 4 x 8 x 128K with 4:1 93.3 -> 90.7; 64 x 4 x 16K with 2:1 57.9 -> 53.7; none slower.
 // On 2-bit records the gather is bound by vector instructions too and there is little to overlap: 32 x 8 x 16K 60.7 us with
-// four heads, 64.2 with two.  Budgets whose lists do not fit the smaller LDS share (about 4000) keep four heads.
+// four heads, 64.2 with two.
+// Where a grid of pairs is resident and one of four heads is not (5:1, 6:1, 9:1, one pair to a KV head), two launches against
+// two chunks of pairs: 10 x 8 x 24000 with 5:1 83 -> 64, 9 x 8 x 36800 109 -> 86, 20 x 8 x 36000 with 2:1 101 -> 83, 12 x 4 x
+// 30000 with 9:1 104 -> 80, lengths falling to a quarter 127 -> 86, one long 129 -> 62.
 int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool kvq, bool forced, bool single, int* nchunk_out, size_t* dyn_out,
               int* listcap_out) {
     if (d.R < 2 || d.R > 255 || cus < 1) return 0;
@@ -98,12 +103,15 @@ int step_plan(const Dims& d, int k, bool appended, int cus, bool fx, bool kvq, b
             if (fits(kHB, tt[0] + tt[1], tt[1])) return tt[0] * 100 + tt[1];
         return 0;
     }
-    for (const auto& tt : kStepT) {
-        if (!fits(kHB, tt[0] + tt[1], tt[1])) continue;
-        if (tt[0] + tt[1] >= 8)
-            for (const auto& pp : kStepPair)
-                if (fits(kHBPair, pp[0] + pp[1], pp[1])) return kStepPairCode + pp[0] * 100 + pp[1];
-        return tt[0] * 100 + tt[1];  // both numbers in one: T * 100 + TL
+    for (const auto& tt : kStepT)
+        if (fits(kHB, tt[0] + tt[1], tt[1])) return tt[0] * 100 + tt[1];  // both numbers in one: T * 100 + TL
+    for (const auto& pp : kStepPair) {
+        if (!fits(kHBPair, pp[0] + pp[1], pp[1])) continue;
+        // (larger budgets in chunks beyond 12288 tokens gain 10 to 15 % with equal lengths and lose as much or more with
+        // unequal ones: 4 x 8 x 64K with 8:1, 3500 selected, 131 -> 111 us and, falling to a quarter, 164 -> 180;
+        // 10 x 8 x 16K 129 -> 116 and, one long, 73 -> 95)
+        if (pp[1] > 0 && k > 3072) return 0;
+        return kStepPairCode + pp[0] * 100 + pp[1];
     }
     return 0;
 }

@@ -24,8 +24,6 @@
 // the host only takes this path when the grid fits the compute units (HB = 2: twice their number).  An appended row needs no wait: its new
 // length is published by the last workgroup of the sequence to leave.  Every counter the kernel uses is left at
 // zero by its last user, so the workspace's sync words need zeroing only once (sik_workspace_init).
-#include <atomic>
-#include <climits>
 // (This header holds the kernel and its launch switch; sik_step_bf16.hip and sik_step_f16.hip instantiate it.  The
 // including file defines SIK_STEP_TL_SETTER, the name of its export for the debug timeline.)
 #pragma once
@@ -81,7 +79,7 @@ __device__ __forceinline__ bool bounded_wait(const uint32_t* word, uint32_t targ
 }
 
 // Exclusive prefix sum over the 256 threads of a group (thread t gets the sum over u > t: a SUFFIX sum, as the
-// threshold search counts from the top bin down).  Called by all 1024 threads; lds4: this group's four words.
+// threshold search counts from the top bin down).  Called by all threads of the workgroup; lds4: this group's four words.
 __device__ __forceinline__ uint32_t group_suffix_sum(uint32_t v, uint32_t* lds4) {
     const int lane = threadIdx.x & 63, wl = (threadIdx.x >> 6) & 3;
 #pragma unroll
@@ -468,102 +466,104 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
         }
     } else {
 #pragma unroll
-    for (int it = 0; it < TT; ++it) {
-        if (start + it * NT >= end) {  // uniform: no token in this slot, nor in those after it
+        for (int it = 0; it < TT; ++it) {
+            if (start + it * NT >= end) {  // uniform: no token in this slot, nor in those after it
 #pragma unroll
-            for (int s = 0; s < HB; ++s)
-                if (it < T) sc[it < T ? it : 0][s] = __builtin_nanf("");
-            if (it >= T) lsc[(it - T) * NT + tid] = make_entry({__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")});
-            if constexpr (FX) fx[it][0] = fx[it][1] = 0u;
-            continue;
-        }
-        const int tok = start + it * NT + tid;
-        uint4 code = cur[it & 1];
-        if (it + 2 < TT) {
-            const int i = tok + 2 * NT;
-            cur[it & 1] = i < end ? cp[i] : make_uint4(0u, 0u, 0u, 0u);
-        }
-        if (tok == t_new) code = *reinterpret_cast<const uint4*>(newcode);
-        // (token slot it of thread tid is token it * NT + tid of the chunk)
-        const bool live =
-            tok < end && !(n_forced > 0 && ((fbits[FORCED ? it * (NT / 32) + (tid >> 5) : 0] >> (tid & 31)) & 1u));
-        if constexpr (FX) {
-            // 8-byte entries, two packed 16-bit adds per lookup: half the adds and half the LDS bytes of the
-            // fp32 scan; the sums only place the token in a bin (exact scores follow for the band, below)
-            typedef unsigned short us2 __attribute__((ext_vector_type(2)));
-            us2 a01 = {0, 0}, a23 = {0, 0};
+                for (int s = 0; s < HB; ++s)
+                    if (it < T) sc[it < T ? it : 0][s] = __builtin_nanf("");
+                if (it >= T)
+                    lsc[(it - T) * NT + tid] =
+                        make_entry({__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")});
+                if constexpr (FX) fx[it][0] = fx[it][1] = 0u;
+                continue;
+            }
+            const int tok = start + it * NT + tid;
+            uint4 code = cur[it & 1];
+            if (it + 2 < TT) {
+                const int i = tok + 2 * NT;
+                cur[it & 1] = i < end ? cp[i] : make_uint4(0u, 0u, 0u, 0u);
+            }
+            if (tok == t_new) code = *reinterpret_cast<const uint4*>(newcode);
+            // (token slot it of thread tid is token it * NT + tid of the chunk)
+            const bool live =
+                tok < end && !(n_forced > 0 && ((fbits[FORCED ? it * (NT / 32) + (tid >> 5) : 0] >> (tid & 31)) & 1u));
+            if constexpr (FX) {
+                // 8-byte entries, two packed 16-bit adds per lookup: half the adds and half the LDS bytes of the
+                // fp32 scan; the sums only place the token in a bin (exact scores follow for the band, below)
+                typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+                us2 a01 = {0, 0}, a23 = {0, 0};
 #pragma unroll
-            for (int dw = 0; dw < 4; ++dw) {
-                const uint32_t word = dw == 0 ? code.x : (dw == 1 ? code.y : (dw == 2 ? code.z : code.w));
-                uint2 v[8];
-                lookup_batch_x(word, dw, lutx, v);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int dw = 0; dw < 4; ++dw) {
+                    const uint32_t word = dw == 0 ? code.x : (dw == 1 ? code.y : (dw == 2 ? code.z : code.w));
+                    uint2 v[8];
+                    lookup_batch_x(word, dw, lutx, v);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int n = 0; n < 8; ++n) {
-                    a01 += __builtin_bit_cast(us2, v[n].x);
-                    a23 += __builtin_bit_cast(us2, v[n].y);
+                    for (int n = 0; n < 8; ++n) {
+                        a01 += __builtin_bit_cast(us2, v[n].x);
+                        a23 += __builtin_bit_cast(us2, v[n].y);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            const uint32_t w01 = __builtin_bit_cast(uint32_t, a01), w23 = __builtin_bit_cast(uint32_t, a23);
-            fx[it][0] = w01;
-            fx[it][1] = w23;
-            livemask |= (live ? 1u : 0u) << it;
-            if (live) {
+                const uint32_t w01 = __builtin_bit_cast(uint32_t, a01), w23 = __builtin_bit_cast(uint32_t, a23);
+                fx[it][0] = w01;
+                fx[it][1] = w23;
+                livemask |= (live ? 1u : 0u) << it;
+                if (live) {
 #pragma unroll
-                for (int s = 0; s < HB; ++s) {
-                    const uint32_t w = s < 2 ? w01 : w23;
-                    const int f6 = static_cast<int>(((s & 1) ? w >> 16 : w & 0xffffu) >> shx[s]);
-                    if (s < nh) atomicAdd(&lhist[s * kBins + min(max(f6 - base6[s], 0), kBins - 1)], 1u);
+                    for (int s = 0; s < HB; ++s) {
+                        const uint32_t w = s < 2 ? w01 : w23;
+                        const int f6 = static_cast<int>(((s & 1) ? w >> 16 : w & 0xffffu) >> shx[s]);
+                        if (s < nh) atomicAdd(&lhist[s * kBins + min(max(f6 - base6[s], 0), kBins - 1)], 1u);
+                    }
+                }
+                continue;
+            }
+            float acc[HB];
+            if constexpr (TT < 6) {
+                // the lookups run one 8-group batch ahead of the adds (8 to 16 LDS reads in flight per wavefront)
+                Entry v[2][8];
+                lookup_batch<HB>(code.x, 0, lut, v[0]);
+#pragma unroll
+                for (int dw = 0; dw < 4; ++dw) {
+                    if (dw < 3)
+                        lookup_batch<HB>(dw == 0 ? code.y : (dw == 1 ? code.z : code.w), dw + 1, lut, v[(dw + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    add_batch<HB>(dw == 0, v[dw & 1], acc);
+#pragma unroll
+                    for (int s = 0; s < HB; ++s) asm volatile("" : "+v"(acc[s]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                // many tokens per thread: their scores take half the registers, so half a batch at a time (the 16
+                // wavefronts of the workgroup hide the LDS latency between them)
+                Entry v[4];
+#pragma unroll
+                for (int dw = 0; dw < 4; ++dw) {
+                    const uint32_t word = dw == 0 ? code.x : (dw == 1 ? code.y : (dw == 2 ? code.z : code.w));
+                    lookup_half<0>(word, dw, lut, v);
+                    __builtin_amdgcn_sched_barrier(0);
+                    add_half(dw == 0, v, acc);
+#pragma unroll
+                    for (int s = 0; s < HB; ++s) asm volatile("" : "+v"(acc[s]));
+                    __builtin_amdgcn_sched_barrier(0);
+                    lookup_half<1>(word, dw, lut, v);
+                    __builtin_amdgcn_sched_barrier(0);
+                    add_half(false, v, acc);
+#pragma unroll
+                    for (int s = 0; s < HB; ++s) asm volatile("" : "+v"(acc[s]));
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            continue;
-        }
-        float acc[HB];
-        if constexpr (TT < 6) {
-            // the lookups run one 8-group batch ahead of the adds (8 to 16 LDS reads in flight per wavefront)
-            Entry v[2][8];
-            lookup_batch<HB>(code.x, 0, lut, v[0]);
 #pragma unroll
-            for (int dw = 0; dw < 4; ++dw) {
-                if (dw < 3)
-                    lookup_batch<HB>(dw == 0 ? code.y : (dw == 1 ? code.z : code.w), dw + 1, lut, v[(dw + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-                add_batch<HB>(dw == 0, v[dw & 1], acc);
-#pragma unroll
-                for (int s = 0; s < HB; ++s) asm volatile("" : "+v"(acc[s]));
-                __builtin_amdgcn_sched_barrier(0);
+            for (int s = 0; s < HB; ++s) {
+                if (live && s < nh)
+                    atomicAdd(&lhist[s * kBins + bin_of_coord(bin_coord_shifted(acc[s], bscale[s], bshift[s]))], 1u);
+                acc[s] = live ? acc[s] : __builtin_nanf("");
+                if (it < T) sc[it < T ? it : 0][s] = acc[s];
             }
-        } else {
-            // many tokens per thread: their scores take half the registers, so half a batch at a time (the 16
-            // wavefronts of the workgroup hide the LDS latency between them)
-            Entry v[4];
-#pragma unroll
-            for (int dw = 0; dw < 4; ++dw) {
-                const uint32_t word = dw == 0 ? code.x : (dw == 1 ? code.y : (dw == 2 ? code.z : code.w));
-                lookup_half<0>(word, dw, lut, v);
-                __builtin_amdgcn_sched_barrier(0);
-                add_half(dw == 0, v, acc);
-#pragma unroll
-                for (int s = 0; s < HB; ++s) asm volatile("" : "+v"(acc[s]));
-                __builtin_amdgcn_sched_barrier(0);
-                lookup_half<1>(word, dw, lut, v);
-                __builtin_amdgcn_sched_barrier(0);
-                add_half(false, v, acc);
-#pragma unroll
-                for (int s = 0; s < HB; ++s) asm volatile("" : "+v"(acc[s]));
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            if (it >= T) lsc[(it - T) * NT + tid] = make_entry(acc);
         }
-#pragma unroll
-        for (int s = 0; s < HB; ++s) {
-            if (live && s < nh)
-                atomicAdd(&lhist[s * kBins + bin_of_coord(bin_coord_shifted(acc[s], bscale[s], bshift[s]))], 1u);
-            acc[s] = live ? acc[s] : __builtin_nanf("");
-            if (it < T) sc[it < T ? it : 0][s] = acc[s];
-        }
-        if (it >= T) lsc[(it - T) * NT + tid] = make_entry(acc);
-    }
     }
     __syncthreads();
 
@@ -1090,7 +1090,7 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
     } else {
     SIK_TL_ANY(46);
     // ---- 4. last workgroup of head g: candidates, merge, output (groups of 256 threads side by side; every
-    // barrier below is reached by all 1024 threads) ---------------------------------------------------------------
+    // barrier below is reached by all threads of the workgroup) -----------------------------------------------------
     // LDS of this phase (the lists are dead): per group kCandCap + 8 sort keys, kCandCap ranks, kCandCap winners
     uint64_t* const lc = reinterpret_cast<uint64_t*>(dyn) + g * (kCandCap + 8);
     uint32_t* const rank_base = reinterpret_cast<uint32_t*>(reinterpret_cast<uint64_t*>(dyn) + HB * (kCandCap + 8));
@@ -1338,11 +1338,6 @@ static hipError_t launch_step_t(const Dims& d, int T, int nchunk, size_t dyn, co
         SIK_STEP(3, 0)
         SIK_STEP(4, 0)
         SIK_STEP(6, 0)
-        SIK_STEP(8, 0)
-        SIK_STEP(12, 0)
-        SIK_STEP(12, 4)
-        SIK_STEP(14, 4)
-        SIK_STEP(16, 4)
         SIK_STEP_FX(4)
         SIK_STEP_FX(8)
         SIK_STEP_FX(12)

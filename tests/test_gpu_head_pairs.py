@@ -57,6 +57,7 @@ CASES = [
     (16, 8, 56, 18000, 700, "fp16", False),   # 2 + 2 + 2 + 1 heads
     (16, 8, 32, 36864, 1500, "bf16", True),   # two chunks of 18432, the second one full
     (16, 8, 32, 36866, 4, "fp16", True),      # two chunks of 20480
+    (10, 8, 40, 24000, 900, "bf16", True),    # two chunks of 12288, more head blocks of four than half the compute units
 ]
 
 
@@ -114,7 +115,7 @@ ROUTES = [(1, 1, 4, 1024, False, 0, True), (1, 1, 4, 2049, False, 0, False), (8,
           (52, 8, 16, 9500, True, 0, True), (24, 8, 40, 16384, True, 0, False), (17, 8, 40, 8192, True, 0, False),
           (18, 8, 32, 16384, True, 0, True), (9, 8, 40, 16384, True, 0, False), (6, 8, 40, 4096, True, 64, False),
           (6, 8, 40, 3000, True, 64, True), (17, 8, 40, 16384, False, 64, False), (32, 8, 64, 8192, False, 64, True),
-          (24, 8, 40, 8192, False, 64, False)]
+          (24, 8, 40, 8192, False, 64, False), (10, 8, 40, 24000, False, 0, True), (10, 8, 40, 28809, True, 0, False)]
 
 
 @pytest.mark.parametrize("B,Hkv,Hq,capacity,q2,forced,one", ROUTES)

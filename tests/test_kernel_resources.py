@@ -1,4 +1,5 @@
 """Registers and scratch memory of the built kernels, as the compiler recorded them in the library (no GPU needed)."""
+import re
 import struct
 
 import pytest
@@ -73,3 +74,11 @@ def test_two_head_pair_workgroups_share_a_compute_unit():
     assert len(some) == 20
     assert all(k[".vgpr_count"] <= 128 and k[".vgpr_spill_count"] == 0 for k in some.values())
     assert all(k[".group_segment_fixed_size"] + 64 * 1024 <= 80 * 1024 for k in some.values())
+
+
+def test_long_chunks_of_rows_are_built_for_pairs_only():
+    # (tokens per thread in registers, in LDS, 16-bit first pass, records, forced set, heads) of every variant
+    built = {tuple(map(int, re.search(r"step_kernelILi\dELi\dELi(\d+)ELi(\d+)ELb(\d)ELb(\d)ELb(\d)ELi(\d)E", n).groups()))
+             for n in _kernels() if "step_kernel" in n}
+    assert {v[:2] for v in built if v[2:] == (0, 0, 0, 4)} == {(1, 0), (2, 0), (3, 0), (4, 0), (6, 0)}
+    assert {v[:2] for v in built if v[5] == 2} == {(16, 0), (24, 0), (24, 8), (28, 8), (32, 8)}
