@@ -150,7 +150,7 @@ __device__ __forceinline__ Threshold find_threshold(const HistLoads& h, int kk, 
 // scores were written by other workgroups of this launch and are read with agent-scope loads.
 // h256: LDS, 256 words; sh: LDS, 4 words.
 // radix_select_members: the same with the membership test handed in (member(v): does a token with score v compete).
-template <int NT, bool COHERENT, class Member>
+template <int NT, bool COHERENT, bool LANES, class Member>
 __device__ inline void radix_select_members(const float* __restrict__ s, int L, Member member, int need,
                                             int32_t* __restrict__ out, uint32_t* h256, uint32_t* sh) {
     const int tid = threadIdx.x;
@@ -168,12 +168,12 @@ __device__ inline void radix_select_members(const float* __restrict__ s, int L, 
                 atomicAdd(&h256[(key >> (8 * pass)) & 255u], 1u);
         }
         __syncthreads();
-        // The digit at which the count from the top reaches `remaining`.  Larger workgroups, which take several heads or all
-        // of the selection on themselves: four digits to a lane of the first wavefront, a suffix sum over the lanes (equal
-        // scores, 10 x 8 x 2000 in one launch 259 -> 74 us).  The 256 threads that select and attend one head: one thread
-        // walking down the counts, a dependent LDS read each; their kernel runs on every step of one sequence and is 0.2 us
-        // slower with the other form in it though it is not taken (8 layers of 1 x 8 x 32K 195.3 -> 196.8 us).
-        if constexpr (NT == kBlock) {
+        // The digit at which the count from the top reaches `remaining`: four digits to a lane of the first wavefront and a
+        // suffix sum over the lanes, or one thread walking down the counts, a dependent LDS read each.  LANES: the
+        // one-launch step, whose workgroups select for several heads one after the other (equal scores, 10 x 8 x 2000
+        // 259 -> 74 us).  The other kernels run on every step or selection and are slower with that form in them though
+        // they seldom get here (8 layers of 1 x 8 x 32K 195.3 -> 196.8 us, sik_topk of 64 x 20000 16.9 -> 17.0).
+        if constexpr (!LANES) {
             if (tid == 0) {
                 uint32_t cum = 0;
                 int dsel = 0;
@@ -261,7 +261,7 @@ __device__ inline void radix_select_members(const float* __restrict__ s, int L, 
 template <int NT = kBlock, bool COHERENT = false>
 __device__ inline void radix_select_in_bin(const float* __restrict__ s, int L, float lo, float scale, int bstar,
                                            int need, int32_t* __restrict__ out, uint32_t* h256, uint32_t* sh) {
-    radix_select_members<NT, COHERENT>(s, L, [=](float v) { return score_bin(v, lo, scale) == bstar; }, need, out,
+    radix_select_members<NT, COHERENT, false>(s, L, [=](float v) { return score_bin(v, lo, scale) == bstar; }, need, out,
                                        h256, sh);
 }
 

@@ -1178,11 +1178,11 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
             if constexpr (FX)
-                radix_select_members<NT, true>(a.scores + (row0 + s) * a.sstride, L,
+                radix_select_members<NT, true, true>(a.scores + (row0 + s) * a.sstride, L,
                                                          [](float v) { return !is_no_score(v); }, need_s, dst, lhist,
                                                          &lds4[0][0]);
             else
-                radix_select_members<NT, true>(
+                radix_select_members<NT, true, true>(
                     a.scores + (row0 + s) * a.sstride, L,
                     [lo = blo[s], sc_ = bscale[s], bst = sthr[s][0]](float v) {
                         return !(FORCED && is_no_score(v)) && score_bin(v, lo, sc_) == bst;
