@@ -32,8 +32,8 @@ MEASURED_TRAFFIC = {
     ("C4", "step_kernel"): (354539110, "profiles/decode_step_one_launch_C4_C5.md"),
     ("C5", "step_kernel"): (241099674, "profiles/decode_step_one_launch_C4_C5.md"),
 }
-# execution times returned by sik_decode_step_profiled, in launch order: small launches run scoring, then fused
-# selection + attention; large ones run as one launch, reported in the last slot and named step_kernel here
+# execution times returned by sik_decode_step_profiled, in launch order: steps run as scoring, then fused selection +
+# attention, or, short and large ones, as one launch, reported in the last slot and named step_kernel here
 KERNELS = ("prep_kernel", "score_kernel", "select_kernel", "select_attend_kernel")
 
 

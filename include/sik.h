@@ -93,8 +93,9 @@ int sik_version(void);
  * is beyond that path), [6] tokens per such chunk, [7] tokens of a chunk of the one-launch decode step on
  * the current device, in units of 1024 (0: no one-launch plan fits this layout, the step always runs as separate
  * launches; sik_decode_step takes the one-launch step for large launches and wherever one chunk per head, which may
- * then be longer, covers the context and fills enough of the device; sik_decode_args.launches chooses).  Every chunk holds at most 64512 tokens and there are at most 64 per head; a layout that cannot be cut
- * that way is SIK_ERR_SHAPE here and in every other call. */
+ * then be longer, covers the context and pays; sik_decode_args.launches chooses).  Every chunk holds at most 64512
+ * tokens and there are at most 64 per head; a layout that cannot be cut that way is SIK_ERR_SHAPE here and in every
+ * other call. */
 #define SIK_PLAN_INFO_LEN 8
 int sik_plan_info(const sik_layout *layout, int32_t *info);
 
