@@ -95,13 +95,14 @@ __device__ __forceinline__ uint32_t group_suffix_sum(uint32_t v, uint32_t* lds4)
     return v;
 }
 
-constexpr int kRankSole = 512;
+constexpr int kRankSole = 512;  // threshold-bin candidates that a workgroup finishing its heads alone ranks
 
-// What stands among a head's scores in memory for a token that does not compete: a NaN of a pattern that no sum has (and
-// the lowest sort key there is).
+// What stands among a head's scores in memory for a token that does not compete: the NaN of the lowest sort key.  A score
+// can be that NaN too (a centroid of these bits goes through the sums) and is written as its neighbour: as_score.
 constexpr uint32_t kNoScoreBits = 0xffffffffu;
 __device__ __forceinline__ float no_score() { return __uint_as_float(kNoScoreBits); }
 __device__ __forceinline__ bool is_no_score(float v) { return __float_as_uint(v) == kNoScoreBits; }
+__device__ __forceinline__ float as_score(float v) { return __uint_as_float(min(__float_as_uint(v), kNoScoreBits - 1u)); }
 
 __device__ __forceinline__ float uniform(float x) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
@@ -721,7 +722,7 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
                     for (int s = 0; s < HB; ++s) {
                         if (crowded[s]) {
                             const bool member = ((gmask[s][0] & ~smask[s][0]) >> (TT - 1 - it)) & 1u;
-                            st_agent(&a.scores[(row0 + s) * a.sstride + tok], member ? exact_score(lut, code, s) : no_score());
+                            st_agent(&a.scores[(row0 + s) * a.sstride + tok], member ? as_score(exact_score(lut, code, s)) : no_score());
                         }
                     }
                 }
@@ -792,7 +793,7 @@ __global__ __launch_bounds__(step_threads(HB), 4) void step_kernel(
 #pragma unroll
                 for (int s = 0; s < HB; ++s)
                     if (crowded[s] && tok < end)
-                        st_agent(&a.scores[(row0 + s) * a.sstride + tok], out ? no_score() : v[s]);
+                        st_agent(&a.scores[(row0 + s) * a.sstride + tok], out ? no_score() : (FORCED ? as_score(v[s]) : v[s]));
             });
         }
     }

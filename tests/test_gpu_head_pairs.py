@@ -198,3 +198,15 @@ def test_query_that_is_not_finite(B, Hkv, Hq, L, q2, launches, forced):
         assert torch.equal(got[1], want[1]) and int(got[1].min()) >= -1
         bad = 3 if forced else 4
         assert torch.equal(got[0][:, :bad], want[0][:, :bad])  # no number comes out of these rows: zero either way
+
+
+@pytest.mark.parametrize("launches,forced", [(1, 16), (3, 0)], ids=["forced", "first pass of 16 bits"])
+def test_scores_with_the_bits_of_a_token_that_does_not_compete(launches, forced):
+    # every score is the NaN that marks such tokens: all are equal, so the lowest indices are taken, forced ones first
+    s = build(3, 2, 8, 4000, [4000, 3999, 1025 + forced], 300, "bf16", seed=11)
+    s["cb"].view(torch.int32).fill_(-1)
+    named = (3 * torch.arange(forced, device="cuda", dtype=torch.int32)).repeat(3, 2, 1).contiguous() if forced else None
+    got = step(s, 300, launches, False, s["q"], forced=named)
+    taken = set(range(0, 3 * forced, 3))
+    want = sorted(taken) + [i for i in range(300 + forced) if i not in taken][:300 - forced]
+    assert torch.equal(got[1], torch.tensor(sorted(want), dtype=torch.int32, device="cuda").expand_as(got[1]))
